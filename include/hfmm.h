@@ -128,7 +128,7 @@ typedef struct fmm_stats {
     int64_t n_m2l_by_order[7]; /* learned selector: accepted pairs at order 2..8 (else 0) */
     int64_t p2p_evaluated;     /* particle pairs the P2P kernel evaluated: the listed pairs less
                                   those of source leaves whose particles' bounding box is
-                                  farther than r_cut from the sink leaf's (FP32 form) */
+                                  farther than r_cut from the sink leaf's */
     /* stage spans (with timing on; stages on the two streams overlap); under schedule 2
        t_m2l_ms and t_p2p_ms are both the span of the one P2P + M2L launch */
     double t_tree_ms, t_upward_ms, t_traverse_ms, t_m2l_ms, t_p2p_ms, t_downward_ms, t_total_ms;

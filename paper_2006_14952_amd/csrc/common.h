@@ -81,7 +81,6 @@ struct P2PConst {
     int split;             // 0: Gaussian split; 1: polynomial split (c[0] = 1 / r_cut, see p2p_setup)
     float two_over_rc2;
     float rc2;
-    double rs, rc2d;
 };
 
 // ---------------------------------------------------------------------------

@@ -12,7 +12,9 @@
 // 7.83 ms at n_crit 48, 16.7M box 56.7 -> 51.6 ms and 134M box 480 -> 430 ms at n_crit 96
 // (chunks of 16: 1% slower).
 //
-// FP64 form: absolute FP64 positions, erfc/exp from the device math library.
+// FP64 form: absolute FP64 positions, and for r_cut up to 5 r_s the same split of the force
+// law, f_(1) = -1/r^3 + S(t)/(8 r_s^3), with S of degree 18 or 22 fitted to FP64 rounding
+// (beyond that erfc and exp of the device math library); sums in FP64.
 // FP32 form: FP32 coordinates relative to each particle's leaf centre, the exact
 // centre offset c_B + s box - c_A added when staging, and
 //   f_(1)(r) = -1/r^3 + S(t)/(8 r_s^3),  t = 2 r^2/r_cut^2 - 1,
@@ -20,9 +22,9 @@
 // polynomial of degree 9, 10 or 14 fitted on the host, the lowest that meets the FP32
 // tolerance at this r_cut / r_s <= 6 (its coefficients carry the factor 1/(8 r_s^3));
 // the sum of each staged block is added to a Kahan-compensated per-particle accumulator.
-// A listed source leaf whose particles' bounding box lies farther than r_cut from the sink
-// leaf's box, and any single source particle farther than r_cut from that box, hold no
-// pair inside the cutoff and are not staged (the lists themselves are unchanged).
+// Both forms: a listed source leaf whose particles' bounding box lies farther than r_cut from
+// the sink leaf's box, and any single source particle farther than r_cut from that box, hold
+// no pair inside the cutoff and are not staged (the lists themselves are unchanged).
 #include <math.h>
 
 #include <algorithm>
@@ -33,18 +35,6 @@
 #include "expand_impl.h"
 
 namespace hfmm {
-
-// largest e in [0, ne) with pref[e] <= slot (pref non-decreasing, pref[0] = 0)
-__device__ __forceinline__ int find_entry(const int *pref, int ne, int slot)
-{
-    int lo = 0, hi = ne - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (pref[mid] <= slot) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
 
 struct P2PArgs {
     const Cell *cells;
@@ -60,7 +50,7 @@ struct P2PArgs {
     double *nearf;  // 3 x n SoA
     int n;
     unsigned long long *pairs;  // listed particle pairs (sum of n_A n_B over P2P leaf pairs)
-    unsigned long long *evaluated;  // particle pairs actually evaluated (FP32 form: after the box test)
+    unsigned long long *evaluated;  // particle pairs actually evaluated (after the box tests)
     const float4 *bbox;             // per cell: lo, hi of the particles relative to the cell centre
     int first;                      // k_p2p: block b takes sink leaf leaves[first + b]
     const int *err;                 // k_p2p: if non-NULL and non-zero, the lists are void: do nothing
@@ -97,7 +87,26 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v)
     s = t;
 }
 
-constexpr int kStage = 256;
+constexpr int kStage = 256;  // FP32 form; the FP64 form's 32-byte records are staged 128 at a time
+template <bool F64> constexpr int stage_slots() { return F64 ? 128 : kStage; }
+
+// FP64 force-law constants: f_(1) = -1/r^3 + S(t)/(8 r_s^3) as in the FP32 form, S fitted to
+// FP64 rounding.  S's terms are summed from the smallest, so the sum is good to a few units
+// of 1e-16 of 1/r^3, which is what the particles' forces are rounded to by their nearest
+// pairs anyway.  Accelerations of 4096 particles against extended precision (median, 99th
+// percentile of the relative error, means of four boxes): uniform 2.3e-16 and 1.1e-15, clustered
+// 2.0e-16 and 1.5e-15; the erfc/exp form on unshifted coordinates 2.8e-16 and 3.8e-15,
+// 2.1e-16 and 2.4e-15.
+// Fits exist up to kP2PFit64Cut: there r^3 f_(1) has fallen to 1/170 at the cutoff; past it
+// the cancellation would show in the forces of isolated particles, and erfc/exp are used.
+constexpr int kP2PPoly64Max = 23;
+constexpr double kP2PFit64Cut = 5.0;
+struct P2PConst64 {
+    double c[kP2PPoly64Max];  // S(t) / (8 r_s^3), coefficients of t^0 .. t^(ncoef-1)
+    double two_over_rc2, rc2, rs, irc2, irc3;
+    float rc;   // for the box tests
+    int ncoef;  // 19 or 23; 0: no fit (erfc and exp)
+};
 // Sink particles per pass over a leaf's list unless fmm_params.p2p_chunk names 16 or 64: a
 // leaf of more is processed in Morton-ordered chunks of this many, each tested against the
 // box of its own particles.
@@ -122,26 +131,60 @@ __device__ __forceinline__ float wave_maxf(float v)
 // in FP32, the factored form does not.
 // Shared memory of one sink leaf's P2P (one 64-lane wave).
 template <bool F64> struct P2PShared {
-    using R = typename std::conditional<F64, double, float>::type;
     using V4 = typename std::conditional<F64, double4, float4>::type;
-    V4 src[kStage];
-    int ebeg[64], epref[64];
-    int smark[kStage];
-    R eoff[64][3];
+    V4 src[stage_slots<F64>()];
+    V4 eoff[64 + 1];        // offset of the entry's records; the last is never read for a slot in use
+    int ebase[64], epref[64];  // particle index less slot, first slot of the entry
+    int smark[stage_slots<F64>()];
 };
 
 // P2P of sink leaf `leaves[li]`.
 // CHUNK: the sink tile (16, 32 or 64 particles), a compile-time constant: a tile read at
 // run time (from P2PConst, or as an extra kernel argument) changed the register allocation
 // of the pair loop and cost 0.8-1.1% of the 134M box's P2P time.
-template <bool F64, bool POLY, int NPC, int CHUNK>
-__device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PConst &k, int li, P2PShared<F64> &sh)
+template <bool F64> using P2PLaw = typename std::conditional<F64, P2PConst64, P2PConst>::type;
+
+// One pair of the FP64 form: the weight m f_(1)(r), zero outside 0 < r^2 < r_cut^2.
+// 1/r^3 from the hardware's estimate y of 1/r (about 23 bits), cut to 26 bits so that y^2 and
+// with it the residual e = 1 - r^2 y^2 are exact: y^3 and one second-order correction then
+// carry three roundings, no more than a square root, a product and a division.  The self
+// pair's NaN is dropped by the select.
+template <bool POLY, int NPC>
+__device__ __forceinline__ double pair_weight64(const P2PConst64 &k, double r2, double m)
 {
+    const bool in = r2 > 0.0 && r2 < k.rc2;
+    if constexpr (!POLY && NPC == 0) {
+        const double rr2 = in ? r2 : 1.0, r = sqrt(rr2), u = r * (0.5 / k.rs);
+        const double h = erfc(u) + r * (1.0 / (k.rs * 1.7724538509055160273)) * exp(-u * u);
+        return in ? -m * h / (rr2 * r) : 0.0;
+    } else {
+        double y = __builtin_amdgcn_rsq(r2);
+        y = __longlong_as_double(__double_as_longlong(y) & ~0x7ffffffll);
+        const double y2 = y * y, y3 = y2 * y, e = fma(-r2, y2, 1.0);
+        const double q = fma(1.875, e, 1.5) * e;  // 1/r^3 = y^3 (1 - e)^(-3/2)
+        double S;
+        if constexpr (POLY) {  // -1/r^3 + 5/(2 r_c^3) - 3 r^2/(2 r_c^5)
+            S = k.irc3 * fma(-1.5 * k.irc2, r2, 2.5);
+        } else {
+            const double t = fma(r2, k.two_over_rc2, -1.0);
+            S = k.c[NPC - 1];
+#pragma unroll
+            for (int c = NPC - 2; c >= 0; --c) S = fma(S, t, k.c[c]);
+        }
+        const double f1 = fma(-y3, q, S - y3);
+        return in ? m * f1 : 0.0;
+    }
+}
+
+template <bool F64, bool POLY, int NPC, int CHUNK>
+__device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k, int li, P2PShared<F64> &sh)
+{
+    constexpr int kStage = stage_slots<F64>();
     using R = typename std::conditional<F64, double, float>::type;
     using V4 = typename std::conditional<F64, double4, float4>::type;
     V4 *src = sh.src;
-    int *ebeg = sh.ebeg, *epref = sh.epref, *smark = sh.smark;
-    R(*eoff)[3] = sh.eoff;
+    V4 *eoff = sh.eoff;
+    int *ebase = sh.ebase, *epref = sh.epref, *smark = sh.smark;
     const int lane = threadIdx.x;
     const uint64_t lt = (1ull << lane) - 1ull;
     const int A = a.leaves[li];
@@ -151,71 +194,99 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PConst &k, in
     const int nA = ca.end - ca.beg;
     const int nlist = a.cnt[A];
     unsigned long long npairs = 0, nevald = 0;
-    float4 alo = make_float4(0, 0, 0, 0), ahi = alo;
-    if constexpr (!F64) {
-        alo = a.bbox[2 * (size_t)A];
-        ahi = a.bbox[2 * (size_t)A + 1];
+    float4 alo = a.bbox[2 * (size_t)A], ahi = a.bbox[2 * (size_t)A + 1];
+    // FP64 form: the boxes are FP32 and relative to their leaves, so their rounding grows with
+    // the leaves' sides, however small the cutoff: the tests' margin does too
+    float cutA = 0.0f;
+    // FP64 form: its coordinates count from the box's far face along an axis where the cutoff
+    // reaches past that face: an image x + box would be rounded to the last place of box, while
+    // x - box of the particles beside the face is exact
+    double Ox = 0.0, Oy = 0.0, Oz = 0.0;
+    if constexpr (F64) {
+        cutA = k.rc * 1.0001f + 1e-6f * (float)hA;
+        const double face = a.box - (double)k.rc - hA;
+        Ox = cax > face ? a.box : 0.0;
+        Oy = cay > face ? a.box : 0.0;
+        Oz = caz > face ? a.box : 0.0;
     }
 
     for (int ib = 0; ib < nA; ib += CHUNK) {
         const int ns = min(CHUNK, nA - ib);
         const int G = 64 / ns, g = lane / ns, si = lane - g * ns;
-        if constexpr (!F64) {
-            if (nA > CHUNK) {  // one chunk of the leaf: the box of its own particles
-                const float4 me = a.rel[ca.beg + ib + (lane < ns ? lane : 0)];
-                alo = make_float4(wave_minf(me.x), wave_minf(me.y), wave_minf(me.z), 0.0f);
-                ahi = make_float4(wave_maxf(me.x), wave_maxf(me.y), wave_maxf(me.z), 0.0f);
-            }
+        if (nA > CHUNK) {  // one chunk of the leaf: the box of its own particles
+            const float4 me = a.rel[ca.beg + ib + (lane < ns ? lane : 0)];
+            alo = make_float4(wave_minf(me.x), wave_minf(me.y), wave_minf(me.z), 0.0f);
+            ahi = make_float4(wave_maxf(me.x), wave_maxf(me.y), wave_maxf(me.z), 0.0f);
         }
         const bool valid = g < G;
         const int i = ca.beg + ib + (valid ? si : 0);
         R xi, yi, zi;
         if constexpr (F64) {
-            xi = a.xs[i]; yi = a.ys[i]; zi = a.zs[i];
+            xi = a.xs[i] - Ox; yi = a.ys[i] - Oy; zi = a.zs[i] - Oz;
         } else {
             float4 me = a.rel[i];
             xi = me.x; yi = me.y; zi = me.z;
         }
+        // the sink's load ends here: left to its first use, inside the pair loop, it would make
+        // that loop wait for the next stage's records too
+        asm volatile("" : "+v"(xi), "+v"(yi), "+v"(zi));
         double ax = 0, ay = 0, az = 0;              // FP64 form
         float sx = 0, sy = 0, sz = 0, cx = 0, cy = 0, cz = 0;  // FP32 form (Kahan)
+        // the list is read a chunk ahead: the next chunk's items are on their way while the
+        // current chunk's sources are summed
         int chunk = a.head[A];
+        uint32_t it = lane < nlist ? a.items[(size_t)chunk * kChunk + lane] : 0u;
         for (int eb = 0; eb < nlist; eb += 64) {
             const int ne = min(64, nlist - eb);
-            int cntj = 0, listed = 0;
+            const bool more = eb + 64 < nlist;
+            int nchunk = 0;
+            if (more) nchunk = a.next[chunk];
+            int cntj = 0, listed = 0, jbeg = 0;
             if (lane < ne) {
-                uint32_t it = a.items[(size_t)chunk * kChunk + lane];
                 int s = (int)(it & 31);
                 Cell cb = a.cells[it >> 5];
                 cntj = listed = cb.end - cb.beg;
-                ebeg[lane] = cb.beg;
+                jbeg = cb.beg;
                 double shx = (double)(s / 9 - 1) * a.box, shy = (double)((s / 3) % 3 - 1) * a.box,
                        shz = (double)(s % 3 - 1) * a.box;
+                // exact in FP64: dyadic centres and integer image shifts
+                double hB = ldexp(a.box, -cell_level(cb));
+                const float ox = (float)((cell_ix(cb) + 0.5) * hB + shx - cax);
+                const float oy = (float)((cb.iy + 0.5) * hB + shy - cay);
+                const float oz = (float)((cb.iz + 0.5) * hB + shz - caz);
+                if constexpr (F64) eoff[lane] = make_double4(shx - Ox, shy - Oy, shz - Oz, 0.0);
+                else eoff[lane] = make_float4(ox, oy, oz, 0.0f);
+                // gap between the two boxes; the margin covers FP32 rounding many times over
+                const float4 blo = a.bbox[2 * (size_t)(it >> 5)], bhi = a.bbox[2 * (size_t)(it >> 5) + 1];
+                const float gx = fmaxf(0.0f, fmaxf(alo.x - (bhi.x + ox), (blo.x + ox) - ahi.x));
+                const float gy = fmaxf(0.0f, fmaxf(alo.y - (bhi.y + oy), (blo.y + oy) - ahi.y));
+                const float gz = fmaxf(0.0f, fmaxf(alo.z - (bhi.z + oz), (blo.z + oz) - ahi.z));
+                float far2;
                 if constexpr (F64) {
-                    eoff[lane][0] = shx; eoff[lane][1] = shy; eoff[lane][2] = shz;
-                } else {  // exact in FP64: dyadic centres and integer image shifts
-                    double hB = ldexp(a.box, -cell_level(cb));
-                    const float ox = (float)((cell_ix(cb) + 0.5) * hB + shx - cax);
-                    const float oy = (float)((cb.iy + 0.5) * hB + shy - cay);
-                    const float oz = (float)((cb.iz + 0.5) * hB + shz - caz);
-                    eoff[lane][0] = ox; eoff[lane][1] = oy; eoff[lane][2] = oz;
-                    // gap between the two boxes; the margin covers FP32 rounding many times over
-                    const float4 blo = a.bbox[2 * (size_t)(it >> 5)], bhi = a.bbox[2 * (size_t)(it >> 5) + 1];
-                    const float gx = fmaxf(0.0f, fmaxf(alo.x - (bhi.x + ox), (blo.x + ox) - ahi.x));
-                    const float gy = fmaxf(0.0f, fmaxf(alo.y - (bhi.y + oy), (blo.y + oy) - ahi.y));
-                    const float gz = fmaxf(0.0f, fmaxf(alo.z - (bhi.z + oz), (blo.z + oz) - ahi.z));
-                    if (gx * gx + gy * gy + gz * gz > k.rc2 * 1.0001f) cntj = 0;
+                    const float cut = cutA + 1e-6f * (float)hB;
+                    far2 = cut * cut;
+                } else {
+                    far2 = k.rc2 * 1.0001f;
                 }
+                if (gx * gx + gy * gy + gz * gz > far2) cntj = 0;
             }
             const int incl = wave_incl_sum(cntj);
-            if (lane < ne) epref[lane] = incl - cntj;
+            if (lane < ne) {
+                epref[lane] = incl - cntj;
+                ebase[lane] = jbeg - (incl - cntj);
+            }
+            if (more) {
+                chunk = nchunk;
+                it = lane < nlist - eb - 64 ? a.items[(size_t)chunk * kChunk + lane] : 0u;
+            }
             const int total = __builtin_amdgcn_readlane(incl, 63);
-            const int ltot = F64 ? total : __builtin_amdgcn_readlane(wave_incl_sum(listed), 63);
+            const int ltot = __builtin_amdgcn_readlane(wave_incl_sum(listed), 63);
             npairs += (unsigned long long)ns * (unsigned)ltot;
             __syncthreads();
-            // FP32: the source records of a stage are loaded into registers one stage
-            // ahead, so their latency is covered by the pair work of the current stage
+            // the source records of a stage are loaded into registers one stage ahead, so
+            // their latency is covered by the pair work of the current stage
             constexpr int kPer = kStage / 64;
-            float4 rv[kPer];
+            V4 rv[kPer];
             int ev[kPer];
             // slot -> list entry for the kStage slots from sbase: each entry marks the slot it
             // starts at (the largest entry wins, so entries left empty by the box test are
@@ -244,76 +315,72 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PConst &k, in
                 const int incl = wave_incl_max(m);
                 const int prev = wave_shift_up1(incl);
                 const int base = max(prev, efirst + 1);
+                // every address first, then the loads back to back: a load under its own
+                // branch waits for the one before it (lanes past the end load record 0)
+                int jv[kPer];
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) jv[u] = ebase[max(base, mrun[u]) - 1];
 #pragma unroll
                 for (int u = 0; u < kPer; ++u) {
                     const int q = kPer * lane + u;
-                    ev[u] = -1;
-                    if (q < nraw) {
-                        const int e = max(base, mrun[u]) - 1;
-                        ev[u] = e;
-                        rv[u] = a.rel[ebeg[e] + sbase + q - epref[e]];
-                    }
+                    ev[u] = q < nraw ? max(base, mrun[u]) - 1 : 64;
+                    jv[u] = q < nraw ? jv[u] + sbase + q : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    if constexpr (F64) rv[u] = make_double4(a.xs[jv[u]], a.ys[jv[u]], a.zs[jv[u]], a.ms[jv[u]]);
+                    else rv[u] = a.rel[jv[u]];
                 }
                 ecarry = __builtin_amdgcn_readlane(ev[kPer - 1], 63);
             };
-            if (!F64 && total > 0) fetch(0);
+            if (total > 0) fetch(0);
             for (int sb = 0; sb < total; sb += kStage) {
-                const int nraw = min(kStage, total - sb);
-                int nst = nraw;
-                if constexpr (F64) {
-                    for (int q = lane; q < nraw; q += 64) {
-                        int slot = sb + q;
-                        int e = find_entry(epref, ne, slot);
-                        int j = ebeg[e] + slot - epref[e];
-                        src[q] = make_double4(a.xs[j] + eoff[e][0], a.ys[j] + eoff[e][1], a.zs[j] + eoff[e][2], a.ms[j]);
-                    }
-                } else {
-                    // a source particle farther than r_cut from the sink leaf's box meets no
-                    // sink particle inside the cutoff: it is not staged (ballot compaction)
-                    nst = 0;
+                // a source particle farther than r_cut from the sink leaf's box meets no
+                // sink particle inside the cutoff: it is not staged (ballot compaction)
+                int nst = 0;
 #pragma unroll
-                    for (int u = 0; u < kPer; ++u) {
-                        bool keep = false;
-                        float4 sv = make_float4(0, 0, 0, 0);
-                        if (ev[u] >= 0) {
-                            const int e = ev[u];
-                            sv = make_float4(rv[u].x + eoff[e][0], rv[u].y + eoff[e][1], rv[u].z + eoff[e][2], rv[u].w);
-                            const float gx = fmaxf(0.0f, fmaxf(alo.x - sv.x, sv.x - ahi.x));
-                            const float gy = fmaxf(0.0f, fmaxf(alo.y - sv.y, sv.y - ahi.y));
-                            const float gz = fmaxf(0.0f, fmaxf(alo.z - sv.z, sv.z - ahi.z));
-                            keep = gx * gx + gy * gy + gz * gz <= k.rc2 * 1.0001f;
-                        }
-                        const uint64_t km = __ballot(keep);
-                        if (keep) src[nst + __popcll(km & lt)] = sv;
-                        nst += __popcll(km);
+                for (int u = 0; u < kPer; ++u) {
+                    const V4 eo = eoff[ev[u]];
+                    V4 sv;
+                    sv.x = rv[u].x + eo.x;
+                    sv.y = rv[u].y + eo.y;
+                    sv.z = rv[u].z + eo.z;
+                    sv.w = rv[u].w;
+                    float px, py, pz, far2;  // the source relative to the sink leaf's centre
+                    if constexpr (F64) {
+                        px = (float)(sv.x - (cax - Ox)); py = (float)(sv.y - (cay - Oy)); pz = (float)(sv.z - (caz - Oz));
+                        far2 = cutA * cutA;
+                    } else {
+                        px = sv.x; py = sv.y; pz = sv.z;
+                        far2 = k.rc2 * 1.0001f;
                     }
-                    if (sb + kStage < total) fetch(sb + kStage);
+                    const float gx = fmaxf(0.0f, fmaxf(alo.x - px, px - ahi.x));
+                    const float gy = fmaxf(0.0f, fmaxf(alo.y - py, py - ahi.y));
+                    const float gz = fmaxf(0.0f, fmaxf(alo.z - pz, pz - ahi.z));
+                    const bool keep = ev[u] < 64 && gx * gx + gy * gy + gz * gz <= far2;
+                    const uint64_t km = __ballot(keep);
+                    if (keep) src[nst + __popcll(km & lt)] = sv;
+                    nst += __popcll(km);
                 }
+                if (sb + kStage < total) fetch(sb + kStage);
                 nevald += (unsigned long long)ns * (unsigned)nst;
                 __syncthreads();
                 if (valid) {
                     if constexpr (F64) {
-                        const double rc2 = k.rc2d, inv2rs = 0.5 / k.rs, c1 = 1.0 / (k.rs * 1.7724538509055160273);
-                        const double irc2 = 1.0 / rc2, irc3 = irc2 / sqrt(rc2);
-                        for (int q = g; q < nst; q += G) {
-                            const double4 s = src[q];
-                            double dx = xi - s.x, dy = yi - s.y, dz = zi - s.z;
-                            double r2 = dx * dx + dy * dy + dz * dz;
-                            bool in = r2 > 0.0 && r2 < rc2;
-                            double rr2 = in ? r2 : 1.0;
-                            double r = sqrt(rr2);
-                            double w;
-                            if (k.split == 1) {  // -1/r^3 + 5/(2 r_c^3) - 3 r^2/(2 r_c^5)
-                                w = in ? s.w * (-1.0 / (rr2 * r) + irc3 * (2.5 - 1.5 * rr2 * irc2)) : 0.0;
-                            } else {
-                                double u = r * inv2rs;
-                                double h = erfc(u) + r * c1 * exp(-u * u);
-                                w = in ? -s.w * h / (rr2 * r) : 0.0;
-                            }
+                        auto pair = [&](const double4 s) __attribute__((always_inline)) {
+                            const double dx = xi - s.x, dy = yi - s.y, dz = zi - s.z;
+                            const double w = pair_weight64<POLY, NPC>(k, dx * dx + dy * dy + dz * dz, s.w);
                             ax += w * dx;
                             ay += w * dy;
                             az += w * dz;
+                        };
+                        int q = g;
+                        for (; q + G < nst; q += 2 * G) {  // two sources per step
+                            const double4 s0 = src[q], s1 = src[q + G];
+                            pair(s0);
+                            pair(s1);
                         }
+                        if (q < nst) pair(src[q]);
                     } else {
                         float px = 0, py = 0, pz = 0;
                         // the leading coefficient as a vector operand: each Horner step then
@@ -363,7 +430,6 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PConst &k, in
                 }
                 __syncthreads();
             }
-            if (eb + 64 < nlist) chunk = a.next[chunk];
         }
         if constexpr (!F64) {
             ax = (double)sx - (double)cx;
@@ -395,8 +461,18 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PConst &k, in
     }
 }
 
+// FP32 form: bound by FP32 issue, 25 operations a pair; the records of a stage and the items
+// of the next list chunk are loaded ahead, every load of a stage issued before the first wait
+// (a load under its own branch waited for the one before it, and the sink's own load for all
+// of them: 300,007 particles, polynomial split, step 3.50 -> 3.33 ms; 2M 8.13 -> 8.01 ms; 64-box
+// forest 11.77 -> 11.46 ms).
+// FP64 form: bound by FP64 issue, 42 operations a pair with the degree-18 law against well over
+// 200 of erfc, exp, the square root and the division, on the pairs the box tests leave (62% of
+// the listed ones on the 2M box) at four waves per SIMD instead of three: uniform 32^3 step
+// 1.21 -> 0.83 ms, 262,144 clustered step 9.0 -> 4.5 ms.
 template <bool F64, bool POLY, int NPC, int CHUNK>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(F64 ? 2 : 5))) void k_p2p(P2PArgs a, P2PConst k)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(F64 ? (NPC ? 4 : 2) : 5))) void k_p2p(P2PArgs a,
+                                                                                                   P2PLaw<F64> k)
 {
     __shared__ P2PShared<F64> sh;
     if (a.err && *a.err) return;  // the traversal overflowed: it reruns, and so does P2P
@@ -534,17 +610,87 @@ int p2p_setup(const fmm_params *P, P2PConst &k)
     if (P->split == 1) k.c[0] = (float)(1.0 / P->r_cut);  // polynomial split: the FP32 kernel needs 1 / r_cut only
     k.two_over_rc2 = (float)(2.0 / (P->r_cut * P->r_cut));
     k.rc2 = (float)(P->r_cut * P->r_cut);
-    k.rs = P->r_s;
-    k.rc2d = P->r_cut * P->r_cut;
     return 0;
 }
 
 
 
-// The FP32 form's leaf bounding boxes (they depend on the tree only).
-int p2p_bbox(fmm_tree *t, const fmm_params *P, hipStream_t st)
+// S(v) in extended precision: sum (-1)^k v^k / (k! (2k+3)), whose terms stay below e^v.
+static long double S_of_v_ext(long double v)
 {
-    if (t->nleaf == 0 || !P->precision) return 0;
+    long double s = 0, term = 1;
+    for (int k = 0; k < 80; ++k) {
+        s += term / (2 * k + 3);
+        term *= -v / (k + 1);
+    }
+    return 4.0L / sqrtl(3.14159265358979323846264338327950288L) * s;
+}
+
+// Interpolation of S at the m Chebyshev points through its Chebyshev series, rewritten in
+// powers of t, in extended precision; returns the largest error of the rounded coefficients
+// in r^3 f_(1) (as fit_error).
+static double fit_S64(double vcut, int m, double *coef)
+{
+    const long double pi = 3.14159265358979323846264338327950288L;
+    long double f[kP2PPoly64Max], mono[kP2PPoly64Max] = {0};
+    for (int k = 0; k < m; ++k) f[k] = S_of_v_ext((cosl(pi * (k + 0.5L) / m) + 1.0L) * 0.5L * vcut);
+    long double t0[kP2PPoly64Max] = {1}, t1[kP2PPoly64Max] = {0, 1}, t2[kP2PPoly64Max];
+    for (int j = 0; j < m; ++j) {
+        long double cj = 0;
+        for (int k = 0; k < m; ++k) cj += f[k] * cosl(pi * j * (k + 0.5L) / m);
+        cj *= (j ? 2.0L : 1.0L) / m;
+        for (int q = 0; q < m; ++q) mono[q] += cj * t0[q];
+        for (int q = 0; q < m; ++q) t2[q] = (q ? 2.0L * t1[q - 1] : 0.0L) - t0[q];  // T_(j+2)
+        for (int q = 0; q < m; ++q) {
+            t0[q] = t1[q];
+            t1[q] = t2[q];
+        }
+    }
+    for (int j = 0; j < m; ++j) coef[j] = (double)mono[j];
+    double worst = 0.0;
+    for (int i = 0; i <= 400; ++i) {
+        const long double t = -1.0L + i / 200.0L, v = (t + 1.0L) * 0.5L * vcut;
+        long double S = coef[m - 1];
+        for (int j = m - 2; j >= 0; --j) S = S * t + coef[j];
+        worst = std::max(worst, (double)(fabsl(S - S_of_v_ext(v)) * v * sqrtl(v)));
+    }
+    return worst;
+}
+
+// FP64 constants: the shorter fit whose error stays within FP64 rounding (19 coefficients
+// serve r_cut up to about 4.5 r_s, 23 up to 5 r_s), else none.  The last fit is kept, by its
+// vcut alone.
+static void p2p_setup64(const fmm_params *P, P2PConst64 &k)
+{
+    constexpr double kTol = 2.0e-16;
+    static std::mutex mu;
+    static double cached_vcut = -1.0, cached[kP2PPoly64Max];
+    static int cached_m = 0;
+    k = P2PConst64{};
+    k.rs = P->r_s;
+    k.rc2 = P->r_cut * P->r_cut;
+    k.rc = (float)P->r_cut;
+    k.two_over_rc2 = 2.0 / k.rc2;
+    k.irc2 = 1.0 / k.rc2;
+    k.irc3 = k.irc2 / P->r_cut;
+    if (P->split == 1 || P->r_cut > kP2PFit64Cut * P->r_s) return;
+    const double vcut = k.rc2 / (4.0 * P->r_s * P->r_s);
+    std::lock_guard<std::mutex> lk(mu);
+    if (vcut != cached_vcut) {
+        cached_m = 0;
+        for (int m : {19, kP2PPoly64Max})
+            if (!cached_m && fit_S64(vcut, m, cached) <= kTol) cached_m = m;
+        cached_vcut = vcut;
+    }
+    k.ncoef = cached_m;
+    const double inv8rs3 = 1.0 / (8.0 * P->r_s * P->r_s * P->r_s);
+    for (int j = 0; j < cached_m; ++j) k.c[j] = cached[j] * inv8rs3;
+}
+
+// The leaves' bounding boxes (they depend on the tree only).
+int p2p_bbox(fmm_tree *t, const fmm_params *, hipStream_t st)
+{
+    if (t->nleaf == 0) return 0;
     if (int rc = grow(t->bbox, (size_t)t->ncell * 32)) return rc;
     k_leaf_bbox<<<(t->nleaf + 63) / 64, 64, 0, st>>>(ptr<Cell>(t->cells), ptr<int>(t->leaves), t->nleaf,
                                                     ptr<float4>(t->rel32), ptr<float4>(t->bbox));
@@ -664,29 +810,41 @@ int p2p_m2l_fused_launch(fmm_tree *t, const fmm_params *P, hipStream_t st)
 template <int CHUNK>
 static void launch_p2p(const fmm_params *P, const P2PConst &k, const P2PArgs &a, int count, hipStream_t st)
 {
-    if (P->precision && P->split == 1) k_p2p<false, true, 11, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (P->precision && k.ncoef == 10) k_p2p<false, false, 10, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (P->precision && k.ncoef == 11) k_p2p<false, false, 11, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (P->precision) k_p2p<false, false, 15, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else k_p2p<true, false, 11, CHUNK><<<count, 64, 0, st>>>(a, k);
+    if (P->split == 1) k_p2p<false, true, 11, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else if (k.ncoef == 10) k_p2p<false, false, 10, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else if (k.ncoef == 11) k_p2p<false, false, 11, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else k_p2p<false, false, 15, CHUNK><<<count, 64, 0, st>>>(a, k);
+}
+
+template <int CHUNK>
+static void launch_p2p64(const fmm_params *P, const P2PConst64 &k, const P2PArgs &a, int count, hipStream_t st)
+{
+    if (P->split == 1) k_p2p<true, true, 1, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else if (k.ncoef == 19) k_p2p<true, false, 19, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else if (k.ncoef == 23) k_p2p<true, false, 23, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else k_p2p<true, false, 0, CHUNK><<<count, 64, 0, st>>>(a, k);
 }
 
 int p2p_range(fmm_tree *t, const fmm_params *P, int first, int count, const int *err, hipStream_t st)
 {
     if (count <= 0) return 0;
     if (first < 0 || count > t->nleaf - first) return set_error(FMM_ERR_STATE, "p2p: leaf range out of bounds");
-    P2PConst k;
-    if (int rc = p2p_setup(P, k)) return rc;
+    if (t->bbox.bytes < (size_t)t->ncell * 32) return set_error(FMM_ERR_STATE, "p2p: leaf boxes not computed");
     P2PArgs a;
     p2p_args(t, a);
     a.first = first;
     a.err = err;
-    if (P->precision) {
-        if (t->bbox.bytes < (size_t)t->ncell * 32) return set_error(FMM_ERR_STATE, "p2p: leaf boxes not computed");
-    } else {
-        a.bbox = nullptr;
+    if (!P->precision) {
+        P2PConst64 k;
+        p2p_setup64(P, k);
+        if (P->p2p_chunk == 16) launch_p2p64<16>(P, k, a, count, st);
+        else if (P->p2p_chunk == 64) launch_p2p64<64>(P, k, a, count, st);
+        else launch_p2p64<kSinkChunk>(P, k, a, count, st);
+        return hip_check(hipGetLastError(), "p2p");
     }
-    if (P->precision && k.split != 1 && k.ncoef != 10 && k.ncoef != 11 && k.ncoef != 15)
+    P2PConst k;
+    if (int rc = p2p_setup(P, k)) return rc;
+    if (k.split != 1 && k.ncoef != 10 && k.ncoef != 11 && k.ncoef != 15)
         return set_error(FMM_ERR_STATE, "p2p: no kernel for a force law of %d coefficients", k.ncoef);
     if (P->p2p_chunk == 16) launch_p2p<16>(P, k, a, count, st);
     else if (P->p2p_chunk == 64) launch_p2p<64>(P, k, a, count, st);

@@ -668,8 +668,7 @@ void fmm_free_tree(fmm_tree *t)
     if (t->host) (void)hipHostFree(t->host);
     if (t->events_ready)
         for (auto &e : t->ev) (void)hipEventDestroy(e);
-    if (t->bev_ready)
-        for (auto &e : t->bev) (void)hipEventDestroy(e);
+    if (t->bev) (void)hipEventDestroy(t->bev);
     if (t->lev_ready) {
         for (auto &e : t->lev) (void)hipEventDestroy(e);
         for (auto &e : t->p2p_t0) (void)hipEventDestroy(e);

@@ -6,7 +6,6 @@
 
 namespace hfmm {
 constexpr int kHostInts = 1024;
-constexpr int kHostLevels = 512;  // tree build: level sizes mirrored at host[kHostLevels ...]
 // Interaction list kinds: 0 M2L, 1 P2P, 2 handed to the children, 3 candidate pairs
 // (training export), 4 M2L pairs of the learned selector (all orders; the order of each
 // entry in a byte beside it).
@@ -74,8 +73,7 @@ struct fmm_tree {
     // second stream (default priority) for stages independent of the caller's stream
     hipStream_t aux = nullptr;
     hipEvent_t dep[4]{};
-    hipEvent_t bev[hfmm::kMaxLevel + 1]{};  // tree build: one per level launch
-    bool bev_ready = false;
+    hipEvent_t bev = nullptr;               // tree build: its sizes are in t->host
     // traversal: the lists of level l's sinks are complete (lev); P2P launch of level l (timing)
     hipEvent_t lev[hfmm::kMaxLevel + 1]{}, p2p_t0[hfmm::kMaxLevel + 1]{}, p2p_t1[hfmm::kMaxLevel + 1]{};
     bool lev_ready = false;

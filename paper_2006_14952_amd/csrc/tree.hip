@@ -1,6 +1,6 @@
 // Octree construction (the particle packs of Sec. 2.1, built as a Morton octree):
-// wrap + 63-bit Morton keys, LSD radix sort (8-bit digits, stable), SoA gather, then
-// cells level by level from the sorted keys.
+// wrap + 63-bit Morton keys, LSD radix sort (8-bit digits, stable), the leaf depth of each
+// particle, SoA gather, and every level's cells at once from the sorted keys.
 #include <math.h>
 
 #include "state.h"
@@ -212,205 +212,374 @@ static int radix_sort(fmm_tree *t, int n, int nbox, int first_digit, hipStream_t
 }
 
 // ---------------------------------------------------------------------------
-// gather into Morton order
+// The cells from the sorted keys, without a loop over the levels.
+//
+// Particle i begins a cell at every level from d_i, the first level at which its key differs
+// from its predecessor's (0 for the first particle of a box), down to D_i, the level of the
+// leaf it lies in: the cells are the pairs (i, l) with d_i <= l <= D_i.  A level-l cell splits
+// if it holds more than n_crit particles, i.e. if n_crit + 1 consecutive particles share it;
+// so D_i is one more than the deepest level shared by any such window over i:
+//   D_i = max over j in [i - n_crit, i] of e_j,  e_j = 1 + level shared by keys j and j + n_crit
+// (0 where that window leaves the box).  Counting the cells and leaves that begin in each
+// tile of particles, level by level, and one scan over (level, tile) number them breadth
+// first; a second pass over the particles writes them.  Bound by memory latency on small
+// boxes, by the key reads on large ones.  Against a pass of seven launches per level: 18
+// launches a build instead of about 130.
 
+__device__ inline uint32_t compact3(uint64_t x)  // every third bit -> 21 bits
+{
+    x &= 0x1249249249249249ULL;
+    x = (x | x >> 2) & 0x10c30c30c30c30c3ULL;
+    x = (x | x >> 4) & 0x100f00f00f00f00fULL;
+    x = (x | x >> 8) & 0x1f0000ff0000ffULL;
+    x = (x | x >> 16) & 0x1f00000000ffffULL;
+    x = (x | x >> 32) & 0x1fffff;
+    return (uint32_t)x;
+}
+
+// What the tree passes read.  lmax: the deepest level the keys' order is exact to (a partial
+// sort's 15, or 21).
+struct TreeIn {
+    const uint64_t *keys;
+    const int *boxoff;
+    int n, nbox, ncrit, lmax;
+};
+
+// Levels shared by two keys, at most lmax.
+__device__ __forceinline__ int shared_levels(uint64_t a, uint64_t b, int lmax)
+{
+    const uint64_t x = a ^ b;
+    const int c = x ? (__clzll((long long)x) - 1) / 3 : kMaxLevel;
+    return c < lmax ? c : lmax;
+}
+
+__device__ __forceinline__ int tree_box(const TreeIn &t, int i) { return t.nbox > 1 ? box_of(t.boxoff, t.nbox, i) : 0; }
+__device__ __forceinline__ int box_end(const TreeIn &t, int b) { return t.nbox > 1 ? t.boxoff[b + 1] : t.n; }
+
+// e_j (0 where j or the window's end lies outside)
+__device__ __forceinline__ int window_level(const TreeIn &t, int64_t j)
+{
+    if (j < 0 || j + t.ncrit >= t.n) return 0;
+    const int a = (int)j, b = a + t.ncrit;
+    if (t.nbox > 1 && b >= t.boxoff[box_of(t.boxoff, t.nbox, a) + 1]) return 0;
+    return 1 + shared_levels(t.keys[a], t.keys[b], t.lmax);
+}
+
+// d_i; past lmax (no cell begins) if the particle shares level lmax with its predecessor
+__device__ __forceinline__ int first_level(const TreeIn &t, int i, int b, uint64_t key)
+{
+    if (i == (t.nbox > 1 ? t.boxoff[b] : 0)) return 0;
+    return 1 + shared_levels(key, t.keys[i - 1], t.lmax);
+}
+
+constexpr int kTreeThreads = 256, kTreeItems = 4, kTreeTile = kTreeThreads * kTreeItems;
+constexpr int kTreeChunks = kTreeTile / 64;  // runs of 64 particles, one wave each
+constexpr int kTreeWin = 512;                // widest window (n_crit) whose maximum is taken in LDS
+
+// Widest windows: e_j for j >= -n_crit in bytes, then maxima over 2, 4, ... of them.
+__global__ void k_window_levels(TreeIn t, unsigned char *__restrict__ e, int len)
+{
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q < len) e[q] = (unsigned char)window_level(t, (int64_t)q - t.ncrit);
+}
+
+__global__ void k_window_max(const unsigned char *__restrict__ in, unsigned char *__restrict__ out, int len, int step)
+{
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= len) return;
+    const unsigned char a = in[q], b = (int64_t)q + step < len ? in[q + step] : 0;
+    out[q] = a > b ? a : b;
+}
+
+// Depths D_i and, per tile and level, the cells and the leaves that begin there:
+// count[(l - 1) nblk + tile] and count[(21 + l - 1) nblk + tile] for l = 1 .. 21.
+// win: maxima over 2^wexp entries of the window array (wide windows), else nullptr.
+__global__ __launch_bounds__(kTreeThreads) void k_depth(TreeIn t, const unsigned char *__restrict__ win, int wexp,
+                                                        unsigned char *__restrict__ depth, int nblk,
+                                                        int *__restrict__ count, int *__restrict__ deep)
+{
+    __shared__ unsigned char m[2][kTreeTile + kTreeWin];
+    __shared__ int cnt[2][kMaxLevel];
+    const int lane = threadIdx.x & 63;
+    const int base = blockIdx.x * kTreeTile;
+    if (threadIdx.x < 2 * kMaxLevel) (&cnt[0][0])[threadIdx.x] = 0;
+    int cur = 0;
+    if (!win && t.ncrit < t.n) {
+        const int len = kTreeTile + t.ncrit;
+        for (int q = threadIdx.x; q < len; q += kTreeThreads)
+            m[0][q] = (unsigned char)window_level(t, (int64_t)base - t.ncrit + q);
+        __syncthreads();
+        for (int k = 0; k < wexp; ++k) {
+            for (int q = threadIdx.x; q < len; q += kTreeThreads) {
+                const int o = q + (1 << k);
+                m[cur ^ 1][q] = max(m[cur][q], o < len ? m[cur][o] : (unsigned char)0);
+            }
+            __syncthreads();
+            cur ^= 1;
+        }
+    } else {
+        __syncthreads();
+    }
+    bool isdeep = false;
+    for (int k = 0; k < kTreeItems; ++k) {
+        const int p = k * kTreeThreads + threadIdx.x, i = base + p;
+        const bool valid = i < t.n;
+        int d = kMaxLevel + 1, D = 0;
+        if (valid) {
+            if (t.ncrit < t.n) {  // the window starts i - n_crit .. i, as two overlapping runs of 2^wexp
+                const int64_t lo = win ? (int64_t)i : (int64_t)p, hi = lo + t.ncrit + 1 - (1 << wexp);
+                D = win ? max(win[lo], win[hi]) : max(m[cur][lo], m[cur][hi]);
+            }
+            isdeep |= D > t.lmax;
+            D = D < kMaxLevel ? D : kMaxLevel;
+            depth[i] = (unsigned char)D;
+            const int b = tree_box(t, i);
+            d = first_level(t, i, b, t.keys[i]);
+        }
+        const bool starts = valid && d <= D;
+        uint64_t left = __ballot(starts);
+        int lo = starts ? d : kMaxLevel + 1, hi = starts ? D : 0;
+        if (left) {
+            for (int o = 32; o > 0; o >>= 1) {
+                lo = min(lo, __shfl_xor(lo, o, 64));
+                hi = max(hi, __shfl_xor(hi, o, 64));
+            }
+            for (int l = lo > 1 ? lo : 1; l <= hi; ++l) {
+                const uint64_t mc = __ballot(starts && d <= l && l <= D), ml = __ballot(starts && D == l);
+                if (lane == 0) {
+                    if (mc) atomicAdd(&cnt[0][l - 1], __popcll(mc));
+                    if (ml) atomicAdd(&cnt[1][l - 1], __popcll(ml));
+                }
+            }
+        }
+    }
+    if (isdeep && t.lmax < kMaxLevel) *deep = 1;
+    __syncthreads();
+    if (threadIdx.x < 2 * kMaxLevel)
+        count[(size_t)threadIdx.x * nblk + blockIdx.x] = (&cnt[0][0])[threadIdx.x];
+}
+
+// One workgroup: the roots (level 0, one per box, empty boxes too).  out: their cells, and
+// their places among the leaves and the cells with children (nullptr: only the leaf count).
+__global__ __launch_bounds__(1024) void k_roots(const int *__restrict__ boxoff, int nbox, int ncrit,
+                                                Cell *__restrict__ cells, int *__restrict__ leaves,
+                                                int *__restrict__ inner, int *__restrict__ nleaf0)
+{
+    __shared__ int wsum[16];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int before = 0;
+    for (int b0 = 0; b0 < nbox; b0 += 1024) {
+        const int b = b0 + threadIdx.x;
+        const int beg = b < nbox ? boxoff[b] : 0, end = b < nbox ? boxoff[b + 1] : 0;
+        const bool leaf = b < nbox && end - beg <= ncrit;
+        const uint64_t m = __ballot(leaf);
+        if (lane == 0) wsum[w] = __popcll(m);
+        __syncthreads();
+        int rank = before + __popcll(m & ((1ull << lane) - 1ull)), tot = 0;
+        for (int q = 0; q < 16; ++q) {
+            if (q < w) rank += wsum[q];
+            tot += wsum[q];
+        }
+        if (cells && b < nbox) {
+            Cell c;
+            c.xln = pack_xln(0, 0, 0);
+            c.iy = c.iz = 0;
+            c.pad = 0;
+            c.beg = beg;
+            c.end = end;
+            c.child = -1;
+            c.parent = -1;
+            cells[b] = c;
+            if (leaves) {
+                if (leaf) leaves[rank] = b;
+                else inner[b - rank] = b;
+            }
+        }
+        before += tot;
+        __syncthreads();
+    }
+    if (nleaf0 && threadIdx.x == 0) *nleaf0 = before;
+}
+
+// The scan's values at the first tile of every level: out[0 .. 41], and its total at out[42].
+__global__ void k_level_starts(const int *__restrict__ scan, int nblk, const int *__restrict__ total, int *__restrict__ out)
+{
+    const int k = threadIdx.x;
+    if (k < 2 * kMaxLevel) out[k] = scan[(size_t)k * nblk];
+    if (k == 2 * kMaxLevel) out[k] = *total;
+}
+
+// The cells of levels 1 .. 21 (all but the child counts), the leaf and inner-cell lists and
+// the leaf of each particle.  Each wave takes runs of 64 particles; a level's cells that begin
+// in the run are numbered by ballots.
+__global__ __launch_bounds__(kTreeThreads) void k_cells(TreeIn t, const unsigned char *__restrict__ depth, int nblk,
+                                                        const int *__restrict__ scan, int nleaf0,
+                                                        Cell *__restrict__ cells, int *__restrict__ leaves,
+                                                        int *__restrict__ inner, int *__restrict__ leaf_of)
+{
+    __shared__ int cc[kTreeChunks][kMaxLevel + 1], cl[kTreeChunks][kMaxLevel + 1];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt = (1ull << lane) - 1ull, le = lt | 1ull << lane;
+    const int base = blockIdx.x * kTreeTile;
+    for (int q = threadIdx.x; q < kTreeChunks * (kMaxLevel + 1); q += kTreeThreads) {
+        (&cc[0][0])[q] = 0;
+        (&cl[0][0])[q] = 0;
+    }
+    __syncthreads();
+    uint64_t key[kTreeItems];
+    int box[kTreeItems], d[kTreeItems], D[kTreeItems];
+#pragma unroll
+    for (int k = 0; k < kTreeItems; ++k) {
+        const int i = base + k * kTreeThreads + threadIdx.x, ch = k * (kTreeThreads / 64) + w;
+        key[k] = 0;
+        box[k] = 0;
+        d[k] = kMaxLevel + 1;
+        D[k] = 0;
+        if (i < t.n) {
+            key[k] = t.keys[i];
+            D[k] = depth[i];
+            box[k] = tree_box(t, i);
+            d[k] = first_level(t, i, box[k], key[k]);
+        }
+        const bool starts = d[k] <= D[k];  // never past the last particle
+        if (__ballot(starts) == 0) continue;
+        int lo = starts ? d[k] : kMaxLevel + 1, hi = starts ? D[k] : 0;
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = min(lo, __shfl_xor(lo, o, 64));
+            hi = max(hi, __shfl_xor(hi, o, 64));
+        }
+        for (int l = lo > 1 ? lo : 1; l <= hi; ++l) {
+            const uint64_t mc = __ballot(starts && d[k] <= l && l <= D[k]), ml = __ballot(starts && D[k] == l);
+            if (lane == 0) {
+                cc[ch][l] = __popcll(mc);
+                cl[ch][l] = __popcll(ml);
+            }
+        }
+    }
+    __syncthreads();
+    if (lane >= 1 && lane <= kMaxLevel && w < 2) {  // exclusive over the runs, from the scan's base
+        const int l = lane;
+        const size_t row = (size_t)((w ? kMaxLevel : 0) + l - 1) * nblk;
+        int run = scan[row + blockIdx.x] + (w ? nleaf0 - scan[(size_t)kMaxLevel * nblk] : t.nbox);
+        for (int q = 0; q < kTreeChunks; ++q) {
+            int *v = w ? &cl[q][l] : &cc[q][l];
+            const int c = *v;
+            *v = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTreeItems; ++k) {
+        const int ch = k * (kTreeThreads / 64) + w, c0 = base + ch * 64, i = c0 + lane;
+        if (c0 >= t.n) continue;
+        const bool valid = i < t.n, starts = valid && d[k] <= D[k];
+        // levels this run needs: a beginning cell's parent level to its leaf, every particle's leaf
+        int lo = starts ? d[k] - 1 : (valid ? D[k] : kMaxLevel), hi = valid ? D[k] : 0;
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = min(lo, __shfl_xor(lo, o, 64));
+            hi = max(hi, __shfl_xor(hi, o, 64));
+        }
+        lo = lo > 0 ? lo : 0;
+        // cells of level l begun up to this particle, as an index past the last of them
+        auto upto = [&](int l) __attribute__((always_inline)) {
+            const uint64_t m = __ballot(starts && d[k] <= l && l <= D[k]);
+            return l == 0 ? box[k] + 1 : cc[ch][l] + (int)__popcll(m & le);
+        };
+        int prev = 0, at = upto(lo), leaf = box[k];
+        for (int l = lo; l <= hi; ++l) {
+            const int next = l < hi ? upto(l + 1) : 0;
+            const uint64_t ml = __ballot(starts && D[k] == l), mb = __ballot(valid && d[k] <= l);
+            if (valid && D[k] == l) leaf = at - 1;
+            if (l == 0) {
+                if (starts && d[k] == 0 && D[k] > 0) cells[box[k]].child = next - 1;
+            } else if (starts && d[k] <= l && l <= D[k]) {
+                const int c = at - 1, sh = 3 * (kMaxLevel - l);
+                const int lb = cl[ch][l] + (int)__popcll(ml & lt);  // leaves before this cell
+                const uint64_t pre = key[k] >> sh;
+                int end;
+                const uint64_t later = mb & ~le;
+                const int bend = box_end(t, box[k]);
+                if (later) {
+                    end = c0 + (int)__ffsll((unsigned long long)later) - 1;
+                } else {  // past this run: the first key outside the cell, by doubling steps, then bisection
+                    int a = c0 + 63, step = 1;  // particle a is inside, or the box ends at it
+                    int z = bend;                // particle z is outside, or z = bend
+                    while (a < bend - 1) {
+                        const int q = a + min(step, bend - 1 - a);
+                        if ((t.keys[q] >> sh) != pre) {
+                            z = q;
+                            break;
+                        }
+                        a = q;
+                        step *= 2;
+                    }
+                    while (z - a > 1) {
+                        const int mid = a + (z - a) / 2;
+                        if ((t.keys[mid] >> sh) == pre) a = mid;
+                        else z = mid;
+                    }
+                    end = z;
+                }
+                Cell q;
+                q.xln = pack_xln((int)compact3(pre >> 2), l, 0);
+                q.iy = (int)compact3(pre >> 1);
+                q.iz = (int)compact3(pre);
+                q.child = l < D[k] ? next - 1 : -1;
+                q.beg = i;
+                q.end = end;
+                q.parent = prev - 1;
+                q.pad = 0;
+                cells[c] = q;
+                if (l == D[k]) leaves[lb] = c;
+                else inner[c - lb] = c;
+            }
+            prev = at;
+            at = next;
+        }
+        if (valid) leaf_of[i] = leaf;
+    }
+}
+
+// Child counts of the cells with children: the run of cells from the first child that name
+// the cell as their parent.
+__global__ void k_child_counts(Cell *__restrict__ cells, int ncell, const int *__restrict__ inner, int ninner)
+{
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= ninner) return;
+    const int c = inner[q], first = cells[c].child;
+    int k = 1;
+    while (k < 8 && first + k < ncell && cells[first + k].parent == c) ++k;
+    cells[c].xln |= k << 26;
+}
+
+// Particles in Morton order: wrapped FP64 positions and masses, and FP32 records relative to
+// the centre of their leaf (the FP32 form keeps FP64 only for absolute positions and the
+// exact cell-centre offsets); the leaf's cube follows from the key and the depth.
 __global__ void k_gather(const double *__restrict__ pos, const double *__restrict__ mass,
-                         const uint32_t *__restrict__ idx, int n, double box, double *__restrict__ xs,
+                         const uint32_t *__restrict__ idx, const uint64_t *__restrict__ keys,
+                         const unsigned char *__restrict__ depth, int n, double box, double *__restrict__ xs,
                          double *__restrict__ ys, double *__restrict__ zs, double *__restrict__ ms,
-                         int *__restrict__ perm)
+                         int *__restrict__ perm, float4 *__restrict__ rel)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     uint32_t j = idx[i];
     double x = pos[3 * (size_t)j], y = pos[3 * (size_t)j + 1], z = pos[3 * (size_t)j + 2];
-    xs[i] = isfinite(x) ? wrap_coord(x, box) : 0.0;
-    ys[i] = isfinite(y) ? wrap_coord(y, box) : 0.0;
-    zs[i] = isfinite(z) ? wrap_coord(z, box) : 0.0;
-    ms[i] = mass[j];
+    x = isfinite(x) ? wrap_coord(x, box) : 0.0;
+    y = isfinite(y) ? wrap_coord(y, box) : 0.0;
+    z = isfinite(z) ? wrap_coord(z, box) : 0.0;
+    const double m = mass[j];
+    xs[i] = x;
+    ys[i] = y;
+    zs[i] = z;
+    ms[i] = m;
     perm[i] = (int)j;
-}
-
-// ---------------------------------------------------------------------------
-// cells, level by level
-
-// one root (level 0, the whole box) per box of the batch
-__global__ void k_roots(Cell *cells, int nbox, const int *__restrict__ boxoff)
-{
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nbox) return;
-    Cell c;
-    c.xln = pack_xln(0, 0, 0);
-    c.iy = c.iz = 0;
-    c.pad = 0;
-    c.beg = boxoff[b];
-    c.end = boxoff[b + 1];
-    c.child = -1;
-    c.parent = -1;
-    cells[b] = c;
-}
-
-// Octant boundaries of a cell at level l: b[o] = first particle of octant o, b[8] = end.
-// The seven lower bounds each search the whole particle range in lockstep (the interval
-// length sequence depends on the range only), so their loads are in flight together:
-// log2(n) dependent steps instead of seven times that.  Invariant per search: keys before
-// base are below the target and the answer lies in [base, base + n].
-__device__ inline void octant_bounds(const uint64_t *keys, const Cell &c, int l, int b[9])
-{
-    const int shift = 3 * (kMaxLevel - 1 - l);
-    const uint64_t prefix = keys[c.beg] >> (shift + 3) << (shift + 3);
-    int base[7];
-    uint64_t tgt[7];
-#pragma unroll
-    for (int o = 0; o < 7; ++o) {
-        base[o] = c.beg;
-        tgt[o] = prefix | ((uint64_t)(o + 1) << shift);
-    }
-    int n = c.end - c.beg;  // >= 1: only cells with more than n_crit particles are split
-    while (n > 1) {
-        const int half = n >> 1;
-#pragma unroll
-        for (int o = 0; o < 7; ++o) base[o] = keys[base[o] + half] < tgt[o] ? base[o] + half : base[o];
-        n -= half;
-    }
-    b[0] = c.beg;
-#pragma unroll
-    for (int o = 0; o < 7; ++o) b[o + 1] = base[o] + (keys[base[o]] < tgt[o] ? 1 : 0);
-    b[8] = c.end;
-}
-
-// Level by level without host round trips: the cells of level l are lv[l] .. lv[l+1]-1
-// in device memory, the cell array has room for `cap` cells, and *ovf is set (and every
-// later level left empty) when a level would not fit; the host then rebuilds with room.
-__global__ void k_level_init(int *__restrict__ lv, int nbox, int *__restrict__ ovf)
-{
-    if (threadIdx.x == 0) {
-        lv[0] = 0;
-        lv[1] = nbox;
-        *ovf = 0;
-    }
-}
-
-__global__ void k_count_children_dev(const Cell *__restrict__ cells, const int *__restrict__ lv, int l, int ncrit,
-                                     const uint64_t *__restrict__ keys, int *__restrict__ nch,
-                                     const int *__restrict__ ovf)
-{
-    if (*ovf) return;
-    const int lbeg = lv[l], ln = lv[l + 1] - lbeg;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < ln; t += gridDim.x * blockDim.x) {
-        Cell c = cells[lbeg + t];
-        int k = 0;
-        if (c.end - c.beg > ncrit && l < kMaxLevel) {
-            int b[9];
-            octant_bounds(keys, c, l, b);
-            for (int o = 0; o < 8; ++o) k += b[o + 1] > b[o];
-        }
-        nch[t] = k;
-    }
-}
-
-__global__ void k_make_children_dev(Cell *__restrict__ cells, const int *__restrict__ lv, int l, int ncrit,
-                                    const uint64_t *__restrict__ keys, const int *__restrict__ off, int cap,
-                                    int *__restrict__ ovf)
-{
-    if (*ovf) return;
-    const int lbeg = lv[l], ln = lv[l + 1] - lbeg, nbeg = lv[l + 1];
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < ln; t += gridDim.x * blockDim.x) {
-        const int ci = lbeg + t;
-        Cell c = cells[ci];
-        if (!(c.end - c.beg > ncrit && l < kMaxLevel)) continue;
-        int b[9];
-        octant_bounds(keys, c, l, b);
-        int nk = 0;
-        for (int o = 0; o < 8; ++o) nk += b[o + 1] > b[o];
-        const int first = nbeg + off[t];
-        if (first + nk > cap) {  // no room: the level is dropped and the tree rebuilt
-            atomicOr(ovf, 1);
-            continue;
-        }
-        int k = 0;
-        for (int o = 0; o < 8; ++o) {
-            if (b[o + 1] == b[o]) continue;
-            Cell ch;
-            ch.xln = pack_xln(2 * cell_ix(c) + ((o >> 2) & 1), l + 1, 0);
-            ch.iy = 2 * c.iy + ((o >> 1) & 1);
-            ch.iz = 2 * c.iz + (o & 1);
-            ch.pad = 0;
-            ch.beg = b[o];
-            ch.end = b[o + 1];
-            ch.child = -1;
-            ch.parent = ci;
-            cells[first + k] = ch;
-            ++k;
-        }
-        c.child = first;
-        c.xln = pack_xln(cell_ix(c), l, k);
-        cells[ci] = c;
-    }
-}
-
-// lv[l+2] = end of the next level; an overflowing level leaves the next one empty
-__global__ void k_level_end(int *__restrict__ lv, int l, const int *__restrict__ total, int cap, int *__restrict__ ovf)
-{
-    if (threadIdx.x != 0) return;
-    int e = lv[l + 1] + (*ovf ? 0 : *total);
-    if (e > cap) {
-        *ovf = 1;
-        e = lv[l + 1];
-    }
-    if (*ovf) e = lv[l + 1];
-    lv[l + 2] = e;
-}
-
-__global__ void k_leaf_flag(const Cell *__restrict__ cells, int ncell, int *__restrict__ flag)
-{
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < ncell) flag[c] = cell_nchild(cells[c]) == 0;
-}
-
-// Leaves before the first cell of each level (the exclusive leaf-flag scan at the level
-// boundaries; the scan total past the last): the leaves of level l are
-// leaves[out[l] .. out[l+1]-1], since cells, and so leaves, are stored level by level.
-struct LevelBounds {
-    int b[kMaxLevel + 2];
-    int n;  // levels; b[0 .. n]
-};
-
-__global__ void k_leaf_levels(const int *__restrict__ off, int ncell, const int *__restrict__ total, LevelBounds lb,
-                              int *__restrict__ out)
-{
-    const int l = threadIdx.x;
-    if (l <= lb.n) out[l] = lb.b[l] < ncell ? off[lb.b[l]] : *total;
-}
-
-// Leaves and the cells with children, each in cell order (so level by level): a cell with
-// children is number c - off[c] among them.
-__global__ void k_leaf_compact(const Cell *__restrict__ cells, int ncell, const int *__restrict__ flag,
-                               const int *__restrict__ off, int *__restrict__ leaves, int *__restrict__ inner,
-                               int *__restrict__ leaf_of)
-{
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
-    if (!flag[c]) {
-        inner[c - off[c]] = c;
-        return;
-    }
-    leaves[off[c]] = c;
-    Cell cc = cells[c];
-    for (int i = cc.beg; i < cc.end; ++i) leaf_of[i] = c;
-}
-
-// FP32 particle records relative to the centre of their leaf (the FP32 form keeps FP64
-// only for absolute positions and the exact cell-centre offsets).
-__global__ void k_rel32(const Cell *__restrict__ cells, const int *__restrict__ leaf_of, const double *__restrict__ xs,
-                        const double *__restrict__ ys, const double *__restrict__ zs, const double *__restrict__ ms,
-                        int n, double box, float4 *__restrict__ rel)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    Cell c = cells[leaf_of[i]];
-    double h = ldexp(box, -cell_level(c));
-    rel[i] = make_float4((float)(xs[i] - (cell_ix(c) + 0.5) * h), (float)(ys[i] - (c.iy + 0.5) * h),
-                         (float)(zs[i] - (c.iz + 0.5) * h), (float)ms[i]);
+    const int l = depth[i];
+    const uint64_t pre = keys[i] >> (3 * (kMaxLevel - l));
+    const double h = ldexp(box, -l);
+    rel[i] = make_float4((float)(x - ((int)compact3(pre >> 2) + 0.5) * h), (float)(y - ((int)compact3(pre >> 1) + 0.5) * h),
+                         (float)(z - ((int)compact3(pre) + 0.5) * h), (float)m);
 }
 
 static inline int blocks(int64_t n, int b) { return (int)((n + b - 1) / b); }
@@ -443,134 +612,114 @@ int tree_build(fmm_tree *t, const fmm_params *P, int64_t n64, const double *pos,
             return set_error(FMM_ERR_NOMEM, "pinned host buffer");
     }
     int *bad = ptr<int>(t->flag);
-    if ((rc = hip_check(hipMemsetAsync(bad, 0, sizeof(int), st), "tree flags"))) return rc;
+    if ((rc = hip_check(hipMemsetAsync(bad, 0, 4 * sizeof(int), st), "tree flags"))) return rc;
+    t->lvl_beg.assign(1, 0);
+    if (n == 0) {  // the empty roots
+        if ((rc = grow(t->cells, sizeof(Cell) * (size_t)nbox))) return rc;
+        k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, P->n_crit, ptr<Cell>(t->cells), nullptr, nullptr, nullptr);
+        t->lvl_beg.push_back(nbox);
+        t->nlevel = 1;
+        t->ncell = nbox;
+        t->nleaf = 0;
+        t->leaf_lvl.assign(2, 0);
+        return hip_check(hipStreamSynchronize(st), "tree");
+    }
+    if (!t->bev && hipEventCreateWithFlags(&t->bev, hipEventDisableTiming) != hipSuccess)
+        return set_error(FMM_ERR_HIP, "hipEventCreateWithFlags");
+    t->sorted = 0;
+    k_keys<<<blocks(n, 256), 256, 0, st>>>(pos, n, P->box, ptr<uint64_t>(t->keys[0]), ptr<uint32_t>(t->idx[0]), bad);
     // The sort starts at the key's third digit: bits 16 .. 62 order the particles exactly to
     // level 15 (a level-l octant is decided by key bits 3 (21 - l) .. 3 (21 - l) + 2).  Only
-    // a tree that splits a level-15 cell needs the two lowest digits; the level loop then
-    // stops at level 16, and the arrays are sorted again over every digit (a full LSD sort
-    // of the partly sorted arrays) before the cells are built anew.
-    constexpr int kPartialDigit = 2, kPartialLevels = 16;
-    auto sort_gather = [&](int first_digit) -> int {
-        if (int r = radix_sort(t, n, nbox, first_digit, st)) return r;
-        k_gather<<<blocks(n, 256), 256, 0, st>>>(pos, mass, ptr<uint32_t>(t->idx[t->sorted]), n, P->box,
-                                                 ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs),
-                                                 ptr<double>(t->ms), ptr<int>(t->perm));
-        return hip_check(hipGetLastError(), "tree sort");
-    };
-    bool partial = n > 0;
-    if (n > 0) {
-        t->sorted = 0;
-        k_keys<<<blocks(n, 256), 256, 0, st>>>(pos, n, P->box, ptr<uint64_t>(t->keys[0]), ptr<uint32_t>(t->idx[0]), bad);
-        if ((rc = sort_gather(kPartialDigit))) return rc;
-    }
-    if ((rc = hip_check(hipGetLastError(), "tree keys"))) return rc;
-
-    // Cells level by level.  The level sizes stay on the device (lv); the host reads each
-    // one back a level late through an event, only to stop the loop, so the GPU never
-    // waits for it.  Room for `cap` cells: the previous tree's count or 8 n / n_crit,
-    // four times more after an overflow.
-    if (!t->bev_ready) {
-        for (auto &e : t->bev)
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
-                return set_error(FMM_ERR_HIP, "hipEventCreateWithFlags");
-        t->bev_ready = true;
-    }
-    int *lv = bad + 8, *ovf = bad + 2;  // flag area: [0] non-finite, [1] scan total, [2] overflow, [8..] lv
-    int *hl = t->host + kHostLevels;    // pinned mirror of lv
-    const int nc_ = P->n_crit > 0 ? P->n_crit : 1;
-    int launched = 0;
-    for (;;) {  // once, or twice after a partial sort that does not reach deep enough
-    const uint64_t *keys = ptr<uint64_t>(t->keys[t->sorted]);
-    int64_t cap64 = (nc_ >= 2 ? 8 * (int64_t)n / nc_ : 4 * (int64_t)n) + 64 * (int64_t)nbox + 1024;
-    if (t->ncell > 0) cap64 = cap64 > (int64_t)t->ncell * 5 / 4 + 1024 ? cap64 : (int64_t)t->ncell * 5 / 4 + 1024;
-    const int lmax = partial ? kPartialLevels : kMaxLevel;
-    for (int attempt = 0;; ++attempt) {
-        if (cap64 > 0x7fffffff || attempt > 3) return set_error(FMM_ERR_NOMEM, "octree does not fit");
-        const int cap = (int)cap64;
-        if ((rc = grow(t->cells, sizeof(Cell) * (size_t)cap) | grow(t->nch, (size_t)cap * 2 * sizeof(int) + 64)))
-            return rc;
-        int *nch = ptr<int>(t->nch), *off = nch + cap;
-        k_roots<<<blocks(nbox, 64), 64, 0, st>>>(ptr<Cell>(t->cells), nbox, ptr<int>(t->boxoff));
-        k_level_init<<<1, 64, 0, st>>>(lv, nbox, ovf);
-        hl[0] = 0;
-        hl[1] = nbox;
-        int64_t bound = nbox;  // the cells of level l are at most 8^l nbox (and cap)
-        launched = 0;
-        for (int l = 0; l < lmax && n > 0; ++l) {
-            const int b = (int)bound, g = blocks(b, 256) < 4096 ? blocks(b, 256) : 4096;
-            k_count_children_dev<<<g, 256, 0, st>>>(ptr<Cell>(t->cells), lv, l, P->n_crit, keys, nch, ovf);
-            if ((rc = scan_exclusive_dn(nch, off, lv + l, lv + l + 1, b, bad + 1, st, t->scan_tmp))) return rc;
-            k_make_children_dev<<<g, 256, 0, st>>>(ptr<Cell>(t->cells), lv, l, P->n_crit, keys, off, cap, ovf);
-            k_level_end<<<1, 64, 0, st>>>(lv, l, bad + 1, cap, ovf);
-            if ((rc = hip_check(hipMemcpyAsync(hl + l + 2, lv + l + 2, sizeof(int), hipMemcpyDeviceToHost, st),
-                                "level size")) ||
-                (rc = hip_check(hipEventRecord(t->bev[l], st), "event")))
-                return rc;
-            launched = l + 1;
-            bound = bound * 8 < cap ? bound * 8 : cap;
-            if (l >= 1) {  // the previous level's result: is level l (launched already) empty?
-                if ((rc = hip_check(hipEventSynchronize(t->bev[l - 1]), "tree level"))) return rc;
-                if (hl[l + 1] == hl[l]) break;
+    // a tree that splits a level-15 cell needs the two lowest digits: its arrays are sorted
+    // again over every digit (a full LSD sort of the partly sorted arrays).
+    constexpr int kPartialDigit = 2, kPartialLevel = 15;
+    const int nblk = blocks(n, kTreeTile), ncount = 2 * kMaxLevel * nblk;
+    const int nc = P->n_crit;
+    int wexp = 0;  // 2^wexp <= n_crit + 1 < 2^(wexp + 1)
+    while (((int64_t)2 << wexp) <= (int64_t)nc + 1) ++wexp;
+    int *total = bad + 1, *deep = bad + 2, *nleaf0 = bad + 3, *starts = bad + 8;  // flag area
+    int *h = t->host;
+    int *scan = nullptr;
+    const unsigned char *depth = nullptr;
+    TreeIn in{nullptr, ptr<int>(t->boxoff), n, nbox, nc, kPartialLevel};
+    for (int first = kPartialDigit;; first = 0) {
+        if ((rc = radix_sort(t, n, nbox, first, st))) return rc;
+        in.keys = ptr<uint64_t>(t->keys[t->sorted]);
+        in.lmax = first ? kPartialLevel : kMaxLevel;
+        // the sort's other buffers are free: depths in the indices', wide windows in the keys'
+        unsigned char *dep = ptr<unsigned char>(t->idx[t->sorted ^ 1]);
+        depth = dep;
+        const unsigned char *win = nullptr;
+        if (nc > kTreeWin && nc < n) {
+            const int len = n + nc;
+            unsigned char *a = ptr<unsigned char>(t->keys[t->sorted ^ 1]), *b = a + len;
+            k_window_levels<<<blocks(len, 256), 256, 0, st>>>(in, a, len);
+            for (int k = 0; k < wexp; ++k) {
+                k_window_max<<<blocks(len, 256), 256, 0, st>>>(a, b, len, 1 << k);
+                unsigned char *c = a;
+                a = b;
+                b = c;
             }
+            win = a;
         }
-        if ((rc = hip_check(hipMemcpyAsync(t->host, bad, 3 * sizeof(int), hipMemcpyDeviceToHost, st), "tree flags")) ||
-            (rc = hip_check(hipStreamSynchronize(st), "tree")))
+        if ((rc = grow(t->nch, (size_t)ncount * 2 * sizeof(int)))) return rc;
+        int *count = ptr<int>(t->nch);
+        scan = count + ncount;
+        k_depth<<<nblk, kTreeThreads, 0, st>>>(in, win, wexp, dep, nblk, count, deep);
+        if ((rc = scan_exclusive(count, scan, ncount, total, st, t->scan_tmp))) return rc;
+        k_level_starts<<<1, 64, 0, st>>>(scan, nblk, total, starts);
+        k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, nc, nullptr, nullptr, nullptr, nleaf0);
+        if ((rc = hip_check(hipMemcpyAsync(h, bad, 64 * sizeof(int), hipMemcpyDeviceToHost, st), "tree sizes")) ||
+            (rc = hip_check(hipEventRecord(t->bev, st), "event")))
             return rc;
-        if (t->host[0]) return set_error(FMM_ERR_NAN, "non-finite particle position");
-        if (!t->host[2]) break;
-        cap64 *= 4;  // a level did not fit: rebuild with more room
+        // runs while the host reads the sizes and prepares the next launches
+        k_gather<<<blocks(n, 256), 256, 0, st>>>(pos, mass, ptr<uint32_t>(t->idx[t->sorted]), in.keys, depth, n, P->box,
+                                                 ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs),
+                                                 ptr<double>(t->ms), ptr<int>(t->perm), ptr<float4>(t->rel32));
+        if ((rc = hip_check(hipGetLastError(), "tree")) || (rc = hip_check(hipEventSynchronize(t->bev), "tree"))) return rc;
+        if (h[0]) return set_error(FMM_ERR_NAN, "non-finite particle position");
+        if (!first || !h[2]) break;
     }
-    if (partial && launched == kPartialLevels && hl[kPartialLevels + 1] > hl[kPartialLevels]) {
-        partial = false;  // a level-15 cell splits: sort over every digit and build again
-        if ((rc = sort_gather(0))) return rc;
-        continue;
+    // level sizes: differences of the scan at the levels' first tiles (modulo 2^32; a level
+    // holds at most n cells, all of them may not fit an int)
+    const int n0 = h[3], *hs = h + 8;
+    int64_t ncell = nbox, nleaf = n0;
+    t->lvl_beg.push_back(nbox);
+    t->leaf_lvl.assign(1, 0);
+    t->leaf_lvl.push_back(n0);
+    for (int l = 1; l <= kMaxLevel; ++l) {
+        const uint32_t cells = (uint32_t)hs[l] - (uint32_t)hs[l - 1];
+        const uint32_t lv = (uint32_t)hs[kMaxLevel + l] - (uint32_t)hs[kMaxLevel + l - 1];
+        if (cells == 0) break;
+        ncell += cells;
+        nleaf += lv;
+        if (ncell >= kMaxCells) break;
+        t->lvl_beg.push_back((int)ncell);
+        t->leaf_lvl.push_back((int)nleaf);
     }
-    break;
-    }
-    t->lvl_beg.assign(1, 0);
-    for (int l = 0; l <= launched && hl[l + 1] > hl[l]; ++l) t->lvl_beg.push_back(hl[l + 1]);
-    t->nlevel = (int)t->lvl_beg.size() - 1;
-    t->ncell = t->lvl_beg.back();
-    if (t->ncell >= kMaxCells) {  // interaction-list entries hold the cell index in 27 bits
-        const int nc = t->ncell;
+    if (ncell >= kMaxCells) {  // interaction-list entries hold the cell index in 27 bits
         t->n = 0;  // the tree is unusable: later calls see an empty tree, never aliased entries
         t->ncell = t->nleaf = t->nlevel = 0;
         t->lvl_beg.assign(1, 0);
         t->leaf_lvl.assign(1, 0);
         t->stats.n = t->stats.n_cells = t->stats.n_leaves = t->stats.max_level = 0;
-        return set_error(FMM_ERR_ARG, "octree of %d cells exceeds the %d cells an interaction-list entry can "
-                                      "address (raise n_crit)", nc, kMaxCells - 1);
+        return set_error(FMM_ERR_ARG, "octree exceeds the %d cells an interaction-list entry can address (raise n_crit)",
+                         kMaxCells - 1);
     }
-    if (n == 0) {
-        t->nleaf = 0;
-        t->leaf_lvl.assign(t->nlevel + 1, 0);
-        return hip_check(hipStreamSynchronize(st), "tree");
-    }
-    // leaves
-    if ((rc = grow(t->nch, (size_t)t->ncell * 2 * sizeof(int) + 64))) return rc;
-    int *flag = ptr<int>(t->nch), *off = flag + t->ncell;
-    k_leaf_flag<<<blocks(t->ncell, 256), 256, 0, st>>>(ptr<Cell>(t->cells), t->ncell, flag);
-    if ((rc = scan_exclusive(flag, off, t->ncell, bad + 1, st, t->scan_tmp))) return rc;
-    if (t->nlevel > kMaxLevel + 1) return set_error(FMM_ERR_STATE, "octree deeper than %d levels", kMaxLevel + 1);
-    LevelBounds lb;
-    lb.n = t->nlevel;
-    for (int l = 0; l <= t->nlevel; ++l) lb.b[l] = t->lvl_beg[l];
-    int *hlev = bad + 32;  // flag area [32 ..]: leaves before each level
-    k_leaf_levels<<<1, 64, 0, st>>>(off, t->ncell, bad + 1, lb, hlev);
-    if ((rc = hip_check(hipMemcpyAsync(t->host, bad + 1, sizeof(int), hipMemcpyDeviceToHost, st), "leaf count")) ||
-        (rc = hip_check(hipMemcpyAsync(t->host + 32, hlev, (size_t)(t->nlevel + 1) * sizeof(int),
-                                       hipMemcpyDeviceToHost, st), "leaves per level")))
+    t->nlevel = (int)t->lvl_beg.size() - 1;
+    t->ncell = (int)ncell;
+    t->nleaf = (int)nleaf;
+    const int ninner = t->ncell - t->nleaf;
+    if ((rc = grow(t->cells, sizeof(Cell) * (size_t)t->ncell) | grow(t->leaves, (size_t)t->nleaf * 4 + 4) |
+              grow(t->inner, (size_t)ninner * 4 + 4)))
         return rc;
-    if ((rc = hip_check(hipStreamSynchronize(st), "leaf count"))) return rc;
-    t->nleaf = t->host[0];
-    t->leaf_lvl.assign(t->host + 32, t->host + 32 + t->nlevel + 1);
-    if ((rc = grow(t->leaves, (size_t)t->nleaf * 4 + 4) | grow(t->inner, (size_t)(t->ncell - t->nleaf) * 4 + 4))) return rc;
-    k_leaf_compact<<<blocks(t->ncell, 256), 256, 0, st>>>(ptr<Cell>(t->cells), t->ncell, flag, off, ptr<int>(t->leaves),
-                                                          ptr<int>(t->inner), ptr<int>(t->leaf_of));
-    k_rel32<<<blocks(n, 256), 256, 0, st>>>(ptr<Cell>(t->cells), ptr<int>(t->leaf_of), ptr<double>(t->xs),
-                                            ptr<double>(t->ys), ptr<double>(t->zs), ptr<double>(t->ms), n, P->box,
-                                            ptr<float4>(t->rel32));
-    return hip_check(hipGetLastError(), "tree leaves");
+    k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, nc, ptr<Cell>(t->cells), ptr<int>(t->leaves),
+                                ptr<int>(t->inner), nullptr);
+    k_cells<<<nblk, kTreeThreads, 0, st>>>(in, depth, nblk, scan, n0, ptr<Cell>(t->cells), ptr<int>(t->leaves),
+                                           ptr<int>(t->inner), ptr<int>(t->leaf_of));
+    if (ninner > 0)
+        k_child_counts<<<blocks(ninner, 256), 256, 0, st>>>(ptr<Cell>(t->cells), t->ncell, ptr<int>(t->inner), ninner);
+    return hip_check(hipGetLastError(), "tree cells");
 }
 
 }  // namespace hfmm

@@ -13,7 +13,7 @@
 // (chunks of 16: 1% slower).
 //
 // FP64 form: absolute FP64 positions, and for r_cut up to 5 r_s the same split of the force
-// law, f_(1) = -1/r^3 + S(t)/(8 r_s^3), with S of degree 18 or 22 fitted to FP64 rounding
+// law, f_(1) = -1/r^3 + S(t)/(8 r_s^3), with S of degree 19 or 22 fitted to FP64 rounding
 // (beyond that erfc and exp of the device math library); sums in FP64.
 // FP32 form: FP32 coordinates relative to each particle's leaf centre, the exact
 // centre offset c_B + s box - c_A added when staging, and
@@ -105,7 +105,7 @@ struct P2PConst64 {
     double c[kP2PPoly64Max];  // S(t) / (8 r_s^3), coefficients of t^0 .. t^(ncoef-1)
     double two_over_rc2, rc2, rs, irc2, irc3;
     float rc;   // for the box tests
-    int ncoef;  // 19 or 23; 0: no fit (erfc and exp)
+    int ncoef;  // 20 or 23; 0: no fit (erfc and exp)
 };
 // Sink particles per pass over a leaf's list unless fmm_params.p2p_chunk names 16 or 64: a
 // leaf of more is processed in Morton-ordered chunks of this many, each tested against the
@@ -466,7 +466,7 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
 // (a load under its own branch waited for the one before it, and the sink's own load for all
 // of them: 300,007 particles, polynomial split, step 3.50 -> 3.33 ms; 2M 8.13 -> 8.01 ms; 64-box
 // forest 11.77 -> 11.46 ms).
-// FP64 form: bound by FP64 issue, 42 operations a pair with the degree-18 law against well over
+// FP64 form: bound by FP64 issue, 43 operations a pair with the degree-19 law against well over
 // 200 of erfc, exp, the square root and the division, on the pairs the box tests leave (62% of
 // the listed ones on the 2M box) at four waves per SIMD instead of three: uniform 32^3 step
 // 1.21 -> 0.83 ms, 262,144 clustered step 9.0 -> 4.5 ms.
@@ -657,8 +657,8 @@ static double fit_S64(double vcut, int m, double *coef)
     return worst;
 }
 
-// FP64 constants: the shorter fit whose error stays within FP64 rounding (19 coefficients
-// serve r_cut up to about 4.5 r_s, 23 up to 5 r_s), else none.  The last fit is kept, by its
+// FP64 constants: the shorter fit whose error stays within FP64 rounding (20 coefficients
+// serve r_cut up to about 4.8 r_s, 23 up to 5 r_s), else none.  The last fit is kept, by its
 // vcut alone.
 static void p2p_setup64(const fmm_params *P, P2PConst64 &k)
 {
@@ -678,7 +678,7 @@ static void p2p_setup64(const fmm_params *P, P2PConst64 &k)
     std::lock_guard<std::mutex> lk(mu);
     if (vcut != cached_vcut) {
         cached_m = 0;
-        for (int m : {19, kP2PPoly64Max})
+        for (int m : {20, kP2PPoly64Max})
             if (!cached_m && fit_S64(vcut, m, cached) <= kTol) cached_m = m;
         cached_vcut = vcut;
     }
@@ -820,7 +820,7 @@ template <int CHUNK>
 static void launch_p2p64(const fmm_params *P, const P2PConst64 &k, const P2PArgs &a, int count, hipStream_t st)
 {
     if (P->split == 1) k_p2p<true, true, 1, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (k.ncoef == 19) k_p2p<true, false, 19, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else if (k.ncoef == 20) k_p2p<true, false, 20, CHUNK><<<count, 64, 0, st>>>(a, k);
     else if (k.ncoef == 23) k_p2p<true, false, 23, CHUNK><<<count, 64, 0, st>>>(a, k);
     else k_p2p<true, false, 0, CHUNK><<<count, 64, 0, st>>>(a, k);
 }

@@ -316,8 +316,8 @@ int fmm_mlp_grad(const float *params, const float *mu, const float *isd, const f
  * HIP graph, training loops that must not call hipMalloc, harnesses that forbid it.  Same
  * arguments, kernels and result as fmm_mlp_grad (to FP32 rounding: the class-weight sum
  * is formed on the device), but it allocates nothing, synchronises nothing and reads
- * nothing back: the per-sample activations and gradients live in a fixed device array of
- * the library (9.4 MB per GPU, held until the process ends) sized for B <= 8192 samples;
+ * nothing back: the workgroups' gradients live in a fixed device array of
+ * the library (5.9 MB per GPU, held until the process ends) sized for B <= 8192 samples;
  * a larger B is rejected with FMM_ERR_ARG.  The loss is cleared by a kernel, not a memset.
  * Labels outside [0, 8) get weight 0; if the weights of the batch's labels sum to 0 the
  * loss and gradient are 0 (fmm_mlp_grad returns FMM_ERR_ARG there).  Every call on a GPU

@@ -98,8 +98,8 @@ static int p2p_level_hook(void *ctx, int l, hipStream_t st)
         (rc = hip_check(hipStreamWaitEvent(c.ax, t->lev[l], 0), "event wait")))
         return rc;
     if (t->timing) (void)hipEventRecord(t->p2p_t0[l], c.ax);  // timing only
-    // the traversal's overflow flag (counter byte 96): void lists are not read
-    if ((rc = p2p_range(t, c.P, first, count, ptr<int>(t->counters) + 24, c.ax))) return rc;
+    // the traversal's overflow flag: void lists are not read
+    if ((rc = p2p_range(t, c.P, first, count, ptr<int>(t->counters) + kErrByte / 4, c.ax))) return rc;
     if (t->timing) (void)hipEventRecord(t->p2p_t1[l], c.ax);
     return 0;
 }
@@ -485,9 +485,13 @@ int fmm_get_stats(const fmm_tree *tc, fmm_stats *out)
     fmm_tree *t = const_cast<fmm_tree *>(tc);
     if (t->counters.p && t->n > 0) {  // the P2P kernel counts listed pairs on the device
         unsigned long long v = 0, e = 0;
-        if (hipMemcpy(&v, ptr<unsigned long long>(t->counters) + 1, 8, hipMemcpyDeviceToHost) != hipSuccess ||
-            hipMemcpy(&e, ptr<unsigned long long>(t->counters) + 24, 8, hipMemcpyDeviceToHost) != hipSuccess)
+        std::vector<unsigned long long> c((size_t)kP2PSlots * kSlotWords);
+        if (hipMemcpy(c.data(), ptr<char>(t->counters) + kP2PByte, c.size() * 8, hipMemcpyDeviceToHost) != hipSuccess)
             return set_error(FMM_ERR_HIP, "reading counters");
+        for (int s = 0; s < kP2PSlots; ++s) {
+            v += c[(size_t)s * kSlotWords];
+            e += c[(size_t)s * kSlotWords + 1];
+        }
         t->stats.p2p_pairs = (int64_t)v;
         t->stats.p2p_evaluated = (int64_t)e;
     }

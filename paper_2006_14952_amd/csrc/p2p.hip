@@ -49,8 +49,9 @@ struct P2PArgs {
     double box;
     double *nearf;  // 3 x n SoA
     int n;
-    unsigned long long *pairs;  // listed particle pairs (sum of n_A n_B over P2P leaf pairs)
-    unsigned long long *evaluated;  // particle pairs actually evaluated (after the box tests)
+    // kP2PSlots lines: [0] listed particle pairs (sum of n_A n_B over P2P leaf pairs), [1]
+    // particle pairs evaluated (after the box tests)
+    unsigned long long *slots;
     const float4 *bbox;             // per cell: lo, hi of the particles relative to the cell centre
     int first;                      // k_p2p: block b takes sink leaf leaves[first + b]
     const int *err;                 // k_p2p: if non-NULL and non-zero, the lists are void: do nothing
@@ -456,8 +457,9 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
         __syncthreads();
     }
     if (lane == 0) {
-        atomicAdd(a.pairs, npairs);
-        atomicAdd(a.evaluated, nevald);
+        unsigned long long *c = a.slots + (size_t)(li % kP2PSlots) * kSlotWords;
+        atomicAdd(&c[0], npairs);
+        atomicAdd(&c[1], nevald);
     }
 }
 
@@ -714,8 +716,7 @@ static void p2p_args(fmm_tree *t, P2PArgs &a)
     a.box = t->box;
     a.nearf = ptr<double>(t->nearf);
     a.n = (int)t->n;
-    a.pairs = ptr<unsigned long long>(t->counters) + 1;
-    a.evaluated = ptr<unsigned long long>(t->counters) + 24;
+    a.slots = reinterpret_cast<unsigned long long *>(ptr<char>(t->counters) + kP2PByte);
     a.bbox = ptr<float4>(t->bbox);
     a.first = 0;
     a.err = nullptr;

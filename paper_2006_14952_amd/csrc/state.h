@@ -5,13 +5,34 @@
 #include "common.h"
 
 namespace hfmm {
-constexpr int kHostInts = 1024;
+constexpr int kHostInts = 4096;
 // Interaction list kinds: 0 M2L, 1 P2P, 2 handed to the children, 3 candidate pairs
 // (training export), 4 M2L pairs of the learned selector (all orders; the order of each
 // entry in a byte beside it).
 constexpr int kKinds = 5;
 constexpr int kKindCand = 3, kKindOrd = 4;
 constexpr int kOrders = 7;  // learned selector: M2L orders 2 .. 8
+
+// Device counters of one evaluation (fmm_tree::counters), in bytes from its start:
+//   kErrByte    int: the traversal's overflow bits
+//   kPoolByte   chunk counters of the list kinds, one 128-byte line each
+//   kTravByte   kTravSlots lines of 64-bit sums of the traversal: visits, M2L pairs, P2P
+//               pairs, M2L pairs of each learned order; the readback ends after them
+//   kP2PByte    kP2PSlots lines of 64-bit sums of P2P: listed pairs, evaluated pairs
+// Atomics on one address end one after the other, about 13 ns apart on this GPU: with one
+// address per sum, a 4096-wave traversal launch took 160 us whatever its work (three sums a
+// wave) and P2P of 4096 leaves 106 us of its 160.  A wave adds to the line of its
+// workgroup's number, and the host sums the lines.  Traversal of the 2M box 1.84 -> 1.04 ms, with the
+// learned selector (ten sums a wave) 2.90 -> 1.16, of 262,144 particles 1.15 -> 0.52.
+constexpr int kErrByte = 96;
+constexpr int kPoolByte = 256;
+constexpr int kPoolStride = 32;  // ints between the pool counters
+constexpr int kSlotWords = 16;   // 64-bit words per line
+constexpr int kTravSlots = 64, kP2PSlots = 256;
+constexpr int kTravByte = kPoolByte + kKinds * kPoolStride * 4;
+constexpr int kP2PByte = kTravByte + kTravSlots * kSlotWords * 8;
+constexpr int kCounterBytes = kP2PByte + kP2PSlots * kSlotWords * 8;
+static_assert(kP2PByte <= kHostInts * 4, "counter readback exceeds the pinned area");
 }
 
 struct fmm_tree {

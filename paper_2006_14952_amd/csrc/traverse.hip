@@ -70,7 +70,7 @@ struct TravArgs {
     uint32_t *stack; // per-wave stacks when they do not fit in LDS
     int stk_cap;
     int *err;        // bit 0: stack overflow, bit 1: pool overflow
-    unsigned long long *counters;  // [0] visits, [1] listed particle pairs (P2P kernel), [2] M2L, [3] P2P
+    unsigned long long *slots;  // kTravSlots lines: [0] visits, [1] M2L, [2] P2P, [3 ..] M2L of each learned order
     // candidate pairs / learned selector
     double theta_max2;             // candidates have (L/S_c)^2 <= theta_max2
     double box, rs, rcut;
@@ -80,7 +80,6 @@ struct TravArgs {
 };
 
 constexpr int kChunkBlock = 32;   // chunks taken from a pool per atomic
-constexpr int kPoolStride = 32;   // ints between the pool counters (one 128-byte line each)
 constexpr int kCandQ = 128;       // learned: ring of candidate pairs (at most 63 wait between steps)
 
 struct ListState {
@@ -382,11 +381,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
             ws[k] = bnext[k];
             ws[kKinds + k] = bend[k];
         }
-        atomicAdd(&a.counters[0], visits);
-        atomicAdd(&a.counters[2], nm2l);
-        atomicAdd(&a.counters[3], np2p);
+        unsigned long long *c = a.slots + (size_t)(blockIdx.x % kTravSlots) * kSlotWords;
+        atomicAdd(&c[0], visits);
+        atomicAdd(&c[1], nm2l);
+        atomicAdd(&c[2], np2p);
         if (MODE == kModeLearned)
-            for (int k = 0; k < kOrders; ++k) atomicAdd(&a.counters[16 + k], (unsigned long long)nord[k]);
+            for (int k = 0; k < kOrders; ++k) atomicAdd(&c[3 + k], (unsigned long long)nord[k]);
     }
 }
 
@@ -440,10 +440,6 @@ __global__ void k_cell_features(const T *__restrict__ M, int stride, int ncell, 
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c < ncell) cf[c] = cell_features<T>(M + (size_t)c * stride);
 }
-
-constexpr int kPoolByte = 256;
-constexpr int kCounterBytes = kPoolByte + kKinds * kPoolStride * 4;
-static_assert(kCounterBytes <= kHostInts * 4, "counter readback exceeds the pinned area");
 
 // Wave w starts with chunks [w kChunkBlock, (w+1) kChunkBlock) of every list kind, and
 // the counters start past those blocks: no wave needs an atomic for its first block.
@@ -527,8 +523,6 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
         nw = nw < cap ? nw : cap;
         if ((rc = grow(t->tstack, (size_t)nw * t->stk_cap * 4))) return rc;
         if ((rc = grow(t->wstate, (size_t)nw * 2 * kKinds * sizeof(int)))) return rc;
-        // counters: [0..3] 64-bit stats, err at byte 96, 64-bit M2L counts per learned order
-        // at byte 128, P2P evaluated pairs at byte 192, pool counters from byte kPoolByte
         unsigned char *cb = ptr<unsigned char>(t->counters);
         if ((rc = zero_async(cb, kCounterBytes, st))) return rc;  // a kernel: also valid inside a recorded graph
         k_wstate_init<<<(nw + 255) / 256, 256, 0, st>>>(ptr<int>(t->wstate), nw,
@@ -542,10 +536,10 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
             a.next[k] = ptr<int>(t->lnext[k]);
             a.cap[k] = t->lcap[k];
         }
-        a.counters = reinterpret_cast<unsigned long long *>(cb);
+        a.slots = reinterpret_cast<unsigned long long *>(cb + kTravByte);
         a.pool = reinterpret_cast<int *>(cb + kPoolByte);
         a.wstate = ptr<int>(t->wstate);
-        a.err = reinterpret_cast<int *>(cb + 96);
+        a.err = reinterpret_cast<int *>(cb + kErrByte);
         a.head = ptr<int>(t->lhead);
         a.cnt = ptr<int>(t->lcnt);
         a.ord = ptr<unsigned char>(t->lord);
@@ -574,22 +568,24 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
         // pools and stacks fitted; the lists, their sizes and every wave's use of pool blocks
         // and stack (sinks are dealt statically) repeat exactly, so no readback is needed.
         if (t->capturing) return 0;
-        if ((rc = hip_check(hipMemcpyAsync(t->host, cb, kCounterBytes, hipMemcpyDeviceToHost, st), "counters")))
+        if ((rc = hip_check(hipMemcpyAsync(t->host, cb, kP2PByte, hipMemcpyDeviceToHost, st), "counters")))
             return rc;
         if ((rc = hip_check(hipStreamSynchronize(st), "traversal sync"))) return rc;
-        unsigned long long c64[4];
+        unsigned long long sum[3 + kOrders] = {0};
         int pools[kKinds], err;
-        memcpy(c64, t->host, 32);
+        for (int s = 0; s < kTravSlots; ++s) {
+            unsigned long long c[3 + kOrders];
+            memcpy(c, (char *)t->host + kTravByte + (size_t)s * kSlotWords * 8, sizeof(c));
+            for (int k = 0; k < 3 + kOrders; ++k) sum[k] += c[k];
+        }
         for (int k = 0; k < kKinds; ++k)  // kinds this mode does not write keep their size
             pools[k] = want[k] ? t->host[kPoolByte / 4 + k * kPoolStride] : 0;
-        memcpy(&err, (char *)t->host + 96, 4);
+        memcpy(&err, (char *)t->host + kErrByte, 4);
         if (err == 0) {
-            unsigned long long ord[kOrders];
-            memcpy(ord, (char *)t->host + 128, sizeof(ord));
-            for (int k = 0; k < kOrders; ++k) t->stats.n_m2l_by_order[k] = mode == kModeLearned ? (int64_t)ord[k] : 0;
-            t->n_visit = (int64_t)c64[0];
-            t->n_m2l = (int64_t)c64[2];
-            t->n_p2p = (int64_t)c64[3];
+            for (int k = 0; k < kOrders; ++k) t->stats.n_m2l_by_order[k] = mode == kModeLearned ? (int64_t)sum[3 + k] : 0;
+            t->n_visit = (int64_t)sum[0];
+            t->n_m2l = (int64_t)sum[1];
+            t->n_p2p = (int64_t)sum[2];
             t->trav_mode = mode;
             return 0;
         }

@@ -42,10 +42,15 @@ __host__ __device__ constexpr int midx(int x, int y, int z)
 // Traversal thresholds: every distance of a cell pair is an integer multiple of
 // u_l = box / 2^(l+1), l the finer level of the pair.
 struct MacConst {
-    double cut2[kMaxLevel + 1];  // (r_cut / u_l)^2
+    double cut2;    // (r_cut / u_0)^2; at level l, 4^l times as much
     double theta2;
     int mode;
-    int pad;
+    // Whole-number forms, used where `whole` says that FP32 holds them (see mac_setup): a
+    // squared distance is beyond r_cut iff it exceeds cut[l]; a pair whose larger cell is 2^k
+    // times the smaller passes item 2 iff its squared centre distance is at least acc[k], and
+    // is a selector candidate iff at least cand[k].
+    int whole;
+    float cut[kMaxLevel + 1], acc[kMaxLevel + 1], cand[kMaxLevel + 1];
 };
 
 // Interaction lists are chains of kChunk-entry chunks (entry = source cell << 5 | image).

@@ -138,7 +138,8 @@ __device__ __forceinline__ short4v relu_pack(const float4v c, const float4 bias)
 }
 
 // Logits of the 64 pairs of a wave (one per lane; lanes without a pair take part with
-// zero features).  `act` is 64 x 64 BF16 of LDS, `out` receives 8 logits per lane.
+// zero features).  `act` is 64 x kActRow BF16 of LDS (16-byte aligned; the 16 inputs of each
+// pair, then its 8 FP32 logits), `out` receives 8 logits per lane.
 // MFMA operand layout (per lane l, lane group g = l/16): v_mfma_f32_16x16x16_bf16 takes
 // A[i = l%16][k = 4g+r] and B[k = 4g+r][j = l%16], r = 0..3; v_mfma_f32_16x16x32_bf16 takes
 // 8 values per lane, K slots (g, r), r = 0..7, paired between A and B the same way; both
@@ -150,6 +151,8 @@ __device__ __forceinline__ bf8v cat_bf8(const short4v lo, const short4v hi)
     return __builtin_bit_cast(bf8v, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+constexpr int kActRow = 16;
+
 __device__ __forceinline__ void mlp_logits_wave(const MlpWeights &W, const float *fin, short *act, float *out)
 {
     const int lane = threadIdx.x & 63;
@@ -159,7 +162,7 @@ __device__ __forceinline__ void mlp_logits_wave(const MlpWeights &W, const float
 #pragma unroll
         for (int k = 0; k < kFeat; k += 2)
             pk[k / 2] = pack_bf16((fin[k] - W.mu[k]) * W.isd[k], (fin[k + 1] - W.mu[k + 1]) * W.isd[k + 1]);
-        uint4 *row = reinterpret_cast<uint4 *>(act + lane * 64);
+        uint4 *row = reinterpret_cast<uint4 *>(act + lane * kActRow);
         row[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         row[1] = make_uint4(pk[4], pk[5], pk[6], pk[7]);
     }
@@ -173,7 +176,7 @@ __device__ __forceinline__ void mlp_logits_wave(const MlpWeights &W, const float
     {
         short4v a1[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a1[t] = *reinterpret_cast<const short4v *>(act + (16 * t + li) * 64 + 4 * lk);
+        for (int t = 0; t < 4; ++t) a1[t] = *reinterpret_cast<const short4v *>(act + (16 * t + li) * kActRow + 4 * lk);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const short4v w = W.w1[u][lane];

@@ -387,7 +387,7 @@ __global__ void k_adam(float *__restrict__ w, const float *__restrict__ g, float
 __global__ __launch_bounds__(64) void k_mlp_infer(const MacModel *__restrict__ M, const float *__restrict__ X, int B,
                                                   float *__restrict__ Z)
 {
-    __shared__ short act[64 * 64];
+    __shared__ __align__(16) short act[64 * kActRow];
     int s = blockIdx.x * 64 + threadIdx.x;
     float f[kFeat], lg[kCls];
     for (int k = 0; k < kFeat; ++k) f[k] = s < B ? X[(size_t)s * kFeat + k] : 0.0f;

@@ -15,6 +15,15 @@
 // with an atomic counter, so one pass and no host round trip per level is needed; a
 // pool or stack that runs out is detected (the counter keeps the exact demand) and the
 // traversal is rerun with enough room.  Per-sink list order is deterministic.
+//
+// Bound by the length of a step (64 pairs) in the waves with the heaviest sinks: a level ends
+// with its longest wave, and more waves per SIMD do not shorten it (4, 6 and 8 measured
+// alike).  So a step is kept short: the top of the stack and the open ends of the lists lie in
+// LDS, whose accesses of one wave stay in order without waits, a list chunk leaves as one
+// store when it is full, and the acceptance criterion runs on whole numbers in FP32.
+// Traversal against pushes to device memory and FP64 decisions: 2M box 1.14 -> 0.78 ms, 64-box
+// forest 1.55 -> 1.10, 16.7M 2.64 -> 1.96, 262,144 particles 0.61 -> 0.50, 2M learned 1.20 -> 1.03.
+#include <math.h>
 #include <string.h>
 
 #include "mlp.h"
@@ -39,7 +48,7 @@ __device__ __forceinline__ int mac_decide(int4 a, int4 b, int s, const MacConst 
     double A0 = fabs(R0), A1 = fabs(R1), A2 = fabs(R2);
     double g0 = fmax(A0 - half, 0.0), g1 = fmax(A1 - half, 0.0), g2 = fmax(A2 - half, 0.0);
     double sm2 = g0 * g0 + g1 * g1 + g2 * g2;
-    double cut2 = ldexp(mc.cut2[0], 2 * l);  // equals (r_cut / u_l)^2 exactly
+    double cut2 = ldexp(mc.cut2, 2 * l);  // equals (r_cut / u_l)^2 exactly
     double sc2 = R0 * R0 + R1 * R1 + R2 * R2;
     if (!(mc.mode & 4)) {  // truncated MAC; mode bit 2: conventional MAC, item 2 alone
         if (sm2 > cut2) return 0;
@@ -82,9 +91,17 @@ struct TravArgs {
 constexpr int kChunkBlock = 32;   // chunks taken from a pool per atomic
 constexpr int kCandQ = 128;       // learned: ring of candidate pairs (at most 63 wait between steps)
 
+// A list being written: its first and latest chunk and its entries so far.  The entries past
+// the last full chunk wait in an LDS ring of two chunks (slot = entry mod 128).
 struct ListState {
-    int head, cur, fill, tot;
+    int head, cur, tot;
 };
+struct ListRing {
+    uint32_t item[2 * kChunk];
+};
+
+// Orders the LDS accesses of one wave for the compiler; the hardware keeps them in order.
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Next free chunk of list k.  Each wave takes kChunkBlock chunks per atomic and hands
 // them out itself; the unused rest of its block passes to the wave with the same index
@@ -108,91 +125,130 @@ __device__ __forceinline__ int new_chunk(const TravArgs &a, int k, int *bnext, i
     return c;
 }
 
-// Append `item` of every lane with `pred` to list k, in lane order.  Chunks are taken
-// only when an entry needs them, so a chain never ends in an empty chunk.  ORD: the
-// byte `ob` is stored beside the entry (list kind kKindOrd).
-template <bool ORD = false>
-__device__ __forceinline__ void emit(const TravArgs &a, int k, ListState &L, int *bnext, int *bend, bool pred,
-                                     uint32_t item, uint64_t lt, int lane, unsigned char ob = 0)
+// Write entries [first, first + n) of list k (a chunk's worth, n <= 64) from its ring.  ORD:
+// with the byte beside each entry (list kind kKindOrd).
+template <bool ORD>
+__device__ __forceinline__ void flush(const TravArgs &a, int k, ListState &L, const ListRing &ring,
+                                      const unsigned char *ordring, int *bnext, int *bend, int first, int n, int lane)
 {
-    uint64_t mask = __ballot(pred);
-    if (mask == 0) return;
-    int m = __popcll(mask);
-    int rank = __popcll(mask & lt);
-    if (L.cur < 0 || L.fill == kChunk) {
-        int c = new_chunk(a, k, bnext, bend, lane);
-        if (L.cur < 0) L.head = c;
-        else if (lane == 0) a.next[k][L.cur] = c;
-        L.cur = c;
-        L.fill = 0;
+    const int c = new_chunk(a, k, bnext, bend, lane);
+    if (L.cur < 0) L.head = c;
+    else if (lane == 0) a.next[k][L.cur] = c;
+    L.cur = c;
+    if (lane < n) {
+        const int at = (first + lane) & (2 * kChunk - 1);
+        a.items[k][(size_t)c * kChunk + lane] = ring.item[at];
+        if (ORD) a.ord[(size_t)c * kChunk + lane] = ordring[at];
     }
-    int room = kChunk - L.fill;
-    if (pred && rank < room) {
-        const size_t at = (size_t)L.cur * kChunk + L.fill + rank;
-        a.items[k][at] = item;
-        if (ORD) a.ord[at] = ob;
-    }
-    if (m > room) {
-        int c = new_chunk(a, k, bnext, bend, lane);
-        if (lane == 0) a.next[k][L.cur] = c;
-        L.cur = c;
-        if (pred && rank >= room) {
-            const size_t at = (size_t)c * kChunk + rank - room;
-            a.items[k][at] = item;
-            if (ORD) a.ord[at] = ob;
-        }
-        L.fill = m - room;
-    } else {
-        L.fill += m;
-    }
-    L.tot += m;
 }
 
-// Full MAC evaluation for the candidate logic: code as mac_decide, plus whether item 3
-// forced the opening and (L / S_c)^2.
+// Append `item` of every lane with `pred` to list k, in lane order.  A chunk is taken when
+// 64 entries are there (or at the sink's end), so a chain never ends in an empty chunk.
+template <bool ORD = false>
+__device__ __forceinline__ void emit(const TravArgs &a, int k, ListState &L, ListRing &ring, unsigned char *ordring,
+                                     int *bnext, int *bend, bool pred, uint32_t item, uint64_t lt, int lane,
+                                     unsigned char ob = 0)
+{
+    const uint64_t mask = __ballot(pred);
+    if (mask == 0) return;
+    const int at = (L.tot + __popcll(mask & lt)) & (2 * kChunk - 1);
+    if (pred) {
+        ring.item[at] = item;
+        if (ORD) ordring[at] = ob;
+    }
+    const int old = L.tot;
+    L.tot += __popcll(mask);
+    if ((L.tot ^ old) & ~(kChunk - 1)) {  // a chunk is full (64 entries at most were added)
+        lds_order();
+        flush<ORD>(a, k, L, ring, ordring, bnext, bend, old & ~(kChunk - 1), kChunk, lane);
+        lds_order();
+    }
+}
+
+// Full MAC evaluation for the candidate logic: code as mac_decide, plus whether the pair is a
+// candidate of the selector (not neglected, not forced open by item 3, (L / S_c)^2 <= theta_max2).
 struct MacEval {
     int code;
-    bool straddle;
-    double q2;
+    bool cand;
 };
 
-__device__ __forceinline__ MacEval mac_eval(int4 a, int4 b, int s, const MacConst &mc)
+__device__ __forceinline__ MacEval mac_eval(int4 a, int4 b, int s, const MacConst &mc, double theta_max2)
 {
-    MacEval r;
+    MacEval r{0, false};
     PairGeo g = pair_geo(a, b, s);
-    double cut2 = ldexp(mc.cut2[0], 2 * g.l);
+    double cut2 = ldexp(mc.cut2, 2 * g.l);
     double w = (mc.mode & 2) ? g.wb : fmax(g.wa, g.wb);
-    r.q2 = 4.0 * w * w / g.sc2;
-    r.straddle = false;
     if (!(mc.mode & 4)) {  // truncated MAC; mode bit 2: conventional MAC, item 2 alone
-        if (g.sm2 > cut2) {
-            r.code = 0;
-            return r;
-        }
-        r.straddle = (mc.mode & 1) ? (g.sc2 > cut2) : (g.sM2 > cut2);
-        if (r.straddle) {
+        if (g.sm2 > cut2) return r;
+        if ((mc.mode & 1) ? (g.sc2 > cut2) : (g.sM2 > cut2)) {
             r.code = 2;
             return r;
         }
     }
     r.code = (4.0 * w * w <= mc.theta2 * g.sc2) ? 1 : 2;
+    r.cand = 4.0 * w * w / g.sc2 <= theta_max2;
     return r;
 }
 
-// Sinks t = blockIdx.x, blockIdx.x + gridDim.x, ... of one level.
-template <int MODE>
+// The same decisions in FP32 on whole numbers (mc.whole): coordinates and distances are below
+// 2^23, a squared distance that decides is below 2^24, and a larger one, though rounded, stays
+// above every threshold.  tab: the three threshold tables.
+__device__ __forceinline__ MacEval mac_whole(int4 a, int la, int4 b, int s, int mode, const float (*tab)[kMaxLevel + 1])
+{
+    const int lb = xln_level(b.x), l = max(la, lb), da = l - la, db = l - lb;
+    const float cut = tab[0][l];
+    const int k = (mode & 2) ? db : da + db;  // log2 of the size of item 2 in cells of the finer level
+    const float acc = tab[1][k], can = tab[2][k];
+    int X = ((2 * xln_ix(a.x) + 1) << da) - ((2 * xln_ix(b.x) + 1) << db);
+    int Y = ((2 * a.y + 1) << da) - ((2 * b.y + 1) << db);
+    int Z = ((2 * a.z + 1) << da) - ((2 * b.z + 1) << db);
+    if (__ballot(s != 13)) {  // some pair is with a periodic image
+        const int sx = (s * 57) >> 9, q = s - 9 * sx, sy = (q * 11) >> 5, sz = q - 3 * sy;
+        X -= (int)((unsigned)(sx - 1) << (l + 1));
+        Y -= (int)((unsigned)(sy - 1) << (l + 1));
+        Z -= (int)((unsigned)(sz - 1) << (l + 1));
+    }
+    const float half = (float)((1 << da) + (1 << db));
+    const float ax = fabsf((float)X), ay = fabsf((float)Y), az = fabsf((float)Z);
+    const float gx = fmaxf(ax - half, 0.0f), gy = fmaxf(ay - half, 0.0f), gz = fmaxf(az - half, 0.0f);
+    const float sm2 = fmaf(gx, gx, fmaf(gy, gy, gz * gz)), sc2 = fmaf(ax, ax, fmaf(ay, ay, az * az));
+    const float fx = ax + half, fy = ay + half, fz = az + half;
+    const float far2 = (mode & 1) ? sc2 : fmaf(fx, fx, fmaf(fy, fy, fz * fz));
+    const bool in = !(sm2 > cut), whole = !(far2 > cut);
+    MacEval r;
+    r.code = in ? (whole && sc2 >= acc ? 1 : 2) : 0;
+    r.cand = in && whole && sc2 >= can;
+    return r;
+}
+
+// Pairs awaiting a decision: positions [0, sp) of a stack whose last entries, from `base` up,
+// lie in an LDS ring and the earlier ones in the wave's device memory.
+constexpr int kStackLds = 1024;  // a step pushes at most 512 entries
+
+// Sinks t = blockIdx.x, blockIdx.x + gridDim.x, ... of one level.  WHOLE: the acceptance
+// criterion on whole numbers in FP32.
+template <int MODE, bool WHOLE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kModeLearned ? 3 : 4))) void k_traverse(TravArgs a, MacConst mc)
 {
-    __shared__ short mlp_act[MODE == kModeLearned ? 64 * 64 : 1];
+    constexpr int kM2L = MODE == kModeLearned ? kKindOrd : 0;
+    __shared__ __align__(16) short mlp_act[MODE == kModeLearned ? 64 * kActRow : 1];
     __shared__ uint32_t cand_q[MODE == kModeLearned ? kCandQ : 1];
+    __shared__ uint32_t stk[kStackLds];
+    __shared__ ListRing rings[MODE == kModeExport ? 4 : 3];  // M2L, P2P, handed down, candidates
+    __shared__ unsigned char ordring[MODE == kModeLearned ? 2 * kChunk : 1];
+    __shared__ float tab[WHOLE ? 3 : 1][kMaxLevel + 1];
 
     const int lane = threadIdx.x;
     const uint64_t lt = (1ull << lane) - 1ull;
-    // per-wave stack of pairs still to decide, in device memory (L2 resident); measured as
-    // fast as an LDS stack, and it leaves the LDS to the learned selector
-    uint32_t *stk = a.stack + (size_t)blockIdx.x * a.stk_cap;
+    uint32_t *deep = a.stack + (size_t)blockIdx.x * a.stk_cap;  // the stack below `base`
     const int scap = a.stk_cap;
     const int4 *cellc = a.cellc;
+    if (WHOLE && lane <= kMaxLevel) {
+        tab[0][lane] = mc.cut[lane];
+        tab[WHOLE ? 1 : 0][lane] = mc.acc[lane];
+        tab[WHOLE ? 2 : 0][lane] = mc.cand[lane];
+    }
+    __syncthreads();
     unsigned long long visits = 0, nm2l = 0, np2p = 0;
     unsigned nord[kOrders] = {0, 0, 0, 0, 0, 0, 0};  // learned: this wave's M2L pairs per order
     int bnext[kKinds], bend[kKinds];
@@ -212,16 +268,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
         int ninh = 27, ichunk = 0;
         if (root && a.cells[A].end == a.cells[A].beg) ninh = 0;  // empty box of a batch: nothing to do
         if (!root) {
-            ninh = a.cnt[2 * a.ncell + parentA];
-            ichunk = a.head[2 * a.ncell + parentA];
+            ninh = __builtin_amdgcn_readfirstlane(a.cnt[2 * a.ncell + parentA]);
+            ichunk = __builtin_amdgcn_readfirstlane(a.head[2 * a.ncell + parentA]);
         }
         double mA0 = 0.0;
         if (MODE == kModeLearned) mA0 = a.cf[A].x;
-        ListState Ls[kKinds];
-#pragma unroll
-        for (int k = 0; k < kKinds; ++k) Ls[k] = ListState{-1, -1, 0, 0};
+        ListState Lm{-1, -1, 0}, Lp{-1, -1, 0}, Ld{-1, -1, 0}, Lc{-1, -1, 0};
         unsigned oc[kOrders] = {0, 0, 0, 0, 0, 0, 0};  // learned: this sink's M2L pairs per order
-        int sp = 0;
         int qhead = 0, qtail = 0;  // learned: queue of candidate pairs awaiting the selector
         bool failed = false;
         // the inherited pairs go onto the stack first, so every step takes a full batch of
@@ -230,55 +283,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
             if (lane == 0) atomicOr(a.err, 1);
             continue;
         }
+        int sp = ninh, base = ninh > kStackLds ? (ninh - kStackLds + 63) & ~63 : 0;
         if (root) {
             if (lane < ninh) stk[lane] = (uint32_t)A << 5 | (uint32_t)lane;
         } else {
             for (int e0 = 0; e0 < ninh; e0 += kChunk) {
-                if (e0 > 0) ichunk = a.next[2][ichunk];
-                if (e0 + lane < ninh) stk[e0 + lane] = a.items[2][(size_t)ichunk * kChunk + lane];
+                const uint32_t v = a.items[2][(size_t)ichunk * kChunk + lane];
+                if (e0 + kChunk < ninh) ichunk = __builtin_amdgcn_readfirstlane(a.next[2][ichunk]);
+                if (e0 >= base) stk[(e0 + lane) & (kStackLds - 1)] = v;  // past ninh: free slots
+                else deep[e0 + lane] = v;                               // base is a multiple of 64
             }
         }
-        sp = ninh;
-        __syncthreads();  // the copied entries are written before they are popped
-
-        // Lists and stack for decided pairs of the lanes with `valid`: `m2l_ord` >= 2 puts
-        // the pair on an M2L list (order m2l_ord in learned mode, else plain), `opened`
-        // hands it to P2P, to the children of A, or opens the source.  Returns false if
-        // the stack overflowed.
-        auto finish = [&](bool valid, uint32_t it, int4 gb, int m2l_ord, bool opened) __attribute__((always_inline))
-            -> bool {
-            const int lvB = xln_level(gb.x);
-            const bool leafB = xln_nchild(gb.x) == 0;
-            const bool is_m2l = valid && m2l_ord >= 2;
-            opened = valid && opened;
-            const bool is_p2p = opened && leafA && leafB;
-            const bool is_pd = opened && !is_p2p && !leafA && (lvA <= lvB || leafB);
-            const bool open_src = opened && !is_p2p && !is_pd;
-            if (MODE == kModeLearned) {
-                emit<true>(a, kKindOrd, Ls[kKindOrd], bnext, bend, is_m2l, it, lt, lane, (unsigned char)m2l_ord);
-            } else {
-                emit(a, 0, Ls[0], bnext, bend, is_m2l, it, lt, lane);
-            }
-            emit(a, 1, Ls[1], bnext, bend, is_p2p, it, lt, lane);
-            emit(a, 2, Ls[2], bnext, bend, is_pd, it, lt, lane);
-            const int nch = open_src ? xln_nchild(gb.x) : 0;
-            const int incl = wave_incl_sum(nch);
-            const int tot = __builtin_amdgcn_readlane(incl, 63);
-            if (tot > 0) {
-                if (sp + tot > scap) {
-                    if (lane == 0) atomicOr(a.err, 1);
-                    return false;
-                }
-                if (nch > 0) {
-                    const int off = sp + incl - nch;
-                    const int s = (int)(it & 31);
-                    for (int q = 0; q < nch; ++q) stk[off + q] = (uint32_t)(gb.w + q) << 5 | (uint32_t)s;
-                }
-                sp += tot;
-                __syncthreads();  // pushes complete before the next pop reads them
-            }
-            return true;
-        };
+        lds_order();
 
         for (;;) {
             // next batch: a flush of the candidate queue (learned: when 64 wait, or when
@@ -289,8 +305,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
                 fk = 64;
             } else if (sp > 0) {
                 kk = sp < 64 ? sp : 64;
+                if (sp - kk < base) {  // the LDS part holds less than the batch: fetch half a ring below it
+                    __syncthreads();
+                    const int nb = base > kStackLds / 2 ? base - kStackLds / 2 : 0;
+                    for (int p = nb; p < base; p += 64) stk[(p + lane) & (kStackLds - 1)] = deep[p + lane];
+                    base = nb;
+                    lds_order();
+                }
                 sp -= kk;
-                if (lane < kk) it = stk[sp + lane];
+                it = stk[(sp + lane) & (kStackLds - 1)];
             } else if (MODE == kModeLearned && qtail > qhead) {
                 fk = qtail - qhead;
             } else {
@@ -302,7 +325,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
             if (MODE == kModeLearned && fk > 0) {
                 // the selector decides fk queued candidates at once (features, MLP on the
                 // matrix cores, order decoding); not accepted means opened
-                __syncthreads();  // queued entries are written before other lanes read them
+                lds_order();
                 valid = lane < fk;
                 it = valid ? cand_q[(qhead + lane) & (kCandQ - 1)] : 0u;
                 qhead += fk;
@@ -323,20 +346,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
             } else {
                 visits += kk;
                 valid = lane < kk;
-                int d = 0;
-                bool cand = false;
+                it = valid ? it : (uint32_t)A << 5 | 13u;  // lanes past the batch: the sink itself, not used
                 const int B = (int)(it >> 5), s = (int)(it & 31);
-                if (valid) {
-                    gb = cellc[B];
-                    if (MODE == kModePlain) {
-                        d = mac_decide(ga, gb, s, mc);
-                    } else {
-                        MacEval ev = mac_eval(ga, gb, s, mc);
-                        d = ev.code;
-                        cand = d != 0 && !ev.straddle && ev.q2 <= a.theta_max2;
-                    }
-                }
-                if (MODE == kModeExport) emit(a, kKindCand, Ls[kKindCand], bnext, bend, cand, it, lt, lane);
+                gb = cellc[B];
+                MacEval ev{0, false};
+                if (WHOLE) ev = mac_whole(ga, lvA, gb, s, mc.mode, tab);
+                else if (MODE == kModePlain) ev.code = mac_decide(ga, gb, s, mc);
+                else ev = mac_eval(ga, gb, s, mc, a.theta_max2);
+                const int d = valid ? ev.code : 0;
+                const bool cand = valid && ev.cand;
+                if (MODE == kModeExport)
+                    emit(a, kKindCand, Lc, rings[MODE == kModeExport ? 3 : 0], nullptr, bnext, bend, cand, it, lt, lane);
                 if (MODE == kModeLearned) {
                     // candidates wait in the queue; the rest are pruned (d = 0) or opened
                     const uint64_t cm = __ballot(cand);
@@ -350,30 +370,74 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
                     opened = d == 2;
                 }
             }
-            if (!finish(valid, it, gb, ord, opened)) {
+            // lists and stack: `ord` >= 2 puts the pair on an M2L list (order ord in learned
+            // mode, else plain), `opened` hands it to P2P, to the children of A, or opens
+            // the source
+            const bool leafB = xln_nchild(gb.x) == 0;
+            opened = valid && opened;
+            const bool is_p2p = opened && leafA && leafB;
+            const bool is_pd = opened && !is_p2p && !leafA && (lvA <= xln_level(gb.x) || leafB);
+            const bool open_src = opened && !is_p2p && !is_pd;
+            emit<MODE == kModeLearned>(a, kM2L, Lm, rings[0], ordring, bnext, bend, valid && ord >= 2, it, lt, lane,
+                                       (unsigned char)ord);
+            emit(a, 1, Lp, rings[1], nullptr, bnext, bend, is_p2p, it, lt, lane);
+            emit(a, 2, Ld, rings[2], nullptr, bnext, bend, is_pd, it, lt, lane);
+            if (__ballot(open_src) == 0) continue;
+            const int nch = open_src ? xln_nchild(gb.x) : 0;
+            const int incl = wave_incl_sum(nch);
+            const int tot = __builtin_amdgcn_readlane(incl, 63);
+            if (sp + tot > scap) {
+                if (lane == 0) atomicOr(a.err, 1);
                 failed = true;
                 break;
             }
+            if (sp + tot > base + kStackLds) {  // room in the ring: its older half moves out
+                for (int p = base; p < base + kStackLds / 2; p += 64) deep[p + lane] = stk[(p + lane) & (kStackLds - 1)];
+                base += kStackLds / 2;
+                lds_order();
+            }
+            const int off = sp + incl - nch;
+            const uint32_t first = (uint32_t)gb.w << 5 | (it & 31u);
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (q < nch) stk[(off + q) & (kStackLds - 1)] = first + ((uint32_t)q << 5);
+            sp += tot;
+            lds_order();
         }
         if (failed) continue;
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < kKinds; ++k) {
-                a.head[k * a.ncell + A] = Ls[k].head;
-                a.cnt[k * a.ncell + A] = Ls[k].tot;
+        // the open ends of the lists
+        lds_order();
+        auto close = [&](int k, ListState &L, const ListRing &ring) __attribute__((always_inline)) {
+            if (L.tot & (kChunk - 1))
+                flush<false>(a, k, L, ring, nullptr, bnext, bend, L.tot & ~(kChunk - 1), L.tot & (kChunk - 1), lane);
+            if (lane == 0) {
+                a.head[k * a.ncell + A] = L.head;
+                a.cnt[k * a.ncell + A] = L.tot;
             }
-        }
+        };
         if (MODE == kModeLearned) {
-            nm2l += Ls[kKindOrd].tot;
+            if (Lm.tot & (kChunk - 1))
+                flush<true>(a, kM2L, Lm, rings[0], ordring, bnext, bend, Lm.tot & ~(kChunk - 1), Lm.tot & (kChunk - 1), lane);
+            if (lane == 0) {
+                a.head[kM2L * a.ncell + A] = Lm.head;
+                a.cnt[kM2L * a.ncell + A] = Lm.tot;
+            }
+        } else {
+            close(kM2L, Lm, rings[0]);
+        }
+        close(1, Lp, rings[1]);
+        close(2, Ld, rings[2]);
+        if (MODE == kModeExport) close(kKindCand, Lc, rings[MODE == kModeExport ? 3 : 0]);
+        lds_order();
+        nm2l += Lm.tot;
+        np2p += Lp.tot;
+        if (MODE == kModeLearned) {
 #pragma unroll
             for (int o = 0; o < kOrders; ++o) {
                 if (lane == 0) a.ocnt[(size_t)o * a.ncell + A] = (int)oc[o];
                 nord[o] += oc[o];
             }
-        } else {
-            nm2l += Ls[0].tot;
         }
-        np2p += Ls[1].tot;
     }
     if (lane == 0) {
 #pragma unroll
@@ -390,15 +454,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
     }
 }
 
-void mac_setup(const fmm_params *P, MacConst &mc)
+// Smallest whole s with pass(s), pass monotone and guessed to begin near `guess`; "none" past
+// 2^24, which no squared distance that reaches the test exceeds in the whole-number form.
+template <class F> static float first_whole(double guess, F pass)
 {
-    for (int l = 0; l <= kMaxLevel; ++l) {
-        double u = ldexp(P->box, -(l + 1));
-        mc.cut2[l] = (P->r_cut * P->r_cut) / (u * u);
-    }
+    if (!(guess < 16777218.0)) return 3.0e38f;
+    double s = ceil(guess);
+    s = s > 0.0 ? s : 0.0;
+    while (s > 0.0 && pass(s - 1.0)) s -= 1.0;
+    while (s < 16777218.0 && !pass(s)) s += 1.0;
+    return s > 16777216.0 ? 3.0e38f : (float)s;
+}
+
+// Thresholds of the traversal.  The whole-number form needs a squared cutoff below 2^24 at
+// the tree's finest level (r_cut below 4096 cell halves there) and a criterion that never
+// looks beyond the cutoff (not the conventional one).
+static void mac_setup(const fmm_params *P, double theta_max, int nlevel, MacConst &mc)
+{
+    const double u0 = 0.5 * P->box;
+    mc.cut2 = (P->r_cut * P->r_cut) / (u0 * u0);
     mc.theta2 = P->theta * P->theta;
     mc.mode = P->mac_mode;
-    mc.pad = 0;
+    mc.whole = !(mc.mode & 4) && nlevel <= kMaxLevel + 1 && ldexp(mc.cut2, 2 * (nlevel - 1)) < 16777216.0;
+    const double tm2 = theta_max * theta_max;
+    for (int l = 0; l <= kMaxLevel; ++l) {
+        const double c = floor(ldexp(mc.cut2, 2 * l)), w = ldexp(4.0, 2 * l);
+        mc.cut[l] = c < 16777216.0 ? (float)c : 3.0e38f;
+        mc.acc[l] = first_whole(w / mc.theta2, [&](double s) { return w <= mc.theta2 * s; });
+        mc.cand[l] = tm2 > 0.0 ? first_whole(w / tm2, [&](double s) { return w / s <= tm2; }) : 3.0e38f;
+    }
 }
 
 // Waves of one traversal kernel that fit on the device at once.  Sinks are dealt to the
@@ -411,7 +495,7 @@ template <int MODE> static int resident_waves()
         int dev = 0, ncu = 0, per = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_traverse<MODE>, 64, 0) != hipSuccess)
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_traverse<MODE, true>, 64, 0) != hipSuccess)
             return 4096;
         cached = (ncu > 0 ? ncu : 1) * (per > 0 ? per : 1);
     }
@@ -476,7 +560,7 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
                   int mprec, const MacModel *model, hipStream_t st, const TravHook *hook)
 {
     MacConst mc;
-    mac_setup(P, mc);
+    mac_setup(P, theta_max, t->nlevel, mc);
     const int ncell = t->ncell;
     // lcnt: kKinds list sizes, then the learned selector's per-order counts
     const size_t ncnt = (size_t)(kKinds + (mode == kModeLearned ? kOrders : 0)) * ncell;
@@ -515,11 +599,7 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
             int ln = t->lvl_beg[l + 1] - t->lvl_beg[l];
             nw = ln > nw ? ln : nw;
         }
-        // measured: below about a million cells the plain traversal runs faster on two
-        // thirds of the resident waves (2M box 3.05 -> 2.83 ms, 64-box forest 3.47 -> 3.23 ms;
-        // the upward pass shares the GPU), above it on all of them (16.7M box 14.6 ms on all,
-        // 17.6 ms on two thirds)
-        const int cap = mode == kModePlain && ncell < (1 << 20) ? resident_waves(mode) * 2 / 3 : resident_waves(mode);
+        const int cap = resident_waves(mode);
         nw = nw < cap ? nw : cap;
         if ((rc = grow(t->tstack, (size_t)nw * t->stk_cap * 4))) return rc;
         if ((rc = grow(t->wstate, (size_t)nw * 2 * kKinds * sizeof(int)))) return rc;
@@ -557,9 +637,15 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
             a.lbeg = t->lvl_beg[l];
             a.ln = t->lvl_beg[l + 1] - a.lbeg;
             int g = a.ln < nw ? a.ln : nw;
-            if (mode == kModePlain) k_traverse<kModePlain><<<g, 64, 0, st>>>(a, mc);
-            else if (mode == kModeExport) k_traverse<kModeExport><<<g, 64, 0, st>>>(a, mc);
-            else k_traverse<kModeLearned><<<g, 64, 0, st>>>(a, mc);
+            if (mc.whole) {
+                if (mode == kModePlain) k_traverse<kModePlain, true><<<g, 64, 0, st>>>(a, mc);
+                else if (mode == kModeExport) k_traverse<kModeExport, true><<<g, 64, 0, st>>>(a, mc);
+                else k_traverse<kModeLearned, true><<<g, 64, 0, st>>>(a, mc);
+            } else {
+                if (mode == kModePlain) k_traverse<kModePlain, false><<<g, 64, 0, st>>>(a, mc);
+                else if (mode == kModeExport) k_traverse<kModeExport, false><<<g, 64, 0, st>>>(a, mc);
+                else k_traverse<kModeLearned, false><<<g, 64, 0, st>>>(a, mc);
+            }
             if (hook)
                 if ((rc = hook->level(hook->ctx, l, st))) return rc;
         }

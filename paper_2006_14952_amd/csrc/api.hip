@@ -136,7 +136,7 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
         t->lev_ready = true;
     }
     hipStream_t ax = t->aux;
-    // Dependencies: upward -> M2L; traversal of level l -> P2P of level l's leaves;
+    // Dependencies: {upward, leaf boxes} -> M2L (and the leaves wide_line selects); traversal of level l -> P2P of level l's leaves;
     // traversal -> M2L; M2L -> L2L; {L2L, P2P} -> L2P.
     // The plain traversal does not read multipoles, so the upward pass runs beside it on
     // the second stream; P2P runs there, level by level beside the traversal, then beside
@@ -158,15 +158,15 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
         mark(t, 9, st);
         if ((rc = upward(t, &P8, st))) return rc;
         mark(t, 1, st);
-        if ((rc = hip_check(hipEventRecord(t->dep[1], st), "event"))) return rc;
         if ((rc = p2p_bbox(t, P, ax))) return rc;
+        if ((rc = hip_check(hipEventRecord(t->dep[1], ax), "event"))) return rc;
         rc = traverse_mode(t, P, 2, hm.theta_max, t->Mc.p, ncoef(8), P->precision, dm, st, hk);
     } else {
         mark(t, 9, ax);
         if ((rc = upward(t, &P8, ax))) return rc;
         mark(t, 1, ax);
-        if ((rc = hip_check(hipEventRecord(t->dep[1], ax), "event"))) return rc;
         if ((rc = p2p_bbox(t, P, ax))) return rc;
+        if ((rc = hip_check(hipEventRecord(t->dep[1], ax), "event"))) return rc;
         rc = traverse(t, P, st, hk);
     }
     if (rc) return rc;
@@ -181,11 +181,18 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
         mark(t, 3, st);
     }
     if (!fused && !per_level) {  // P2P after the whole traversal
+        // the costliest leaves, if any, by workgroups of several waves on st (the launch of
+        // the others waits for their selection only, so they find the GPU empty)
+        long long line;
+        if ((rc = p2p_wide(t, P, st, &line))) return rc;
         if ((rc = hip_check(hipEventRecord(t->dep[2], st), "event")) ||
             (rc = hip_check(hipStreamWaitEvent(ax, t->dep[2], 0), "event wait")))
             return rc;
+        if (line < 1ll << 62)
+            if ((rc = hip_check(hipStreamWaitEvent(st, t->dep[1], 0), "event wait")) || (rc = p2p_wide_launch(t, P, line, st)))
+                return rc;
         mark(t, 5, ax);
-        if ((rc = p2p(t, P, ax))) return rc;
+        if ((rc = p2p(t, P, line, ax))) return rc;
         mark(t, 6, ax);
     }
     if (!fused) {  // (per level: P2P was launched during the traversal)
@@ -658,7 +665,7 @@ void fmm_free_tree(fmm_tree *t)
 {
     if (!t) return;
     DevBuf *bufs[] = {&t->keys[0], &t->keys[1], &t->idx[0], &t->idx[1], &t->xs, &t->ys, &t->zs, &t->ms, &t->perm,
-                      &t->leaf_of, &t->rel32, &t->nearf, &t->cells, &t->leaves, &t->inner, &t->Mc, &t->Lc, &t->lhead,
+                      &t->leaf_of, &t->p2p_wide, &t->rel32, &t->nearf, &t->cells, &t->leaves, &t->inner, &t->Mc, &t->Lc, &t->lhead,
                       &t->lcnt, &t->tstack, &t->counters, &t->scan_tmp, &t->nch, &t->flag, &t->boxoff,
                       &t->m2l_ctr, &t->m2l_pairs, &t->bbox, &t->wstate, &t->cfeat, &t->cellc, &t->mf_ne,
                       &t->mf_no, &t->mf_offe, &t->mf_offn, &t->mf_spos, &t->mf_sinks, &t->mf_csr, &t->mf_tot};

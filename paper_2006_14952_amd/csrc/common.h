@@ -10,7 +10,7 @@ namespace hfmm {
 constexpr int kMaxLevel = FMM_MAXLEVEL;
 constexpr int kPMax = FMM_PMAX;
 
-// One octree cell: the cube [i h, (i+1) h)^3 with h = box / 2^level, holding the
+// One octree cell (read by the traversal as two int4): the cube [i h, (i+1) h)^3 with h = box / 2^level, holding the
 // Morton-sorted particles beg..end-1.  Children are contiguous (child .. child+nchild-1)
 // and ordered by octant 4 bx + 2 by + bz.  32 bytes; the first 16 hold everything the
 // traversal needs (x index, level, number of children, y and z indices, first child).

@@ -55,6 +55,9 @@ struct P2PArgs {
     const float4 *bbox;             // per cell: lo, hi of the particles relative to the cell centre
     int first;                      // k_p2p: block b takes sink leaf leaves[first + b]
     const int *err;                 // k_p2p: if non-NULL and non-zero, the lists are void: do nothing
+    long long wide_cost;            // leaves of this p2p_cost or more go to k_p2p_wide
+    int lcap;                       // last P2P list chunk
+    int *wide;                      // [0] their number, [1 ..] their places in `leaves`
 };
 
 // Bounding box of each leaf's particles in the FP32 cell-relative frame.
@@ -86,6 +89,13 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v)
     float t = s + y;
     c = (t - s) - y;
     s = t;
+}
+
+// Orders one wave's LDS accesses (the hardware keeps them in order, the compiler is told to).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 constexpr int kStage = 256;  // FP32 form; the FP64 form's 32-byte records are staged 128 at a time
@@ -139,10 +149,6 @@ template <bool F64> struct P2PShared {
     int smark[stage_slots<F64>()];
 };
 
-// P2P of sink leaf `leaves[li]`.
-// CHUNK: the sink tile (16, 32 or 64 particles), a compile-time constant: a tile read at
-// run time (from P2PConst, or as an extra kernel argument) changed the register allocation
-// of the pair loop and cost 0.8-1.1% of the 134M box's P2P time.
 template <bool F64> using P2PLaw = typename std::conditional<F64, P2PConst64, P2PConst>::type;
 
 // One pair of the FP64 form: the weight m f_(1)(r), zero outside 0 < r^2 < r_cut^2.
@@ -177,51 +183,48 @@ __device__ __forceinline__ double pair_weight64(const P2PConst64 &k, double r2, 
     }
 }
 
-template <bool F64, bool POLY, int NPC, int CHUNK>
-__device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k, int li, P2PShared<F64> &sh)
-{
-    constexpr int kStage = stage_slots<F64>();
-    using R = typename std::conditional<F64, double, float>::type;
-    using V4 = typename std::conditional<F64, double4, float4>::type;
-    V4 *src = sh.src;
-    V4 *eoff = sh.eoff;
-    int *ebase = sh.ebase, *epref = sh.epref, *smark = sh.smark;
-    const int lane = threadIdx.x;
-    const uint64_t lt = (1ull << lane) - 1ull;
-    const int A = a.leaves[li];
-    const Cell ca = a.cells[A];
-    const double hA = ldexp(a.box, -cell_level(ca));
-    const double cax = (cell_ix(ca) + 0.5) * hA, cay = (ca.iy + 0.5) * hA, caz = (ca.iz + 0.5) * hA;
-    const int nA = ca.end - ca.beg;
-    const int nlist = a.cnt[A];
-    unsigned long long npairs = 0, nevald = 0;
-    float4 alo = a.bbox[2 * (size_t)A], ahi = a.bbox[2 * (size_t)A + 1];
-    // FP64 form: the boxes are FP32 and relative to their leaves, so their rounding grows with
-    // the leaves' sides, however small the cutoff: the tests' margin does too
-    float cutA = 0.0f;
+// One sink leaf: its cell and the box of the particles at hand (relative to the cell's centre).
+template <bool F64> struct P2PSink {
+    Cell ca;
+    double hA, cax, cay, caz;
     // FP64 form: its coordinates count from the box's far face along an axis where the cutoff
     // reaches past that face: an image x + box would be rounded to the last place of box, while
     // x - box of the particles beside the face is exact
     double Ox = 0.0, Oy = 0.0, Oz = 0.0;
-    if constexpr (F64) {
-        cutA = k.rc * 1.0001f + 1e-6f * (float)hA;
-        const double face = a.box - (double)k.rc - hA;
-        Ox = cax > face ? a.box : 0.0;
-        Oy = cay > face ? a.box : 0.0;
-        Oz = caz > face ? a.box : 0.0;
+    // FP64 form: the boxes are FP32 and relative to their leaves, so their rounding grows with
+    // the leaves' sides, however small the cutoff: the tests' margin does too
+    float cutA = 0.0f;
+    float4 alo, ahi;
+
+    __device__ __forceinline__ P2PSink(const P2PArgs &a, const P2PLaw<F64> &k, int A)
+    {
+        ca = a.cells[A];
+        hA = ldexp(a.box, -cell_level(ca));
+        cax = (cell_ix(ca) + 0.5) * hA;
+        cay = (ca.iy + 0.5) * hA;
+        caz = (ca.iz + 0.5) * hA;
+        alo = a.bbox[2 * (size_t)A];
+        ahi = a.bbox[2 * (size_t)A + 1];
+        if constexpr (F64) {
+            cutA = k.rc * 1.0001f + 1e-6f * (float)hA;
+            const double face = a.box - (double)k.rc - hA;
+            Ox = cax > face ? a.box : 0.0;
+            Oy = cay > face ? a.box : 0.0;
+            Oz = caz > face ? a.box : 0.0;
+        }
     }
 
-    for (int ib = 0; ib < nA; ib += CHUNK) {
-        const int ns = min(CHUNK, nA - ib);
-        const int G = 64 / ns, g = lane / ns, si = lane - g * ns;
-        if (nA > CHUNK) {  // one chunk of the leaf: the box of its own particles
-            const float4 me = a.rel[ca.beg + ib + (lane < ns ? lane : 0)];
-            alo = make_float4(wave_minf(me.x), wave_minf(me.y), wave_minf(me.z), 0.0f);
-            ahi = make_float4(wave_maxf(me.x), wave_maxf(me.y), wave_maxf(me.z), 0.0f);
-        }
-        const bool valid = g < G;
-        const int i = ca.beg + ib + (valid ? si : 0);
-        R xi, yi, zi;
+    // the box of the ns particles from `first` (one chunk of the leaf)
+    __device__ __forceinline__ void chunk_box(const P2PArgs &a, int first, int ns, int lane)
+    {
+        const float4 me = a.rel[first + (lane < ns ? lane : 0)];
+        alo = make_float4(wave_minf(me.x), wave_minf(me.y), wave_minf(me.z), 0.0f);
+        ahi = make_float4(wave_maxf(me.x), wave_maxf(me.y), wave_maxf(me.z), 0.0f);
+    }
+
+    // sink particle i in the pair loop's coordinates
+    template <class R> __device__ __forceinline__ void load(const P2PArgs &a, int i, R &xi, R &yi, R &zi) const
+    {
         if constexpr (F64) {
             xi = a.xs[i] - Ox; yi = a.ys[i] - Oy; zi = a.zs[i] - Oz;
         } else {
@@ -231,6 +234,256 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
         // the sink's load ends here: left to its first use, inside the pair loop, it would make
         // that loop wait for the next stage's records too
         asm volatile("" : "+v"(xi), "+v"(yi), "+v"(zi));
+    }
+
+    // List entry `it` of this lane: its record offset into eoff[lane], its first particle and
+    // particle count; cntj is 0 if its box lies beyond the cutoff of the sink's.
+    template <class V4>
+    __device__ __forceinline__ void entry(const P2PArgs &a, const P2PLaw<F64> &k, uint32_t it, V4 *eoff, int lane,
+                                          int &cntj, int &listed, int &jbeg) const
+    {
+        int s = (int)(it & 31);
+        Cell cb = a.cells[it >> 5];
+        cntj = listed = cb.end - cb.beg;
+        jbeg = cb.beg;
+        double shx = (double)(s / 9 - 1) * a.box, shy = (double)((s / 3) % 3 - 1) * a.box,
+               shz = (double)(s % 3 - 1) * a.box;
+        // exact in FP64: dyadic centres and integer image shifts
+        double hB = ldexp(a.box, -cell_level(cb));
+        const float ox = (float)((cell_ix(cb) + 0.5) * hB + shx - cax);
+        const float oy = (float)((cb.iy + 0.5) * hB + shy - cay);
+        const float oz = (float)((cb.iz + 0.5) * hB + shz - caz);
+        if constexpr (F64) eoff[lane] = make_double4(shx - Ox, shy - Oy, shz - Oz, 0.0);
+        else eoff[lane] = make_float4(ox, oy, oz, 0.0f);
+        // gap between the two boxes; the margin covers FP32 rounding many times over
+        const float4 blo = a.bbox[2 * (size_t)(it >> 5)], bhi = a.bbox[2 * (size_t)(it >> 5) + 1];
+        const float gx = fmaxf(0.0f, fmaxf(alo.x - (bhi.x + ox), (blo.x + ox) - ahi.x));
+        const float gy = fmaxf(0.0f, fmaxf(alo.y - (bhi.y + oy), (blo.y + oy) - ahi.y));
+        const float gz = fmaxf(0.0f, fmaxf(alo.z - (bhi.z + oz), (blo.z + oz) - ahi.z));
+        float far2;
+        if constexpr (F64) {
+            const float cut = cutA + 1e-6f * (float)hB;
+            far2 = cut * cut;
+        } else {
+            far2 = k.rc2 * 1.0001f;
+        }
+        if (gx * gx + gy * gy + gz * gz > far2) cntj = 0;
+    }
+};
+
+// Source records of one stage, a lane's kPer slots, in registers: loaded one stage ahead, so
+// their latency is covered by the pair work of the current stage.
+template <bool F64> struct P2PFetch {
+    using V4 = typename std::conditional<F64, double4, float4>::type;
+    static constexpr int kPer = stage_slots<F64>() / 64;
+    V4 rv[kPer];
+    int ev[kPer];  // list entry of each slot; 64: past the end
+
+    // Slots [sbase, sbase + stage) of the list block in m (its ne entries, `total` slots).
+    // Slot -> list entry: each entry marks the slot it starts at (the largest entry wins, so
+    // entries left empty by the box test are skipped), and a max-scan over the slots carries
+    // the marks forward.  Lane l owns slots kPer l .. kPer l + kPer - 1.  efirst: the entry
+    // that holds slot sbase unless one starts there (the marks then supply it).
+    __device__ __forceinline__ void fetch(const P2PArgs &a, const P2PShared<F64> &m, int *smark, int ne, int total,
+                                          int sbase, int efirst, int lane)
+    {
+        constexpr int kStage = stage_slots<F64>();
+        const int nraw = min(kStage, total - sbase);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) smark[kPer * lane + u] = 0;
+        wave_sync();
+        if (lane < ne) {
+            const int st = m.epref[lane] - sbase;
+            if (st >= 0 && st < kStage) atomicMax(&smark[st], lane + 1);
+        }
+        wave_sync();
+        int mrun[kPer], mx = 0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            mx = max(mx, smark[kPer * lane + u]);
+            mrun[u] = mx;
+        }
+        const int incl = wave_incl_max(mx);
+        const int prev = wave_shift_up1(incl);
+        const int base = max(prev, efirst + 1);
+        // every address first, then the loads back to back: a load under its own
+        // branch waits for the one before it (lanes past the end load record 0)
+        int jv[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) jv[u] = m.ebase[max(base, mrun[u]) - 1];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int q = kPer * lane + u;
+            ev[u] = q < nraw ? max(base, mrun[u]) - 1 : 64;
+            jv[u] = q < nraw ? jv[u] + sbase + q : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            if constexpr (F64) rv[u] = make_double4(a.xs[jv[u]], a.ys[jv[u]], a.zs[jv[u]], a.ms[jv[u]]);
+            else rv[u] = a.rel[jv[u]];
+        }
+    }
+
+    // The fetched sources, moved by their entries' offsets, into src; returns their number.
+    // A source particle farther than r_cut from the sink's box meets no sink particle inside
+    // the cutoff: it is not staged (ballot compaction).
+    __device__ __forceinline__ int stage(const P2PSink<F64> &sk, const P2PLaw<F64> &k, const V4 *eoff, V4 *src,
+                                         uint64_t lt) const
+    {
+        int nst = 0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const V4 eo = eoff[ev[u]];
+            V4 sv;
+            sv.x = rv[u].x + eo.x;
+            sv.y = rv[u].y + eo.y;
+            sv.z = rv[u].z + eo.z;
+            sv.w = rv[u].w;
+            float px, py, pz, far2;  // the source relative to the sink leaf's centre
+            if constexpr (F64) {
+                px = (float)(sv.x - (sk.cax - sk.Ox));
+                py = (float)(sv.y - (sk.cay - sk.Oy));
+                pz = (float)(sv.z - (sk.caz - sk.Oz));
+                far2 = sk.cutA * sk.cutA;
+            } else {
+                px = sv.x; py = sv.y; pz = sv.z;
+                far2 = k.rc2 * 1.0001f;
+            }
+            const float gx = fmaxf(0.0f, fmaxf(sk.alo.x - px, px - sk.ahi.x));
+            const float gy = fmaxf(0.0f, fmaxf(sk.alo.y - py, py - sk.ahi.y));
+            const float gz = fmaxf(0.0f, fmaxf(sk.alo.z - pz, pz - sk.ahi.z));
+            const bool keep = ev[u] < 64 && gx * gx + gy * gy + gz * gz <= far2;
+            const uint64_t km = __ballot(keep);
+            if (keep) src[nst + __popcll(km & lt)] = sv;
+            nst += __popcll(km);
+        }
+        return nst;
+    }
+};
+
+// FP32 form: the force of the staged sources g, g + G, ... on one sink particle.
+template <bool POLY, int NPC>
+__device__ __forceinline__ void p2p_sum32(const P2PConst &k, const float4 *src, int nst, int g, int G, float xi, float yi,
+                                          float zi, float &px, float &py, float &pz)
+{
+    px = py = pz = 0.0f;
+    // the leading coefficient as a vector operand: each Horner step then reads a single scalar
+    float clead = k.c[NPC - 1];
+    asm volatile("" : "+v"(clead));
+    auto pair = [&](const float4 s) __attribute__((always_inline)) {
+        const float dx = xi - s.x, dy = yi - s.y, dz = zi - s.z;
+        // a particle meets itself (and exact duplicates) at d = 0: the 1e-20 added to r^2 keeps
+        // w finite, so w d = 0 without a separate r > 0 test; for any other pair it is far
+        // below r^2's rounding
+        const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, 1e-20f)));
+        const float rinv = __frsqrt_rn(r2);
+        float f1;
+        if constexpr (POLY) {
+            const float x = r2 * rinv * k.c[0], omx = 1.0f - x;
+            const float q = fmaf(fmaf(fmaf(1.5f, x, 3.0f), x, 2.0f), x, 1.0f);
+            f1 = -(omx * omx) * q * (rinv * rinv * rinv);
+        } else {
+            const float t = fmaf(r2, k.two_over_rc2, -1.0f);
+            float S = clead;  // S(t) / (8 r_s^3)
+#pragma unroll
+            for (int c = NPC - 2; c >= 0; --c) S = fmaf(S, t, k.c[c]);
+            f1 = fmaf(-rinv * rinv, rinv, S);
+        }
+        const float w = r2 < k.rc2 ? s.w * f1 : 0.0f;
+        px = fmaf(w, dx, px);
+        py = fmaf(w, dy, py);
+        pz = fmaf(w, dz, pz);
+    };
+    // four sources per step, read two at a time
+    const float4 *sp = src + g;
+    const float4 *const send = src + nst;
+    for (; sp + 3 * G < send; sp += 4 * G) {
+        const float4 s0 = sp[0], s1 = sp[G];
+        pair(s0);
+        pair(s1);
+        const float4 s2 = sp[2 * G], s3 = sp[3 * G];
+        pair(s2);
+        pair(s3);
+    }
+    for (; sp < send; sp += G) pair(sp[0]);
+}
+
+// FP64 form: the same, added to ax, ay, az.
+template <bool POLY, int NPC>
+__device__ __forceinline__ void p2p_sum64(const P2PConst64 &k, const double4 *src, int nst, int g, int G, double xi,
+                                          double yi, double zi, double &ax, double &ay, double &az)
+{
+    auto pair = [&](const double4 s) __attribute__((always_inline)) {
+        const double dx = xi - s.x, dy = yi - s.y, dz = zi - s.z;
+        const double w = pair_weight64<POLY, NPC>(k, dx * dx + dy * dy + dz * dz, s.w);
+        ax += w * dx;
+        ay += w * dy;
+        az += w * dz;
+    };
+    int q = g;
+    for (; q + G < nst; q += 2 * G) {  // two sources per step
+        const double4 s0 = src[q], s1 = src[q + G];
+        pair(s0);
+        pair(s1);
+    }
+    if (q < nst) pair(src[q]);
+}
+
+// The copies of each sink particle (red[copy ns + particle]) summed and written.
+__device__ __forceinline__ void p2p_write(const P2PArgs &a, const double (*red)[3], int first, int ns, int G, int lane)
+{
+    if (lane >= ns) return;
+    double tx = 0, ty = 0, tz = 0;
+    for (int q = 0; q < G; ++q) {
+        tx += red[q * ns + lane][0];
+        ty += red[q * ns + lane][1];
+        tz += red[q * ns + lane][2];
+    }
+    const int o = first + lane;
+    a.nearf[o] = tx;
+    a.nearf[(size_t)a.n + o] = ty;
+    a.nearf[2 * (size_t)a.n + o] = tz;
+}
+
+__device__ __forceinline__ void p2p_count(const P2PArgs &a, int li, unsigned long long npairs, unsigned long long nevald)
+{
+    unsigned long long *c = a.slots + (size_t)(li % kP2PSlots) * kSlotWords;
+    atomicAdd(&c[0], npairs);
+    atomicAdd(&c[1], nevald);
+}
+
+// What a sink leaf costs one wave: list entries times passes over the list.
+template <int CHUNK> __device__ __forceinline__ long long p2p_cost(int nA, int nlist)
+{
+    return (long long)nlist * ((nA + CHUNK - 1) / CHUNK);
+}
+
+// P2P of sink leaf `leaves[li]` by one wave (leaves of a.wide_cost or more are left to
+// p2p_leaf_wide).
+// CHUNK: the sink tile (16, 32 or 64 particles), a compile-time constant: a tile read at
+// run time (from P2PConst, or as an extra kernel argument) changed the register allocation
+// of the pair loop and cost 0.8-1.1% of the 134M box's P2P time.
+template <bool F64, bool POLY, int NPC, int CHUNK>
+__device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k, int li, P2PShared<F64> &sh)
+{
+    constexpr int kStage = stage_slots<F64>();
+    using R = typename std::conditional<F64, double, float>::type;
+    const int lane = threadIdx.x;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const int A = a.leaves[li];
+    P2PSink<F64> sk(a, k, A);
+    const int nA = sk.ca.end - sk.ca.beg;
+    const int nlist = a.cnt[A];
+    if (p2p_cost<CHUNK>(nA, nlist) >= a.wide_cost) return;
+    unsigned long long npairs = 0, nevald = 0;
+
+    for (int ib = 0; ib < nA; ib += CHUNK) {
+        const int ns = min(CHUNK, nA - ib);
+        const int G = 64 / ns, g = lane / ns, si = lane - g * ns;
+        if (nA > CHUNK) sk.chunk_box(a, sk.ca.beg + ib, ns, lane);
+        const bool valid = g < G;
+        R xi, yi, zi;
+        sk.load(a, sk.ca.beg + ib + (valid ? si : 0), xi, yi, zi);
         double ax = 0, ay = 0, az = 0;              // FP64 form
         float sx = 0, sy = 0, sz = 0, cx = 0, cy = 0, cz = 0;  // FP32 form (Kahan)
         // the list is read a chunk ahead: the next chunk's items are on their way while the
@@ -243,38 +496,11 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
             int nchunk = 0;
             if (more) nchunk = a.next[chunk];
             int cntj = 0, listed = 0, jbeg = 0;
-            if (lane < ne) {
-                int s = (int)(it & 31);
-                Cell cb = a.cells[it >> 5];
-                cntj = listed = cb.end - cb.beg;
-                jbeg = cb.beg;
-                double shx = (double)(s / 9 - 1) * a.box, shy = (double)((s / 3) % 3 - 1) * a.box,
-                       shz = (double)(s % 3 - 1) * a.box;
-                // exact in FP64: dyadic centres and integer image shifts
-                double hB = ldexp(a.box, -cell_level(cb));
-                const float ox = (float)((cell_ix(cb) + 0.5) * hB + shx - cax);
-                const float oy = (float)((cb.iy + 0.5) * hB + shy - cay);
-                const float oz = (float)((cb.iz + 0.5) * hB + shz - caz);
-                if constexpr (F64) eoff[lane] = make_double4(shx - Ox, shy - Oy, shz - Oz, 0.0);
-                else eoff[lane] = make_float4(ox, oy, oz, 0.0f);
-                // gap between the two boxes; the margin covers FP32 rounding many times over
-                const float4 blo = a.bbox[2 * (size_t)(it >> 5)], bhi = a.bbox[2 * (size_t)(it >> 5) + 1];
-                const float gx = fmaxf(0.0f, fmaxf(alo.x - (bhi.x + ox), (blo.x + ox) - ahi.x));
-                const float gy = fmaxf(0.0f, fmaxf(alo.y - (bhi.y + oy), (blo.y + oy) - ahi.y));
-                const float gz = fmaxf(0.0f, fmaxf(alo.z - (bhi.z + oz), (blo.z + oz) - ahi.z));
-                float far2;
-                if constexpr (F64) {
-                    const float cut = cutA + 1e-6f * (float)hB;
-                    far2 = cut * cut;
-                } else {
-                    far2 = k.rc2 * 1.0001f;
-                }
-                if (gx * gx + gy * gy + gz * gz > far2) cntj = 0;
-            }
+            if (lane < ne) sk.entry(a, k, it, sh.eoff, lane, cntj, listed, jbeg);
             const int incl = wave_incl_sum(cntj);
             if (lane < ne) {
-                epref[lane] = incl - cntj;
-                ebase[lane] = jbeg - (incl - cntj);
+                sh.epref[lane] = incl - cntj;
+                sh.ebase[lane] = jbeg - (incl - cntj);
             }
             if (more) {
                 chunk = nchunk;
@@ -283,153 +509,27 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
             const int total = __builtin_amdgcn_readlane(incl, 63);
             const int ltot = __builtin_amdgcn_readlane(wave_incl_sum(listed), 63);
             npairs += (unsigned long long)ns * (unsigned)ltot;
-            __syncthreads();
-            // the source records of a stage are loaded into registers one stage ahead, so
-            // their latency is covered by the pair work of the current stage
-            constexpr int kPer = kStage / 64;
-            V4 rv[kPer];
-            int ev[kPer];
-            // slot -> list entry for the kStage slots from sbase: each entry marks the slot it
-            // starts at (the largest entry wins, so entries left empty by the box test are
-            // skipped), and a max-scan over the slots carries the marks forward.  Lane l
-            // owns slots kPer l .. kPer l + kPer - 1.
-            // ecarry: the entry holding the last slot fetched so far (it holds slot sbase
-            // unless an entry starts there, which the marks then supply)
-            int ecarry = 0;
-            auto fetch = [&](int sbase) __attribute__((always_inline)) {
-                const int nraw = min(kStage, total - sbase);
-                const int efirst = ecarry;
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) smark[kPer * lane + u] = 0;
-                __syncthreads();
-                if (lane < ne) {
-                    const int st = epref[lane] - sbase;
-                    if (st >= 0 && st < kStage) atomicMax(&smark[st], lane + 1);
-                }
-                __syncthreads();
-                int mrun[kPer], m = 0;
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    m = max(m, smark[kPer * lane + u]);
-                    mrun[u] = m;
-                }
-                const int incl = wave_incl_max(m);
-                const int prev = wave_shift_up1(incl);
-                const int base = max(prev, efirst + 1);
-                // every address first, then the loads back to back: a load under its own
-                // branch waits for the one before it (lanes past the end load record 0)
-                int jv[kPer];
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) jv[u] = ebase[max(base, mrun[u]) - 1];
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const int q = kPer * lane + u;
-                    ev[u] = q < nraw ? max(base, mrun[u]) - 1 : 64;
-                    jv[u] = q < nraw ? jv[u] + sbase + q : 0;
-                }
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    if constexpr (F64) rv[u] = make_double4(a.xs[jv[u]], a.ys[jv[u]], a.zs[jv[u]], a.ms[jv[u]]);
-                    else rv[u] = a.rel[jv[u]];
-                }
-                ecarry = __builtin_amdgcn_readlane(ev[kPer - 1], 63);
-            };
-            if (total > 0) fetch(0);
+            wave_sync();
+            P2PFetch<F64> f;
+            if (total > 0) f.fetch(a, sh, sh.smark, ne, total, 0, 0, lane);
             for (int sb = 0; sb < total; sb += kStage) {
-                // a source particle farther than r_cut from the sink leaf's box meets no
-                // sink particle inside the cutoff: it is not staged (ballot compaction)
-                int nst = 0;
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const V4 eo = eoff[ev[u]];
-                    V4 sv;
-                    sv.x = rv[u].x + eo.x;
-                    sv.y = rv[u].y + eo.y;
-                    sv.z = rv[u].z + eo.z;
-                    sv.w = rv[u].w;
-                    float px, py, pz, far2;  // the source relative to the sink leaf's centre
-                    if constexpr (F64) {
-                        px = (float)(sv.x - (cax - Ox)); py = (float)(sv.y - (cay - Oy)); pz = (float)(sv.z - (caz - Oz));
-                        far2 = cutA * cutA;
-                    } else {
-                        px = sv.x; py = sv.y; pz = sv.z;
-                        far2 = k.rc2 * 1.0001f;
-                    }
-                    const float gx = fmaxf(0.0f, fmaxf(alo.x - px, px - ahi.x));
-                    const float gy = fmaxf(0.0f, fmaxf(alo.y - py, py - ahi.y));
-                    const float gz = fmaxf(0.0f, fmaxf(alo.z - pz, pz - ahi.z));
-                    const bool keep = ev[u] < 64 && gx * gx + gy * gy + gz * gz <= far2;
-                    const uint64_t km = __ballot(keep);
-                    if (keep) src[nst + __popcll(km & lt)] = sv;
-                    nst += __popcll(km);
-                }
-                if (sb + kStage < total) fetch(sb + kStage);
+                const int nst = f.stage(sk, k, sh.eoff, sh.src, lt);
+                if (sb + kStage < total)
+                    f.fetch(a, sh, sh.smark, ne, total, sb + kStage, __builtin_amdgcn_readlane(f.ev[f.kPer - 1], 63), lane);
                 nevald += (unsigned long long)ns * (unsigned)nst;
-                __syncthreads();
+                wave_sync();
                 if (valid) {
                     if constexpr (F64) {
-                        auto pair = [&](const double4 s) __attribute__((always_inline)) {
-                            const double dx = xi - s.x, dy = yi - s.y, dz = zi - s.z;
-                            const double w = pair_weight64<POLY, NPC>(k, dx * dx + dy * dy + dz * dz, s.w);
-                            ax += w * dx;
-                            ay += w * dy;
-                            az += w * dz;
-                        };
-                        int q = g;
-                        for (; q + G < nst; q += 2 * G) {  // two sources per step
-                            const double4 s0 = src[q], s1 = src[q + G];
-                            pair(s0);
-                            pair(s1);
-                        }
-                        if (q < nst) pair(src[q]);
+                        p2p_sum64<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, ax, ay, az);
                     } else {
-                        float px = 0, py = 0, pz = 0;
-                        // the leading coefficient as a vector operand: each Horner step then
-                        // reads a single scalar
-                        float clead = k.c[NPC - 1];
-                        asm volatile("" : "+v"(clead));
-                        auto pair = [&](const float4 s) __attribute__((always_inline)) {
-                            const float dx = xi - s.x, dy = yi - s.y, dz = zi - s.z;
-                            // a particle meets itself (and exact duplicates) at d = 0: the 1e-20
-                            // added to r^2 keeps w finite, so w d = 0 without a separate r > 0
-                            // test; for any other pair it is far below r^2's rounding
-                            const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, 1e-20f)));
-                            const float rinv = __frsqrt_rn(r2);
-                            float f1;
-                            if constexpr (POLY) {
-                                const float x = r2 * rinv * k.c[0], omx = 1.0f - x;
-                                const float q = fmaf(fmaf(fmaf(1.5f, x, 3.0f), x, 2.0f), x, 1.0f);
-                                f1 = -(omx * omx) * q * (rinv * rinv * rinv);
-                            } else {
-                                const float t = fmaf(r2, k.two_over_rc2, -1.0f);
-                                float S = clead;  // S(t) / (8 r_s^3)
-#pragma unroll
-                                for (int c = NPC - 2; c >= 0; --c) S = fmaf(S, t, k.c[c]);
-                                f1 = fmaf(-rinv * rinv, rinv, S);
-                            }
-                            const float w = r2 < k.rc2 ? s.w * f1 : 0.0f;
-                            px = fmaf(w, dx, px);
-                            py = fmaf(w, dy, py);
-                            pz = fmaf(w, dz, pz);
-                        };
-                        // four sources per step, read two at a time
-                        const float4 *sp = reinterpret_cast<const float4 *>(src) + g;
-                        const float4 *const send = reinterpret_cast<const float4 *>(src) + nst;
-                        for (; sp + 3 * G < send; sp += 4 * G) {
-                            const float4 s0 = sp[0], s1 = sp[G];
-                            pair(s0);
-                            pair(s1);
-                            const float4 s2 = sp[2 * G], s3 = sp[3 * G];
-                            pair(s2);
-                            pair(s3);
-                        }
-                        for (; sp < send; sp += G) pair(sp[0]);
+                        float px, py, pz;
+                        p2p_sum32<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, px, py, pz);
                         kahan_add(sx, cx, px);
                         kahan_add(sy, cy, py);
                         kahan_add(sz, cz, pz);
                     }
                 }
-                __syncthreads();
+                wave_sync();
             }
         }
         if constexpr (!F64) {
@@ -437,30 +537,165 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
             ay = (double)sy - (double)cy;
             az = (double)sz - (double)cz;
         }
-        double(*red)[3] = reinterpret_cast<double(*)[3]>(&src[0]);  // staging area is free here
+        double(*red)[3] = reinterpret_cast<double(*)[3]>(&sh.src[0]);  // staging area is free here
+        red[lane][0] = ax;
+        red[lane][1] = ay;
+        red[lane][2] = az;
+        wave_sync();
+        p2p_write(a, red, sk.ca.beg + ib, ns, G, lane);
+        wave_sync();
+    }
+    if (lane == 0) p2p_count(a, li, npairs, nevald);
+}
+
+// P2P of one sink leaf by a workgroup of kWide waves, for leaves so costly that one wave
+// would outlast all others.  Each wave reads the entries of one list block of 64; the blocks'
+// stages, as the one-wave form cuts them, are then dealt to the waves in turn.  FP32 form: the
+// stages' sums go through LDS and wave 0 adds them in the one-wave form's order, so the
+// results are the same bit for bit; FP64 form: each wave sums its stages, the waves' sums are
+// added in order.
+constexpr int kWide = 8;
+constexpr int kWideIds = 512;  // list blocks whose chunks are looked up at a time
+template <bool F64> struct P2PWideShared {
+    P2PShared<F64> w[kWide];
+    int tot[kWide], ids[kWideIds];
+    float sums[2][F64 ? 1 : kWide][3][64];
+};
+
+template <bool F64, bool POLY, int NPC, int CHUNK>
+__device__ __forceinline__ void p2p_leaf_wide(const P2PArgs &a, const P2PLaw<F64> &k, int li, P2PWideShared<F64> &ws)
+{
+    constexpr int kStage = stage_slots<F64>();
+    using R = typename std::conditional<F64, double, float>::type;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const int A = a.leaves[li];
+    P2PSink<F64> sk(a, k, A);
+    P2PShared<F64> &sh = ws.w[w];
+    const int nA = sk.ca.end - sk.ca.beg;
+    const int nlist = a.cnt[A], nblk = (nlist + 63) / 64;
+    unsigned long long npairs = 0, nevald = 0;
+    for (int ib = 0; ib < nA; ib += CHUNK) {
+        const int ns = min(CHUNK, nA - ib);
+        const int G = 64 / ns, g = lane / ns, si = lane - g * ns;
+        if (nA > CHUNK) sk.chunk_box(a, sk.ca.beg + ib, ns, lane);
+        const bool valid = g < G;
+        R xi, yi, zi;
+        sk.load(a, sk.ca.beg + ib + (valid ? si : 0), xi, yi, zi);
+        double ax = 0, ay = 0, az = 0;
+        float sx = 0, sy = 0, sz = 0, cx = 0, cy = 0, cz = 0;  // FP32 form: wave 0
+        int cur = a.head[A];
+        for (int b0 = 0; b0 < nblk; b0 += kWide) {
+            if (b0 % kWideIds == 0) {
+                // the chunks of the next list blocks: a wave writes its chunks in runs, so 64
+                // links read at once usually settle as many blocks
+                __syncthreads();
+                if (w == 0) {
+                    const int need = min(kWideIds, nblk - b0);
+                    for (int pos = 0; pos < need;) {
+                        const int v = cur + lane <= a.lcap ? a.next[cur + lane] : -1;
+                        const uint64_t brk = __ballot(v != cur + lane + 1);
+                        const int run = brk ? (int)__ffsll((unsigned long long)brk) : 64;  // chunks cur .. cur + run - 1
+                        const int n = min(run, need - pos);
+                        if (lane < n) ws.ids[pos + lane] = cur + lane;
+                        pos += n;
+                        cur = __builtin_amdgcn_readlane(v, n - 1);
+                    }
+                }
+                __syncthreads();
+            }
+            // entries of this wave's list block
+            const int b = b0 + w;
+            int total = 0;
+            if (b < nblk) {
+                const int ne = min(64, nlist - 64 * b);
+                int cntj = 0, listed = 0, jbeg = 0;
+                if (lane < ne)
+                    sk.entry(a, k, a.items[(size_t)ws.ids[b % kWideIds] * kChunk + lane], sh.eoff, lane, cntj, listed, jbeg);
+                const int incl = wave_incl_sum(cntj);
+                if (lane < ne) {
+                    sh.epref[lane] = incl - cntj;
+                    sh.ebase[lane] = jbeg - (incl - cntj);
+                }
+                total = __builtin_amdgcn_readlane(incl, 63);
+                npairs += (unsigned long long)ns * (unsigned)__builtin_amdgcn_readlane(wave_incl_sum(listed), 63);
+            }
+            if (lane == 0) ws.tot[w] = total;
+            __syncthreads();
+            int nstage = 0;
+#pragma unroll
+            for (int v = 0; v < kWide; ++v) nstage += (ws.tot[v] + kStage - 1) / kStage;
+            nstage = __builtin_amdgcn_readfirstlane(nstage);
+            // stage j of these blocks: its block and first slot, fetched into f
+            P2PFetch<F64> f;
+            int fb = 0;
+            auto fetch = [&](int j) __attribute__((always_inline)) {
+                int first = 0, v = 0;
+                for (; v < kWide - 1; ++v) {
+                    const int n = (ws.tot[v] + kStage - 1) / kStage;
+                    if (j < first + n) break;
+                    first += n;
+                }
+                fb = __builtin_amdgcn_readfirstlane(v);
+                const int sbase = (j - first) * kStage, ne = min(64, nlist - 64 * (b0 + fb)), tot = ws.tot[fb];
+                // the entry that holds the first slot: the last one that begins at or before it
+                const uint64_t at = __ballot(lane < ne && ws.w[fb].epref[lane] <= sbase);
+                f.fetch(a, ws.w[fb], sh.smark, ne, tot, sbase, 63 - (int)__clzll((long long)at), lane);
+            };
+            if (w < nstage) fetch(w);
+            const int rounds = (nstage + kWide - 1) / kWide;
+            for (int q = 0; q < rounds; ++q) {
+                const int j = q * kWide + w;
+                float px = 0, py = 0, pz = 0;
+                if (j < nstage) {
+                    const int nst = f.stage(sk, k, ws.w[fb].eoff, sh.src, lt);
+                    if (j + kWide < nstage) fetch(j + kWide);
+                    nevald += (unsigned long long)ns * (unsigned)nst;
+                    wave_sync();
+                    if (valid) {
+                        if constexpr (F64) p2p_sum64<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, ax, ay, az);
+                        else p2p_sum32<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, px, py, pz);
+                    }
+                    wave_sync();
+                }
+                if constexpr (!F64) {
+                    ws.sums[q & 1][w][0][lane] = px;
+                    ws.sums[q & 1][w][1][lane] = py;
+                    ws.sums[q & 1][w][2][lane] = pz;
+                    __syncthreads();  // the other half of the sums is rewritten only after the next one
+                    if (w == 0 && valid)
+                        for (int v = 0; v < min(kWide, nstage - q * kWide); ++v) {
+                            kahan_add(sx, cx, ws.sums[q & 1][v][0][lane]);
+                            kahan_add(sy, cy, ws.sums[q & 1][v][1][lane]);
+                            kahan_add(sz, cz, ws.sums[q & 1][v][2][lane]);
+                        }
+                }
+            }
+            __syncthreads();  // the entries are read to the end
+        }
+        if constexpr (!F64) {
+            ax = (double)sx - (double)cx;
+            ay = (double)sy - (double)cy;
+            az = (double)sz - (double)cz;
+        }
+        double(*red)[3] = reinterpret_cast<double(*)[3]>(&sh.src[0]);
         red[lane][0] = ax;
         red[lane][1] = ay;
         red[lane][2] = az;
         __syncthreads();
-        if (lane < ns) {
-            double tx = 0, ty = 0, tz = 0;
-            for (int q = 0; q < G; ++q) {
-                tx += red[q * ns + lane][0];
-                ty += red[q * ns + lane][1];
-                tz += red[q * ns + lane][2];
+        if (w == 0) {
+            if constexpr (F64) {
+                for (int v = 1; v < kWide; ++v) {
+                    const double(*o)[3] = reinterpret_cast<const double(*)[3]>(&ws.w[v].src[0]);
+                    for (int c = 0; c < 3; ++c) red[lane][c] += o[lane][c];
+                }
+                wave_sync();
             }
-            int o = ca.beg + ib + lane;
-            a.nearf[o] = tx;
-            a.nearf[(size_t)a.n + o] = ty;
-            a.nearf[2 * (size_t)a.n + o] = tz;
+            p2p_write(a, red, sk.ca.beg + ib, ns, G, lane);
         }
         __syncthreads();
     }
-    if (lane == 0) {
-        unsigned long long *c = a.slots + (size_t)(li % kP2PSlots) * kSlotWords;
-        atomicAdd(&c[0], npairs);
-        atomicAdd(&c[1], nevald);
-    }
+    if (lane == 0) p2p_count(a, li, npairs, nevald);
 }
 
 // FP32 form: bound by FP32 issue, 25 operations a pair; the records of a stage and the items
@@ -479,6 +714,27 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(F64 ? (NPC ?
     __shared__ P2PShared<F64> sh;
     if (a.err && *a.err) return;  // the traversal overflowed: it reruns, and so does P2P
     p2p_leaf<F64, POLY, NPC, CHUNK>(a, k, a.first + xcd_order(blockIdx.x, gridDim.x), sh);
+}
+
+// The leaves of a.wide_cost or more, in any order.
+template <int CHUNK> __global__ __launch_bounds__(64) void k_p2p_wide_select(P2PArgs a)
+{
+    const int li = blockIdx.x * 64 + threadIdx.x;
+    if (li >= a.nleaf) return;
+    const int A = a.leaves[li];
+    if (p2p_cost<CHUNK>(a.cells[A].end - a.cells[A].beg, a.cnt[A]) >= a.wide_cost) a.wide[1 + atomicAdd(a.wide, 1)] = li;
+}
+
+template <bool F64, bool POLY, int NPC, int CHUNK>
+__global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(F64 ? 2 : 4))) void k_p2p_wide(P2PArgs a,
+                                                                                                     P2PLaw<F64> k)
+{
+    __shared__ P2PWideShared<F64> sh;
+    const int n = a.wide[0];
+    for (int h = blockIdx.x; h < n; h += gridDim.x) {
+        p2p_leaf_wide<F64, POLY, NPC, CHUNK>(a, k, a.wide[1 + h], sh);
+        __syncthreads();
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -720,6 +976,9 @@ static void p2p_args(fmm_tree *t, P2PArgs &a)
     a.bbox = ptr<float4>(t->bbox);
     a.first = 0;
     a.err = nullptr;
+    a.wide_cost = 1ll << 62;
+    a.lcap = t->lcap[1];
+    a.wide = ptr<int>(t->p2p_wide);
 }
 
 // Whether the fused persistent kernel serves these parameters: the FP32 plain form with
@@ -808,22 +1067,43 @@ int p2p_m2l_fused_launch(fmm_tree *t, const fmm_params *P, hipStream_t st)
     return set_error(FMM_ERR_ARG, "fused kernel compiled for orders 3..8 and force laws of degree 9 or 10");
 }
 
-template <int CHUNK>
-static void launch_p2p(const fmm_params *P, const P2PConst &k, const P2PArgs &a, int count, hipStream_t st)
+// One launch of k_p2p (count > 0: a wave per leaf) or k_p2p_wide (count = 0).
+template <bool F64, bool POLY, int NPC, int CHUNK>
+static void launch_one(const P2PLaw<F64> &k, const P2PArgs &a, int count, hipStream_t st)
 {
-    if (P->split == 1) k_p2p<false, true, 11, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (k.ncoef == 10) k_p2p<false, false, 10, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (k.ncoef == 11) k_p2p<false, false, 11, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else k_p2p<false, false, 15, CHUNK><<<count, 64, 0, st>>>(a, k);
+    if (count > 0) k_p2p<F64, POLY, NPC, CHUNK><<<count, 64, 0, st>>>(a, k);
+    else k_p2p_wide<F64, POLY, NPC, CHUNK><<<256, 64 * kWide, 0, st>>>(a, k);
 }
 
 template <int CHUNK>
-static void launch_p2p64(const fmm_params *P, const P2PConst64 &k, const P2PArgs &a, int count, hipStream_t st)
+static int launch_p2p(const fmm_params *P, const P2PArgs &a, int count, hipStream_t st)
 {
-    if (P->split == 1) k_p2p<true, true, 1, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (k.ncoef == 20) k_p2p<true, false, 20, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else if (k.ncoef == 23) k_p2p<true, false, 23, CHUNK><<<count, 64, 0, st>>>(a, k);
-    else k_p2p<true, false, 0, CHUNK><<<count, 64, 0, st>>>(a, k);
+    if (!P->precision) {
+        P2PConst64 k;
+        p2p_setup64(P, k);
+        if (P->split == 1) launch_one<true, true, 1, CHUNK>(k, a, count, st);
+        else if (k.ncoef == 20) launch_one<true, false, 20, CHUNK>(k, a, count, st);
+        else if (k.ncoef == 23) launch_one<true, false, 23, CHUNK>(k, a, count, st);
+        else launch_one<true, false, 0, CHUNK>(k, a, count, st);
+        return hip_check(hipGetLastError(), "p2p");
+    }
+    P2PConst k;
+    if (int rc = p2p_setup(P, k)) return rc;
+    if (k.split == 1) launch_one<false, true, 11, CHUNK>(k, a, count, st);
+    else if (k.ncoef == 10) launch_one<false, false, 10, CHUNK>(k, a, count, st);
+    else if (k.ncoef == 11) launch_one<false, false, 11, CHUNK>(k, a, count, st);
+    else if (k.ncoef == 15) launch_one<false, false, 15, CHUNK>(k, a, count, st);
+    else return set_error(FMM_ERR_STATE, "p2p: no kernel for a force law of %d coefficients", k.ncoef);
+    return hip_check(hipGetLastError(), "p2p");
+}
+
+int p2p_tile(const fmm_params *P) { return P->p2p_chunk == 16 || P->p2p_chunk == 64 ? P->p2p_chunk : kSinkChunk; }
+
+static int launch_p2p(const fmm_params *P, const P2PArgs &a, int count, hipStream_t st)
+{
+    if (P->p2p_chunk == 16) return launch_p2p<16>(P, a, count, st);
+    if (P->p2p_chunk == 64) return launch_p2p<64>(P, a, count, st);
+    return launch_p2p<kSinkChunk>(P, a, count, st);
 }
 
 int p2p_range(fmm_tree *t, const fmm_params *P, int first, int count, const int *err, hipStream_t st)
@@ -835,24 +1115,61 @@ int p2p_range(fmm_tree *t, const fmm_params *P, int first, int count, const int 
     p2p_args(t, a);
     a.first = first;
     a.err = err;
-    if (!P->precision) {
-        P2PConst64 k;
-        p2p_setup64(P, k);
-        if (P->p2p_chunk == 16) launch_p2p64<16>(P, k, a, count, st);
-        else if (P->p2p_chunk == 64) launch_p2p64<64>(P, k, a, count, st);
-        else launch_p2p64<kSinkChunk>(P, k, a, count, st);
-        return hip_check(hipGetLastError(), "p2p");
-    }
-    P2PConst k;
-    if (int rc = p2p_setup(P, k)) return rc;
-    if (k.split != 1 && k.ncoef != 10 && k.ncoef != 11 && k.ncoef != 15)
-        return set_error(FMM_ERR_STATE, "p2p: no kernel for a force law of %d coefficients", k.ncoef);
-    if (P->p2p_chunk == 16) launch_p2p<16>(P, k, a, count, st);
-    else if (P->p2p_chunk == 64) launch_p2p<64>(P, k, a, count, st);
-    else launch_p2p<kSinkChunk>(P, k, a, count, st);
-    return hip_check(hipGetLastError(), "p2p");
+    return launch_p2p(P, a, count, st);
 }
 
-int p2p(fmm_tree *t, const fmm_params *P, hipStream_t st) { return p2p_range(t, P, 0, t->nleaf, nullptr, st); }
+// Where the line lies between one wave and a workgroup for a leaf, in p2p_cost: a leaf that
+// would take a wave more than a quarter of the time the whole launch needs if evenly spread
+// (over about four waves on each of the GPU's 1024 SIMDs) and at least four times the mean
+// leaf.  One wave per leaf against this line (before, after): step of
+// 300,007 particles 2.91 -> 1.79 ms (the costliest leaf alone took 2.2), 262,144 FP64 3.60 -> 2.57,
+// 2M learned 8.4 -> 7.1, 2M plain 6.4 -> 6.1; 64-box forest and 16.7M box, whose launches are
+// long beside any leaf, unchanged.
+static long long wide_line(const fmm_tree *t)
+{
+    const long long even = t->n_p2p / 4096, mean = t->nleaf > 0 ? t->n_p2p / t->nleaf : 0;
+    return std::max(std::max(even / 4, 4 * mean), 256ll);
+}
+
+// Selects the leaves for workgroups, on `st`.  *line receives the cost from which k_p2p leaves
+// them out, or 2^62 if there are none.
+int p2p_wide(fmm_tree *t, const fmm_params *P, hipStream_t st, long long *line)
+{
+    *line = 1ll << 62;
+    // deterministic FP64 results are the same for every schedule: the one-wave order
+    if (t->nleaf == 0 || (P->deterministic && !P->precision)) return 0;
+    const long long cost = wide_line(t);
+    if (t->p2p_max_cost < cost) return 0;  // no leaf is that costly
+    if (int rc = grow(t->p2p_wide, ((size_t)t->nleaf + 1) * 4)) return rc;
+    if (int rc = zero_async(t->p2p_wide.p, 4, st)) return rc;
+    P2PArgs a;
+    p2p_args(t, a);
+    a.wide_cost = cost;
+    const int nb = (t->nleaf + 63) / 64;
+    if (P->p2p_chunk == 16) k_p2p_wide_select<16><<<nb, 64, 0, st>>>(a);
+    else if (P->p2p_chunk == 64) k_p2p_wide_select<64><<<nb, 64, 0, st>>>(a);
+    else k_p2p_wide_select<kSinkChunk><<<nb, 64, 0, st>>>(a);
+    *line = cost;
+    return hip_check(hipGetLastError(), "p2p selection");
+}
+
+int p2p_wide_launch(fmm_tree *t, const fmm_params *P, long long line, hipStream_t st)
+{
+    if (line >= 1ll << 62) return 0;
+    P2PArgs a;
+    p2p_args(t, a);
+    a.wide_cost = line;
+    return launch_p2p(P, a, 0, st);
+}
+
+int p2p(fmm_tree *t, const fmm_params *P, long long line, hipStream_t st)
+{
+    if (t->nleaf == 0) return 0;
+    if (t->bbox.bytes < (size_t)t->ncell * 32) return set_error(FMM_ERR_STATE, "p2p: leaf boxes not computed");
+    P2PArgs a;
+    p2p_args(t, a);
+    a.wide_cost = line;
+    return launch_p2p(P, a, t->nleaf, st);
+}
 
 }  // namespace hfmm

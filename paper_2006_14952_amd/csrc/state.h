@@ -17,7 +17,8 @@ constexpr int kOrders = 7;  // learned selector: M2L orders 2 .. 8
 //   kErrByte    int: the traversal's overflow bits
 //   kPoolByte   chunk counters of the list kinds, one 128-byte line each
 //   kTravByte   kTravSlots lines of 64-bit sums of the traversal: visits, M2L pairs, P2P
-//               pairs, M2L pairs of each learned order; the readback ends after them
+//               pairs, M2L pairs of each learned order, largest P2P leaf; the readback ends
+//               after them
 //   kP2PByte    kP2PSlots lines of 64-bit sums of P2P: listed pairs, evaluated pairs
 // Atomics on one address end one after the other, about 13 ns apart on this GPU: with one
 // address per sum, a 4096-wave traversal launch took 160 us whatever its work (three sums a
@@ -75,6 +76,8 @@ struct fmm_tree {
     hfmm::DevBuf cellc;                              // packed 16-byte cell view for the traversal
     int stk_cap = 4096;                              // entries per wave (grows on overflow)
     int64_t n_m2l = 0, n_p2p = 0, n_visit = 0, p2p_pairs = 0;
+    int64_t p2p_max_cost = 0;                        // most list entries x passes of one sink leaf
+    hfmm::DevBuf p2p_wide;                           // sink leaves computed by workgroups of several waves
     hfmm::DevBuf counters;                           // device counters
 
     // scratch
@@ -137,7 +140,12 @@ int upward(fmm_tree *t, const fmm_params *P, hipStream_t st);
 int m2l(fmm_tree *t, const fmm_params *P, hipStream_t st);
 int m2l_learned(fmm_tree *t, const fmm_params *P, hipStream_t st);
 int downward_l2l(fmm_tree *t, const fmm_params *P, hipStream_t st);
-int p2p(fmm_tree *t, const fmm_params *P, hipStream_t st);
+// P2P of every sink leaf costing less than `line`; p2p_wide selects the others for workgroups
+// of several waves (line: 2^62 if there are none) and p2p_wide_launch computes them
+int p2p(fmm_tree *t, const fmm_params *P, long long line, hipStream_t st);
+int p2p_wide(fmm_tree *t, const fmm_params *P, hipStream_t st, long long *line);
+int p2p_wide_launch(fmm_tree *t, const fmm_params *P, long long line, hipStream_t st);
+int p2p_tile(const fmm_params *P);  // sink particles per pass over a leaf's list
 // P2P of the sink leaves leaves[first .. first+count-1]; with err non-NULL the launch does
 // nothing while *err is non-zero (lists of a traversal that overflowed)
 int p2p_range(fmm_tree *t, const fmm_params *P, int first, int count, const int *err, hipStream_t st);

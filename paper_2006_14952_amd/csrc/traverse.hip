@@ -79,7 +79,10 @@ struct TravArgs {
     uint32_t *stack; // per-wave stacks when they do not fit in LDS
     int stk_cap;
     int *err;        // bit 0: stack overflow, bit 1: pool overflow
-    unsigned long long *slots;  // kTravSlots lines: [0] visits, [1] M2L, [2] P2P, [3 ..] M2L of each learned order
+    // kTravSlots lines: [0] visits, [1] M2L, [2] P2P, [3 ..] M2L of each learned order, last the
+    // most P2P entries times passes (of `tile` sink particles) of one leaf
+    unsigned long long *slots;
+    int tile;
     // candidate pairs / learned selector
     double theta_max2;             // candidates have (L/S_c)^2 <= theta_max2
     double box, rs, rcut;
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
         tab[WHOLE ? 2 : 0][lane] = mc.cand[lane];
     }
     __syncthreads();
-    unsigned long long visits = 0, nm2l = 0, np2p = 0;
+    unsigned long long visits = 0, nm2l = 0, np2p = 0, most = 0;
     unsigned nord[kOrders] = {0, 0, 0, 0, 0, 0, 0};  // learned: this wave's M2L pairs per order
     int bnext[kKinds], bend[kKinds];
     int *ws = a.wstate + (size_t)blockIdx.x * 2 * kKinds;
@@ -261,12 +264,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
     for (int t = xcd_order(blockIdx.x, gridDim.x); t < a.ln; t += gridDim.x) {
         const int A = a.lbeg + t;
         const int4 ga = cellc[A];
-        const int parentA = a.cells[A].parent;
+        const int4 ra = reinterpret_cast<const int4 *>(a.cells)[2 * (size_t)A + 1];  // beg, end, parent
+        const int parentA = ra.z, nA = ra.y - ra.x;
         const bool leafA = xln_nchild(ga.x) == 0;
         const int lvA = xln_level(ga.x);
         const bool root = lvA == 0;  // a root meets the 27 periodic images of itself
         int ninh = 27, ichunk = 0;
-        if (root && a.cells[A].end == a.cells[A].beg) ninh = 0;  // empty box of a batch: nothing to do
+        if (root && nA == 0) ninh = 0;  // empty box of a batch: nothing to do
         if (!root) {
             ninh = __builtin_amdgcn_readfirstlane(a.cnt[2 * a.ncell + parentA]);
             ichunk = __builtin_amdgcn_readfirstlane(a.head[2 * a.ncell + parentA]);
@@ -431,6 +435,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
         lds_order();
         nm2l += Lm.tot;
         np2p += Lp.tot;
+        if (Lp.tot > 0) {
+            const unsigned long long c = (unsigned long long)Lp.tot * ((nA + a.tile - 1) / a.tile);
+            most = c > most ? c : most;
+        }
         if (MODE == kModeLearned) {
 #pragma unroll
             for (int o = 0; o < kOrders; ++o) {
@@ -451,6 +459,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE == kMod
         atomicAdd(&c[2], np2p);
         if (MODE == kModeLearned)
             for (int k = 0; k < kOrders; ++k) atomicAdd(&c[3 + k], (unsigned long long)nord[k]);
+        if (most > 0) atomicMax(&c[3 + kOrders], most);
     }
 }
 
@@ -616,6 +625,7 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
             a.next[k] = ptr<int>(t->lnext[k]);
             a.cap[k] = t->lcap[k];
         }
+        a.tile = p2p_tile(P);
         a.slots = reinterpret_cast<unsigned long long *>(cb + kTravByte);
         a.pool = reinterpret_cast<int *>(cb + kPoolByte);
         a.wstate = ptr<int>(t->wstate);
@@ -657,12 +667,13 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
         if ((rc = hip_check(hipMemcpyAsync(t->host, cb, kP2PByte, hipMemcpyDeviceToHost, st), "counters")))
             return rc;
         if ((rc = hip_check(hipStreamSynchronize(st), "traversal sync"))) return rc;
-        unsigned long long sum[3 + kOrders] = {0};
+        unsigned long long sum[3 + kOrders] = {0}, most = 0;
         int pools[kKinds], err;
         for (int s = 0; s < kTravSlots; ++s) {
-            unsigned long long c[3 + kOrders];
+            unsigned long long c[4 + kOrders];
             memcpy(c, (char *)t->host + kTravByte + (size_t)s * kSlotWords * 8, sizeof(c));
             for (int k = 0; k < 3 + kOrders; ++k) sum[k] += c[k];
+            most = c[3 + kOrders] > most ? c[3 + kOrders] : most;
         }
         for (int k = 0; k < kKinds; ++k)  // kinds this mode does not write keep their size
             pools[k] = want[k] ? t->host[kPoolByte / 4 + k * kPoolStride] : 0;
@@ -672,6 +683,7 @@ int traverse_mode(fmm_tree *t, const fmm_params *P, int mode, double theta_max, 
             t->n_visit = (int64_t)sum[0];
             t->n_m2l = (int64_t)sum[1];
             t->n_p2p = (int64_t)sum[2];
+            t->p2p_max_cost = (int64_t)most;
             t->trav_mode = mode;
             return 0;
         }

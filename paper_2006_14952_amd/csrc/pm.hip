@@ -16,10 +16,12 @@
 
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "state.h"
 
 namespace hfmm {
+void clear_error();
 
 struct PMPlan {
     int mesh = 0;
@@ -29,6 +31,17 @@ struct PMPlan {
 
 static std::mutex g_pm_mu;
 static std::map<int, PMPlan *> g_pm;  // one plan set per mesh size per process
+// Caller-order particles brought into mesh order, for every mesh size (guarded by g_pm_mu, as
+// every use of a plan is); given back after a call that needed more than kOrderKeep bytes.
+static MortonSort g_order;
+constexpr size_t kOrderKeep = (size_t)2 << 30;
+
+static void release_order()
+{
+    MortonSort &s = g_order;
+    for (DevBuf *b : {&s.keys[0], &s.keys[1], &s.idx[0], &s.idx[1], &s.xs, &s.ys, &s.zs, &s.ms, &s.tmp, &s.scan_tmp})
+        release(*b);
+}
 
 static int pm_plan(int mesh, PMPlan **out)
 {
@@ -59,7 +72,8 @@ static int pm_plan(int mesh, PMPlan **out)
 // Mass-assignment weights of the B-spline schemes on the cell-centred mesh (node i at
 // (i + 0.5) Delta): ORDER 2 cloud-in-cell, 3 triangular-shaped cloud, 4 piecewise cubic.
 // The particle touches nodes i0 .. i0 + ORDER - 1 (mod M) with weights w[0 .. ORDER-1].
-template <int ORDER> __device__ __forceinline__ void assign_weights(double x, double inv_d, int M, int &i0, double *w)
+// The same without the wrap: first node (may lie outside [0, M)) and weights.
+template <int ORDER> __device__ __forceinline__ int assign_first(double x, double inv_d, double *w)
 {
     const double g = x * inv_d - 0.5;
     double first;
@@ -82,7 +96,12 @@ template <int ORDER> __device__ __forceinline__ void assign_weights(double x, do
         w[3] = t3 / 6.0;
         first = f - 1.0;
     }
-    const int i = (int)first;
+    return (int)first;
+}
+
+template <int ORDER> __device__ __forceinline__ void assign_weights(double x, double inv_d, int M, int &i0, double *w)
+{
+    const int i = assign_first<ORDER>(x, inv_d, w);
     i0 = ((i % M) + M) % M;
 }
 
@@ -123,6 +142,102 @@ __global__ void k_deposit(S src, int n, double box, int M, double inv_vol, doubl
                 size_t idx = ((size_t)((i[0] + dx) % M) * M + (i[1] + dy) % M) * M + (i[2] + dz) % M;
                 atomicAdd(&rho[idx], m * w[0][dx] * w[1][dy] * w[2][dz]);
             }
+}
+
+// Deposit of particles in Morton order.  A workgroup takes 4096 consecutive particles; those of
+// one cube of 2^-levels the box (at most 19 - ORDER mesh cells wide) add into that cube's
+// nodes in LDS, which then go to the mesh with one atomic per node: in clumps thousands of
+// particles share a node, and same-address atomics on the mesh end one after the other
+// (about 13 ns apart), while in random order every particle's eight atomics miss the caches.
+// A workgroup whose particles lie in more than kDepositCubes cubes (a mesh much finer than the
+// particles, whose nodes are hardly shared) adds straight to the mesh.
+// %DEPOSIT%
+constexpr int kDepositThreads = 512, kDepositTile = 4096, kDepositSide = 20, kDepositCubes = 32;
+
+template <int ORDER>
+__global__ __launch_bounds__(kDepositThreads) void k_deposit_cubes(MortonOrder src, const uint64_t *__restrict__ keys,
+                                                                   int levels, int n, double box, int M, double inv_vol,
+                                                                   double *__restrict__ rho)
+{
+    __shared__ double acc[kDepositSide * kDepositSide * kDepositSide];
+    __shared__ int heads[kDepositCubes + 1], nhead;
+    const int base = blockIdx.x * kDepositTile, cnt = min(kDepositTile, n - base), sh = 63 - 3 * levels;
+    if (threadIdx.x == 0) nhead = 0;
+    __syncthreads();
+    for (int q = threadIdx.x; q < cnt; q += kDepositThreads)
+        if (q == 0 || (keys[base + q] ^ keys[base + q - 1]) >> sh) {
+            const int h = atomicAdd(&nhead, 1);
+            if (h < kDepositCubes) heads[h] = q;
+        }
+    __syncthreads();
+    const int cubes = nhead;
+    const double inv_d = M / box;
+    auto direct = [&](const int *i, const double (*w)[ORDER], double m) __attribute__((always_inline)) {
+        for (int dx = 0; dx < ORDER; ++dx)
+            for (int dy = 0; dy < ORDER; ++dy)
+                for (int dz = 0; dz < ORDER; ++dz) {
+                    const int ix = ((i[0] + dx) % M + M) % M, iy = ((i[1] + dy) % M + M) % M, iz = ((i[2] + dz) % M + M) % M;
+                    atomicAdd(&rho[((size_t)ix * M + iy) * M + iz], m * w[0][dx] * w[1][dy] * w[2][dz]);
+                }
+    };
+    if (cubes > kDepositCubes) {
+        for (int q = threadIdx.x; q < cnt; q += kDepositThreads) {
+            const int p = base + q;
+            int i[3];
+            double w[3][ORDER];
+            for (int a = 0; a < 3; ++a) i[a] = assign_first<ORDER>(src.x(p, a), inv_d, w[a]);
+            direct(i, w, src.m(p) * inv_vol);
+        }
+        return;
+    }
+    const double side = ldexp(box, -levels);
+    for (int c = 0, beg = 0; c < cubes; ++c) {
+        int end = cnt;  // the next cube's first particle: heads are in no particular order
+        for (int h = 0; h < cubes; ++h)
+            if (heads[h] > beg && heads[h] < end) end = heads[h];
+        // the cube's nodes, from its lowest corner's first to its highest corner's last
+        const uint64_t pre = keys[base + beg] >> sh;
+        int lo[3], len[3];
+        for (int a = 0; a < 3; ++a) {
+            int k = 0;
+            for (int l = 0; l < levels; ++l) k |= (int)((pre >> (3 * l + 2 - a)) & 1) << l;
+            double w[ORDER];
+            lo[a] = assign_first<ORDER>(k * side, inv_d, w);
+            len[a] = min(assign_first<ORDER>((k + 1) * side, inv_d, w) + ORDER - lo[a], kDepositSide);
+        }
+        const int nnode = len[0] * len[1] * len[2];
+        for (int q = threadIdx.x; q < nnode; q += kDepositThreads) acc[q] = 0.0;
+        __syncthreads();
+        for (int q = beg + threadIdx.x; q < end; q += kDepositThreads) {
+            const int p = base + q;
+            int i[3];
+            double w[3][ORDER];
+            bool inside = true;
+            for (int a = 0; a < 3; ++a) {
+                i[a] = assign_first<ORDER>(src.x(p, a), inv_d, w[a]);
+                inside = inside && i[a] >= lo[a] && i[a] + ORDER <= lo[a] + len[a];
+            }
+            const double m = src.m(p) * inv_vol;
+            if (!inside) {  // a particle on the cube's face, rounded to its other side
+                direct(i, w, m);
+                continue;
+            }
+            const int o = ((i[0] - lo[0]) * len[1] + i[1] - lo[1]) * len[2] + i[2] - lo[2];
+            for (int dx = 0; dx < ORDER; ++dx)
+                for (int dy = 0; dy < ORDER; ++dy)
+                    for (int dz = 0; dz < ORDER; ++dz)
+                        atomicAdd(&acc[o + (dx * len[1] + dy) * len[2] + dz], m * w[0][dx] * w[1][dy] * w[2][dz]);
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < nnode; q += kDepositThreads) {
+            const double v = acc[q];
+            if (v == 0.0) continue;
+            const int iz = lo[2] + q % len[2], iy = lo[1] + q / len[2] % len[1], ix = lo[0] + q / (len[1] * len[2]);
+            atomicAdd(&rho[((size_t)((ix % M + M) % M) * M + (iy % M + M) % M) * M + (iz % M + M) % M], v);
+        }
+        __syncthreads();
+        beg = end;
+    }
 }
 
 // Deterministic deposit (fmm_params.deterministic): every contribution m w / d^3 is rounded
@@ -267,22 +382,39 @@ __global__ void k_check_finite(const double *__restrict__ pos, size_t n3, int *b
     if (i < n3 && !isfinite(pos[i])) *bad = 1;
 }
 
-template <class S>
-static int pm_run(const fmm_params *P, int mesh, int n, S src, const double *pos_check, double *acc, hipStream_t st)
+// Reads the non-finite flag back (synchronises the stream).
+static int check_flag(const int *bad, hipStream_t st)
 {
-    PMPlan *pl;
-    if (int rc = pm_plan(mesh, &pl)) return rc;
-    std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and mesh buffers are shared per mesh size
+    int hbad = 0;
+    if (hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return set_error(FMM_ERR_HIP, "pm sync");
+    return hbad ? set_error(FMM_ERR_NAN, "non-finite particle position") : 0;
+}
+
+// Caller-order particles are brought into mesh order from this many on: %ORDER%
+constexpr int kOrderMin = 1 << 19;
+
+// Morton levels at which a cube is at most 19 - order mesh cells wide (k_deposit_cubes).
+static int cube_levels(int mesh, int order)
+{
+    int l = 0;
+    while (mesh > (19 - order) << l) ++l;
+    return l;
+}
+
+// keys: the Morton keys of src's particles, in order by their first 3 cube_levels bits at
+// least, or nullptr (any order).
+template <class S>
+static int pm_run(PMPlan *pl, const fmm_params *P, int mesh, int n, S src, const uint64_t *keys, const double *pos_check,
+                  double *acc, hipStream_t st)
+{
     size_t nr = (size_t)mesh * mesh * mesh, nc = (size_t)mesh * mesh * (mesh / 2 + 1);
     if (pos_check) {
         int *bad = ptr<int>(pl->amesh);  // scratch flag in the (not yet used) output mesh
         if (int rc = hip_check(hipMemsetAsync(bad, 0, sizeof(int), st), "pm check")) return rc;
         k_check_finite<<<(unsigned)((3 * (size_t)n + 255) / 256), 256, 0, st>>>(pos_check, 3 * (size_t)n, bad);
-        int hbad = 0;
-        if (hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return set_error(FMM_ERR_HIP, "pm sync");
-        if (hbad) return set_error(FMM_ERR_NAN, "non-finite particle position");
+        if (int rc = check_flag(bad, st)) return rc;
     }
     if (int rc = hip_check(hipMemsetAsync(pl->rho.p, 0, nr * 8, st), "pm mesh")) return rc;
     double d = P->box / mesh;
@@ -298,6 +430,15 @@ static int pm_run(const fmm_params *P, int mesh, int n, S src, const double *pos
         else if (order == 4) k_deposit_fixed<S, 4><<<nb, 256, 0, st>>>(src, n, P->box, mesh, inv_vol, mx, irho);
         else k_deposit_fixed<S, 2><<<nb, 256, 0, st>>>(src, n, P->box, mesh, inv_vol, mx, irho);
         k_fixed_to_double<<<(unsigned)((nr + 255) / 256), 256, 0, st>>>(irho, nr, mx, n, inv_vol);
+    } else if (keys) {
+        if constexpr (std::is_same<S, MortonOrder>::value) {
+            const unsigned g = (unsigned)((n + kDepositTile - 1) / kDepositTile);
+            const int lv = cube_levels(mesh, order);
+            double *rho = ptr<double>(pl->rho);
+            if (order == 3) k_deposit_cubes<3><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, inv_vol, rho);
+            else if (order == 4) k_deposit_cubes<4><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, inv_vol, rho);
+            else k_deposit_cubes<2><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, inv_vol, rho);
+        }
     } else if (order == 3) {
         k_deposit<S, 3><<<nb, 256, 0, st>>>(src, n, P->box, mesh, inv_vol, ptr<double>(pl->rho));
     } else if (order == 4) {
@@ -332,7 +473,29 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
     if (n64 < 0 || n64 > ((int64_t)1 << 30)) return set_error(FMM_ERR_ARG, "n out of range");
     const int n = (int)n64;
     if (n == 0) return 0;
-    return pm_run(P, mesh, n, CallerOrder{pos, mass}, pos, acc, st);
+    PMPlan *pl;
+    if (int rc = pm_plan(mesh, &pl)) return rc;
+    std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
+    if (n >= kOrderMin && !P->deterministic) {
+        int *bad = ptr<int>(pl->amesh);  // scratch flag in the (not yet used) output mesh
+        if (int rc = hip_check(hipMemsetAsync(bad, 0, sizeof(int), st), "pm check")) return rc;
+        const int order = P->pm_assign == 0 ? 2 : P->pm_assign;
+        MortonSort &s = g_order;
+        int rc = morton_order(s, n, P->box, pos, mass, cube_levels(mesh, order), bad, st);
+        if (rc == 0) {
+            if ((rc = check_flag(bad, st)) == 0)
+                rc = pm_run(pl, P, mesh, n,
+                            MortonOrder{ptr<double>(s.xs), ptr<double>(s.ys), ptr<double>(s.zs), ptr<double>(s.ms),
+                                        ptr<int>(s.idx[s.sorted])},
+                            ptr<uint64_t>(s.keys[s.sorted]), nullptr, acc, st);
+            if ((size_t)n * 56 > kOrderKeep) release_order();
+            return rc;
+        }
+        if (rc != FMM_ERR_NOMEM) return rc;
+        clear_error();  // no room for the order: the particles as they come
+        release_order();
+    }
+    return pm_run(pl, P, mesh, n, CallerOrder{pos, mass}, nullptr, pos, acc, st);
 }
 
 // PM on the particles of a built tree (Morton order, already wrapped and checked).
@@ -340,10 +503,13 @@ int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipS
 {
     if (mesh < 8 || mesh > 1024) return set_error(FMM_ERR_ARG, "mesh must be in [8, 1024]");
     if (t->n == 0) return 0;
-    return pm_run(P, mesh, (int)t->n,
+    PMPlan *pl;
+    if (int rc = pm_plan(mesh, &pl)) return rc;
+    std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
+    return pm_run(pl, P, mesh, (int)t->n,
                   MortonOrder{ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs), ptr<double>(t->ms),
                               ptr<int>(t->perm)},
-                  nullptr, acc, st);
+                  ptr<uint64_t>(t->keys[t->sorted]), nullptr, acc, st);
 }
 
 int add_into(double *acc, const double *other, int64_t n3, hipStream_t st)

@@ -122,6 +122,13 @@ struct fmm_tree {
 };
 
 namespace hfmm {
+// Particles ordered by their Morton keys' leading bits (morton_order), with its buffers.
+struct MortonSort {
+    DevBuf keys[2], idx[2], xs, ys, zs, ms, tmp, scan_tmp;
+    int sorted = 0;  // the pair of keys and idx (sorted -> caller index) in order
+};
+int morton_order(MortonSort &s, int n, double box, const double *pos, const double *mass, int levels, int *bad,
+                 hipStream_t st);
 int tree_build(fmm_tree *t, const fmm_params *P, int64_t n, const double *pos, const double *mass, int nbox,
                const int64_t *offsets, hipStream_t st);
 // Called by the traversal after it has launched the kernel of sink level l on st: once that

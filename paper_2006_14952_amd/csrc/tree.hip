@@ -185,29 +185,29 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint64_t *__res
 }
 
 // Passes over the Morton key's digits first_digit .. 7, then (batches) 1 or 2 passes over
-// the box index, so the order is by box, then by key; stable throughout.  Sorts the
-// buffer pair t->sorted holds (t->sorted = 0 after k_keys) and sets t->sorted to the result.
-static int radix_sort(fmm_tree *t, int n, int nbox, int first_digit, hipStream_t st)
+// the box index, so the order is by box, then by key; stable throughout.  Sorts the buffer
+// pair `sorted` of keys and idx (0 after k_keys) and sets it to the pair with the result.
+static int radix_sort(DevBuf (&keys)[2], DevBuf (&idx)[2], DevBuf &tmp, DevBuf &scan_tmp, int &sorted, int n,
+                      const int *boxoff, int nbox, int first_digit, hipStream_t st)
 {
     int nb = (n + kRsTile - 1) / kRsTile;
-    if (int rc = grow(t->nch, (size_t)256 * nb * 2 * sizeof(int))) return rc;
-    int *hist = ptr<int>(t->nch), *offs = hist + 256 * nb;
-    const int *boxoff = ptr<int>(t->boxoff);
+    if (int rc = grow(tmp, (size_t)256 * nb * 2 * sizeof(int))) return rc;
+    int *hist = ptr<int>(tmp), *offs = hist + 256 * nb;
     int npass = 8 + (nbox > 1) + (nbox > 256);
-    int cur = t->sorted;
+    int cur = sorted;
     for (int pass = first_digit; pass < npass; ++pass) {
         bool bpass = pass >= 8;
         int shift = bpass ? 8 * (pass - 8) : 8 * pass;
         const int *bo = bpass ? boxoff : nullptr;
-        k_rs_hist<<<nb, kRsThreads, 0, st>>>(ptr<uint64_t>(t->keys[cur]), ptr<uint32_t>(t->idx[cur]), n, shift, bo,
-                                             nbox, nb, hist);
-        if (int rc = scan_exclusive(hist, offs, 256 * nb, nullptr, st, t->scan_tmp)) return rc;
-        k_rs_scatter<<<nb, kRsThreads, 0, st>>>(ptr<uint64_t>(t->keys[cur]), ptr<uint32_t>(t->idx[cur]),
-                                                ptr<uint64_t>(t->keys[cur ^ 1]), ptr<uint32_t>(t->idx[cur ^ 1]), n,
-                                                shift, bo, nbox, nb, offs);
+        k_rs_hist<<<nb, kRsThreads, 0, st>>>(ptr<uint64_t>(keys[cur]), ptr<uint32_t>(idx[cur]), n, shift, bo, nbox, nb,
+                                             hist);
+        if (int rc = scan_exclusive(hist, offs, 256 * nb, nullptr, st, scan_tmp)) return rc;
+        k_rs_scatter<<<nb, kRsThreads, 0, st>>>(ptr<uint64_t>(keys[cur]), ptr<uint32_t>(idx[cur]),
+                                                ptr<uint64_t>(keys[cur ^ 1]), ptr<uint32_t>(idx[cur ^ 1]), n, shift, bo,
+                                                nbox, nb, offs);
         cur ^= 1;
     }
-    t->sorted = cur;
+    sorted = cur;
     return hip_check(hipGetLastError(), "radix sort");
 }
 
@@ -555,7 +555,8 @@ __global__ void k_child_counts(Cell *__restrict__ cells, int ncell, const int *_
 
 // Particles in Morton order: wrapped FP64 positions and masses, and FP32 records relative to
 // the centre of their leaf (the FP32 form keeps FP64 only for absolute positions and the
-// exact cell-centre offsets); the leaf's cube follows from the key and the depth.
+// exact cell-centre offsets); the leaf's cube follows from the key and the depth.  Without
+// rel: positions and masses only.
 __global__ void k_gather(const double *__restrict__ pos, const double *__restrict__ mass,
                          const uint32_t *__restrict__ idx, const uint64_t *__restrict__ keys,
                          const unsigned char *__restrict__ depth, int n, double box, double *__restrict__ xs,
@@ -574,6 +575,7 @@ __global__ void k_gather(const double *__restrict__ pos, const double *__restric
     ys[i] = y;
     zs[i] = z;
     ms[i] = m;
+    if (!rel) return;
     perm[i] = (int)j;
     const int l = depth[i];
     const uint64_t pre = keys[i] >> (3 * (kMaxLevel - l));
@@ -583,6 +585,25 @@ __global__ void k_gather(const double *__restrict__ pos, const double *__restric
 }
 
 static inline int blocks(int64_t n, int b) { return (int)((n + b - 1) / b); }
+
+// Particles of one box ordered by the first 3 `levels` bits of their Morton keys.
+int morton_order(MortonSort &s, int n, double box, const double *pos, const double *mass, int levels, int *bad,
+                 hipStream_t st)
+{
+    const size_t nn = (size_t)n;
+    int rc = 0;
+    for (int b = 0; b < 2 && !rc; ++b) rc = grow(s.keys[b], nn * 8) | grow(s.idx[b], nn * 4);
+    if (!rc) rc = grow(s.xs, nn * 8) | grow(s.ys, nn * 8) | grow(s.zs, nn * 8) | grow(s.ms, nn * 8);
+    if (rc) return rc;
+    s.sorted = 0;
+    k_keys<<<blocks(n, 256), 256, 0, st>>>(pos, n, box, ptr<uint64_t>(s.keys[0]), ptr<uint32_t>(s.idx[0]), bad);
+    const int first = (63 - 3 * levels) / 8;
+    if ((rc = radix_sort(s.keys, s.idx, s.tmp, s.scan_tmp, s.sorted, n, nullptr, 1, first, st))) return rc;
+    k_gather<<<blocks(n, 256), 256, 0, st>>>(pos, mass, ptr<uint32_t>(s.idx[s.sorted]), nullptr, nullptr, n, box,
+                                             ptr<double>(s.xs), ptr<double>(s.ys), ptr<double>(s.zs), ptr<double>(s.ms),
+                                             nullptr, nullptr);
+    return hip_check(hipGetLastError(), "particle order");
+}
 
 int tree_build(fmm_tree *t, const fmm_params *P, int64_t n64, const double *pos, const double *mass, int nbox,
                const int64_t *hoff, hipStream_t st)
@@ -643,7 +664,8 @@ int tree_build(fmm_tree *t, const fmm_params *P, int64_t n64, const double *pos,
     const unsigned char *depth = nullptr;
     TreeIn in{nullptr, ptr<int>(t->boxoff), n, nbox, nc, kPartialLevel};
     for (int first = kPartialDigit;; first = 0) {
-        if ((rc = radix_sort(t, n, nbox, first, st))) return rc;
+        if ((rc = radix_sort(t->keys, t->idx, t->nch, t->scan_tmp, t->sorted, n, ptr<int>(t->boxoff), nbox, first, st)))
+            return rc;
         in.keys = ptr<uint64_t>(t->keys[t->sorted]);
         in.lmax = first ? kPartialLevel : kMaxLevel;
         // the sort's other buffers are free: depths in the indices', wide windows in the keys'

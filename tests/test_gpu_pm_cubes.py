@@ -1,0 +1,76 @@
+"""PM mass deposit by Morton cubes and the mesh order of caller-order particles, against the numpy reference."""
+import numpy as np
+import pytest
+
+from oracle import pm_ewald
+from paper_2006_14952_amd import inputs
+
+
+def _run(pos, m, mesh, assign, limit=None):
+    import torch
+
+    import paper_2006_14952_amd as hf
+    prm = hf.params(r_s=min(0.1, 1.25 / mesh), pm_assign=assign)
+    d = [torch.tensor(a, device="cuda") for a in (pos, m)]
+    if limit is None:
+        return hf.pm_long_range(*d, prm, mesh).cpu().numpy()
+    hf.pm_long_range(d[0][:1000].contiguous(), d[1][:1000].contiguous(), prm, mesh)  # the meshes are held
+    hf.set_memory_limit(hf.memory_in_use() + limit)
+    try:
+        return hf.pm_long_range(*d, prm, mesh).cpu().numpy()
+    finally:
+        hf.set_memory_limit(0)
+
+
+def _close(a, b):
+    """The bars of the small boxes' tests: FFT rounding of two implementations."""
+    assert np.sqrt(((a - b) ** 2).sum() / (b ** 2).sum()) < 1e-10
+    assert np.abs(a - b).max() < 1e-8 * np.abs(b).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mesh,assign", [(8, 0), (17, 0), (18, 0), (33, 3), (64, 4), (60, 3), (100, 0), (129, 4), (200, 0)])
+def test_mesh_ordered_deposit(mesh, assign):
+    """From 2^19 particles on the library orders them by mesh cubes (one cube, cubes whose sides are no
+    whole number of cells, and a mesh with more cells than particles)."""
+    n = (1 << 19) + 4097
+    pos, m = inputs.clustered(n, 40, inputs.rng_for(651, mesh))
+    pos[:64] = np.round(pos[:64] * mesh) / mesh  # on cell faces, some on the box's
+    pos[64:96] += 3.0                            # outside the box
+    _close(_run(pos, m, mesh, assign), pm_ewald.pm_forces(pos, m, 1.0, min(0.1, 1.25 / mesh), mesh, order=assign or 2))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,mesh", [(5000, 16), (9000, 64), (3000, 128)])
+def test_hybrid_deposits_in_tree_order(n, mesh):
+    """The hybrid step deposits the tree's particles by cubes at any size; few of them share a cube here."""
+    import torch
+
+    import paper_2006_14952_amd as hf
+    pos, m = inputs.clustered(n, 3, inputs.rng_for(654, n))
+    prm = hf.params(r_s=1.25 / mesh, p=3, n_crit=16)
+    d = [torch.tensor(a, device="cuda") for a in (pos, m)]
+    t = hf.Tree()
+    total = t.hybrid(*d, prm, mesh).cpu().numpy()
+    short = t.short_range(prm).cpu().numpy()
+    _close(total - short, pm_ewald.pm_forces(pos, m, 1.0, 1.25 / mesh, mesh))
+
+
+@pytest.mark.gpu
+def test_no_room_for_the_order_falls_back():
+    n = (1 << 19) + 5
+    pos, m = inputs.clustered(n, 40, inputs.rng_for(652))
+    _close(_run(pos, m, 48, 0, limit=1 << 20), _run(pos, m, 48, 0))
+
+
+@pytest.mark.gpu
+def test_non_finite_positions_are_still_refused():
+    import torch
+
+    import paper_2006_14952_amd as hf
+    n = 1 << 19
+    pos, m = inputs.uniform(n, inputs.rng_for(653))
+    pos[12345, 1] = np.inf
+    with pytest.raises(hf.FMMError) as e:
+        hf.pm_long_range(torch.tensor(pos, device="cuda"), torch.tensor(m, device="cuda"), hf.params(r_s=0.02), 64)
+    assert e.value.code == hf.FMM_ERR_NAN

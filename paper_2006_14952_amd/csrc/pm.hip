@@ -151,8 +151,71 @@ __global__ void k_deposit(S src, int n, double box, int M, double inv_vol, doubl
 // (about 13 ns apart), while in random order every particle's eight atomics miss the caches.
 // A workgroup whose particles lie in more than kDepositCubes cubes (a mesh much finer than the
 // particles, whose nodes are hardly shared) adds straight to the mesh.
-// %DEPOSIT%
+// 16.7M clustered particles on 256^3 (in this order): 6.27 -> 0.30 ms; the 2M box in tree order on
+// 128^3: 1.81 -> 0.09 ms.
 constexpr int kDepositThreads = 512, kDepositTile = 4096, kDepositSide = 20, kDepositCubes = 32;
+constexpr int kDepositPer = kDepositTile / kDepositThreads;
+
+// Node index modulo M; nodes lie in [-2, M + 4] and M >= 8.
+__device__ __forceinline__ int wrap_node(int i, int M) { return i < 0 ? i + M : i >= M ? i - M : i; }
+
+// Where the cubes of a workgroup's particles begin (in no particular order); the number of
+// cubes may exceed kDepositCubes, the places kept.
+struct CubeHeads {
+    int at[kDepositCubes], n;
+};
+
+__device__ __forceinline__ int find_cubes(CubeHeads &h, const uint64_t *__restrict__ keys, int base, int cnt, int sh)
+{
+    if (threadIdx.x == 0) h.n = 0;
+    __syncthreads();
+    for (int q = threadIdx.x; q < cnt; q += kDepositThreads)
+        if (q == 0 || (keys[base + q] ^ keys[base + q - 1]) >> sh) {
+            const int k = atomicAdd(&h.n, 1);
+            if (k < kDepositCubes) h.at[k] = q;
+        }
+    __syncthreads();
+    return h.n;
+}
+
+__device__ __forceinline__ int next_cube(const CubeHeads &h, int cubes, int beg, int cnt)
+{
+    int end = cnt;
+    for (int k = 0; k < cubes; ++k)
+        if (h.at[k] > beg && h.at[k] < end) end = h.at[k];
+    return end;
+}
+
+// The nodes of the cube with Morton prefix `pre`: from its lowest corner's first to its highest
+// corner's last, along each axis lo .. lo + len - 1 (unwrapped).
+template <int ORDER> struct CubeNodes {
+    int lo[3], len[3];
+    __device__ __forceinline__ CubeNodes(uint64_t pre, int levels, double side, double inv_d)
+    {
+        for (int a = 0; a < 3; ++a) {
+            int k = 0;
+            for (int l = 0; l < levels; ++l) k |= (int)((pre >> (3 * l + 2 - a)) & 1) << l;
+            double w[ORDER];
+            lo[a] = assign_first<ORDER>(k * side, inv_d, w);
+            len[a] = min(assign_first<ORDER>((k + 1) * side, inv_d, w) + ORDER - lo[a], kDepositSide);
+        }
+    }
+    __device__ __forceinline__ int count() const { return len[0] * len[1] * len[2]; }
+    // mesh index of node q of the cube
+    __device__ __forceinline__ size_t mesh(int q, int M) const
+    {
+        const int iz = lo[2] + q % len[2], iy = lo[1] + q / len[2] % len[1], ix = lo[0] + q / (len[1] * len[2]);
+        return ((size_t)wrap_node(ix, M) * M + wrap_node(iy, M)) * M + wrap_node(iz, M);
+    }
+    // cube index of a particle's first node, -1 if its nodes are not all among the cube's (a
+    // particle on the cube's face, rounded to its other side)
+    __device__ __forceinline__ int first(const int *i) const
+    {
+        for (int a = 0; a < 3; ++a)
+            if (i[a] < lo[a] || i[a] + ORDER > lo[a] + len[a]) return -1;
+        return ((i[0] - lo[0]) * len[1] + i[1] - lo[1]) * len[2] + i[2] - lo[2];
+    }
+};
 
 template <int ORDER>
 __global__ __launch_bounds__(kDepositThreads) void k_deposit_cubes(MortonOrder src, const uint64_t *__restrict__ keys,
@@ -160,23 +223,15 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit_cubes(MortonOrder s
                                                                    double *__restrict__ rho)
 {
     __shared__ double acc[kDepositSide * kDepositSide * kDepositSide];
-    __shared__ int heads[kDepositCubes + 1], nhead;
+    __shared__ CubeHeads heads;
     const int base = blockIdx.x * kDepositTile, cnt = min(kDepositTile, n - base), sh = 63 - 3 * levels;
-    if (threadIdx.x == 0) nhead = 0;
-    __syncthreads();
-    for (int q = threadIdx.x; q < cnt; q += kDepositThreads)
-        if (q == 0 || (keys[base + q] ^ keys[base + q - 1]) >> sh) {
-            const int h = atomicAdd(&nhead, 1);
-            if (h < kDepositCubes) heads[h] = q;
-        }
-    __syncthreads();
-    const int cubes = nhead;
+    const int cubes = find_cubes(heads, keys, base, cnt, sh);
     const double inv_d = M / box;
     auto direct = [&](const int *i, const double (*w)[ORDER], double m) __attribute__((always_inline)) {
         for (int dx = 0; dx < ORDER; ++dx)
             for (int dy = 0; dy < ORDER; ++dy)
                 for (int dz = 0; dz < ORDER; ++dz) {
-                    const int ix = ((i[0] + dx) % M + M) % M, iy = ((i[1] + dy) % M + M) % M, iz = ((i[2] + dz) % M + M) % M;
+                    const int ix = wrap_node(i[0] + dx, M), iy = wrap_node(i[1] + dy, M), iz = wrap_node(i[2] + dz, M);
                     atomicAdd(&rho[((size_t)ix * M + iy) * M + iz], m * w[0][dx] * w[1][dy] * w[2][dz]);
                 }
     };
@@ -191,50 +246,31 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit_cubes(MortonOrder s
         return;
     }
     const double side = ldexp(box, -levels);
-    for (int c = 0, beg = 0; c < cubes; ++c) {
-        int end = cnt;  // the next cube's first particle: heads are in no particular order
-        for (int h = 0; h < cubes; ++h)
-            if (heads[h] > beg && heads[h] < end) end = heads[h];
-        // the cube's nodes, from its lowest corner's first to its highest corner's last
-        const uint64_t pre = keys[base + beg] >> sh;
-        int lo[3], len[3];
-        for (int a = 0; a < 3; ++a) {
-            int k = 0;
-            for (int l = 0; l < levels; ++l) k |= (int)((pre >> (3 * l + 2 - a)) & 1) << l;
-            double w[ORDER];
-            lo[a] = assign_first<ORDER>(k * side, inv_d, w);
-            len[a] = min(assign_first<ORDER>((k + 1) * side, inv_d, w) + ORDER - lo[a], kDepositSide);
-        }
-        const int nnode = len[0] * len[1] * len[2];
+    for (int beg = 0; beg < cnt;) {
+        const int end = next_cube(heads, cubes, beg, cnt);
+        const CubeNodes<ORDER> cube(keys[base + beg] >> sh, levels, side, inv_d);
+        const int nnode = cube.count();
         for (int q = threadIdx.x; q < nnode; q += kDepositThreads) acc[q] = 0.0;
         __syncthreads();
         for (int q = beg + threadIdx.x; q < end; q += kDepositThreads) {
             const int p = base + q;
             int i[3];
             double w[3][ORDER];
-            bool inside = true;
-            for (int a = 0; a < 3; ++a) {
-                i[a] = assign_first<ORDER>(src.x(p, a), inv_d, w[a]);
-                inside = inside && i[a] >= lo[a] && i[a] + ORDER <= lo[a] + len[a];
-            }
+            for (int a = 0; a < 3; ++a) i[a] = assign_first<ORDER>(src.x(p, a), inv_d, w[a]);
             const double m = src.m(p) * inv_vol;
-            if (!inside) {  // a particle on the cube's face, rounded to its other side
+            const int o = cube.first(i);
+            if (o < 0) {
                 direct(i, w, m);
                 continue;
             }
-            const int o = ((i[0] - lo[0]) * len[1] + i[1] - lo[1]) * len[2] + i[2] - lo[2];
             for (int dx = 0; dx < ORDER; ++dx)
                 for (int dy = 0; dy < ORDER; ++dy)
                     for (int dz = 0; dz < ORDER; ++dz)
-                        atomicAdd(&acc[o + (dx * len[1] + dy) * len[2] + dz], m * w[0][dx] * w[1][dy] * w[2][dz]);
+                        atomicAdd(&acc[o + (dx * cube.len[1] + dy) * cube.len[2] + dz], m * w[0][dx] * w[1][dy] * w[2][dz]);
         }
         __syncthreads();
-        for (int q = threadIdx.x; q < nnode; q += kDepositThreads) {
-            const double v = acc[q];
-            if (v == 0.0) continue;
-            const int iz = lo[2] + q % len[2], iy = lo[1] + q / len[2] % len[1], ix = lo[0] + q / (len[1] * len[2]);
-            atomicAdd(&rho[((size_t)((ix % M + M) % M) * M + (iy % M + M) % M) * M + (iz % M + M) % M], v);
-        }
+        for (int q = threadIdx.x; q < nnode; q += kDepositThreads)
+            if (acc[q] != 0.0) atomicAdd(&rho[cube.mesh(q, M)], acc[q]);
         __syncthreads();
         beg = end;
     }
@@ -370,30 +406,136 @@ __global__ void k_interp(S src, int n, double box, int M, const double *__restri
     for (int a = 0; a < 3; ++a) acc[o + a] = g[a];
 }
 
+// Interpolation to particles in Morton order: as k_deposit_cubes, with a cube's nodes of one
+// component at a time in LDS (read once for all its particles, coalesced) and the particles'
+// three sums in registers.  For particles ordered to the cubes only (within one they are in the
+// caller's order), from 2^21 of them and two cells a particle on, and 8 or 27 nodes a particle:
+// 16.7M on 256^3 1.37 -> 1.09 ms, 4M on 160^3 with 27 nodes 1.43 -> 1.20 in all; below, and in tree
+// order (2M on 128^3 0.14 against 0.12 ms), the plain gather is as fast, and 64 nodes a particle
+// leave this form too few registers.
+template <int ORDER>
+__global__ __launch_bounds__(kDepositThreads) void k_interp_cubes(MortonOrder src, const uint64_t *__restrict__ keys,
+                                                                  int levels, int n, double box, int M,
+                                                                  const double *__restrict__ am, double *__restrict__ acc)
+{
+    __shared__ double node[kDepositSide * kDepositSide * kDepositSide];
+    __shared__ CubeHeads heads;
+    const int base = blockIdx.x * kDepositTile, cnt = min(kDepositTile, n - base), sh = 63 - 3 * levels;
+    const int cubes = find_cubes(heads, keys, base, cnt, sh);
+    const double inv_d = M / box, side = ldexp(box, -levels);
+    const size_t nr = (size_t)M * M * M;
+    auto direct = [&](const int *i, const double (*w)[ORDER], int a) __attribute__((always_inline)) {
+        double g = 0;
+        for (int dx = 0; dx < ORDER; ++dx)
+            for (int dy = 0; dy < ORDER; ++dy)
+                for (int dz = 0; dz < ORDER; ++dz) {
+                    const int ix = wrap_node(i[0] + dx, M), iy = wrap_node(i[1] + dy, M), iz = wrap_node(i[2] + dz, M);
+                    g += w[0][dx] * w[1][dy] * w[2][dz] * am[a * nr + ((size_t)ix * M + iy) * M + iz];
+                }
+        return g;
+    };
+    if (cubes > kDepositCubes) {
+        for (int q = threadIdx.x; q < cnt; q += kDepositThreads) {
+            const int p = base + q;
+            int i[3];
+            double w[3][ORDER];
+            for (int a = 0; a < 3; ++a) i[a] = assign_first<ORDER>(src.x(p, a), inv_d, w[a]);
+            const size_t o = src.row(p);
+            for (int a = 0; a < 3; ++a) acc[o + a] = direct(i, w, a);
+        }
+        return;
+    }
+    for (int beg = 0; beg < cnt;) {
+        const int end = next_cube(heads, cubes, beg, cnt);
+        const CubeNodes<ORDER> cube(keys[base + beg] >> sh, levels, side, inv_d);
+        const int nnode = cube.count();
+        double g[kDepositPer][3];
+        unsigned outside = 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            for (int q = threadIdx.x; q < nnode; q += kDepositThreads) node[q] = am[a * nr + cube.mesh(q, M)];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kDepositPer; ++r) {
+                const int q = beg + threadIdx.x + r * kDepositThreads, p = base + q;
+                g[r][a] = 0.0;
+                if (q >= end) continue;
+                int i[3];
+                double w[3][ORDER];
+                for (int b = 0; b < 3; ++b) i[b] = assign_first<ORDER>(src.x(p, b), inv_d, w[b]);
+                const int o = cube.first(i);
+                if (o < 0) {
+                    outside |= 1u << r;
+                    continue;
+                }
+                for (int dx = 0; dx < ORDER; ++dx)
+                    for (int dy = 0; dy < ORDER; ++dy)
+                        for (int dz = 0; dz < ORDER; ++dz)
+                            g[r][a] += w[0][dx] * w[1][dy] * w[2][dz] * node[o + (dx * cube.len[1] + dy) * cube.len[2] + dz];
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < kDepositPer; ++r) {
+            const int q = beg + threadIdx.x + r * kDepositThreads;
+            if (q >= end) continue;
+            const size_t o = src.row(base + q);
+            for (int a = 0; a < 3; ++a) acc[o + a] = g[r][a];
+        }
+        for (int r = 0; outside >> r; ++r) {
+            if (!(outside >> r & 1)) continue;
+            const int p = base + beg + threadIdx.x + r * kDepositThreads;
+            int i[3];
+            double w[3][ORDER];
+            for (int b = 0; b < 3; ++b) i[b] = assign_first<ORDER>(src.x(p, b), inv_d, w[b]);
+            const size_t o = src.row(p);
+            for (int a = 0; a < 3; ++a) acc[o + a] = direct(i, w, a);
+        }
+        beg = end;
+    }
+}
+
 __global__ void k_add3(double *__restrict__ acc, const double *__restrict__ other, size_t n3)
 {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n3) acc[i] += other[i];
 }
 
-__global__ void k_check_finite(const double *__restrict__ pos, size_t n3, int *bad)
+// out[0]: a position is not finite; out[1]: particles in the mesh cell of the one before them.
+__global__ __launch_bounds__(256) void k_check_positions(const double *__restrict__ pos, int n, double inv_d,
+                                                         int *__restrict__ out)
 {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n3 && !isfinite(pos[i])) *bad = 1;
+    __shared__ int same;
+    if (threadIdx.x == 0) same = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+        bool eq = i > 0;
+        for (int a = 0; a < 3; ++a) {
+            const double x = pos[3 * (size_t)i + a];
+            if (!isfinite(x)) out[0] = 1;
+            if (i > 0) eq = eq && floor(x * inv_d) == floor(pos[3 * (size_t)i + a - 3] * inv_d);
+        }
+        mine += eq;
+    }
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+    if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&same, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && same) atomicAdd(&out[1], same);
 }
 
-// Reads the non-finite flag back (synchronises the stream).
-static int check_flag(const int *bad, hipStream_t st)
+// Whether to bring n caller-order particles, `same` of them in the cell of the one before,
+// into mesh order.  Two things make the direct deposit slow: particles of a clump that follow
+// each other in the caller's arrays and queue on the same nodes (some 10 ns each, against 0.1 to
+// 0.2 ms for the order), and mesh nodes that miss the caches.  Measured, ms direct / ordered:
+// clustered 65,536 on 32^3 0.60 / 0.23, 100,000 on 64^3 0.90 / 0.35, 30,000 on 64^3 0.24 / 0.45;
+// uniform 262,144 on 64^3 0.25 / 0.28, 500,000 on 80^3 0.41 / 0.33, 1,048,576 on 100^3 0.81 / 0.44, but
+// 1,000,000 on 250^3, whose nodes hardly two particles share, 1.92 / 2.06.
+static bool use_order(int n, int mesh, int same)
 {
-    int hbad = 0;
-    if (hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return set_error(FMM_ERR_HIP, "pm sync");
-    return hbad ? set_error(FMM_ERR_NAN, "non-finite particle position") : 0;
+    const double cells = (double)mesh * mesh * mesh;
+    return same >= 1 << 14 || (n >= 1 << 19 && 8.0 * n >= cells);
 }
-
-// Caller-order particles are brought into mesh order from this many on: %ORDER%
-constexpr int kOrderMin = 1 << 19;
 
 // Morton levels at which a cube is at most 19 - order mesh cells wide (k_deposit_cubes).
 static int cube_levels(int mesh, int order)
@@ -403,19 +545,13 @@ static int cube_levels(int mesh, int order)
     return l;
 }
 
-// keys: the Morton keys of src's particles, in order by their first 3 cube_levels bits at
-// least, or nullptr (any order).
+// keys: the Morton keys of src's particles, in order by their first 3 cube_levels bits
+// (full_order: by far more than a mesh cell's), or nullptr (any order).
 template <class S>
-static int pm_run(PMPlan *pl, const fmm_params *P, int mesh, int n, S src, const uint64_t *keys, const double *pos_check,
+static int pm_run(PMPlan *pl, const fmm_params *P, int mesh, int n, S src, const uint64_t *keys, bool full_order,
                   double *acc, hipStream_t st)
 {
     size_t nr = (size_t)mesh * mesh * mesh, nc = (size_t)mesh * mesh * (mesh / 2 + 1);
-    if (pos_check) {
-        int *bad = ptr<int>(pl->amesh);  // scratch flag in the (not yet used) output mesh
-        if (int rc = hip_check(hipMemsetAsync(bad, 0, sizeof(int), st), "pm check")) return rc;
-        k_check_finite<<<(unsigned)((3 * (size_t)n + 255) / 256), 256, 0, st>>>(pos_check, 3 * (size_t)n, bad);
-        if (int rc = check_flag(bad, st)) return rc;
-    }
     if (int rc = hip_check(hipMemsetAsync(pl->rho.p, 0, nr * 8, st), "pm mesh")) return rc;
     double d = P->box / mesh;
     const int order = P->pm_assign == 0 ? 2 : P->pm_assign;
@@ -458,7 +594,17 @@ static int pm_run(PMPlan *pl, const fmm_params *P, int mesh, int n, S src, const
             HIPFFT_SUCCESS)
             return set_error(FMM_ERR_HIP, "hipfftExecZ2D");
     }
-    if (order == 3) k_interp<S, 3><<<nb, 256, 0, st>>>(src, n, P->box, mesh, ptr<double>(pl->amesh), acc);
+    bool cubed = false;
+    if constexpr (std::is_same<S, MortonOrder>::value) {
+        cubed = keys && !full_order && order <= 3 && n >= 1 << 21 && 2 * (size_t)n >= nr;
+        const unsigned g = (unsigned)((n + kDepositTile - 1) / kDepositTile);
+        const int lv = cube_levels(mesh, order);
+        const double *am = ptr<double>(pl->amesh);
+        if (cubed && order == 3) k_interp_cubes<3><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, am, acc);
+        else if (cubed) k_interp_cubes<2><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, am, acc);
+    }
+    if (cubed) {}
+    else if (order == 3) k_interp<S, 3><<<nb, 256, 0, st>>>(src, n, P->box, mesh, ptr<double>(pl->amesh), acc);
     else if (order == 4) k_interp<S, 4><<<nb, 256, 0, st>>>(src, n, P->box, mesh, ptr<double>(pl->amesh), acc);
     else k_interp<S, 2><<<nb, 256, 0, st>>>(src, n, P->box, mesh, ptr<double>(pl->amesh), acc);
     int rc = hip_check(hipGetLastError(), "pm");
@@ -476,18 +622,23 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
     PMPlan *pl;
     if (int rc = pm_plan(mesh, &pl)) return rc;
     std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
-    if (n >= kOrderMin && !P->deterministic) {
-        int *bad = ptr<int>(pl->amesh);  // scratch flag in the (not yet used) output mesh
-        if (int rc = hip_check(hipMemsetAsync(bad, 0, sizeof(int), st), "pm check")) return rc;
+    int *check = ptr<int>(pl->amesh), found[2];  // scratch in the (not yet used) output mesh
+    if (int rc = hip_check(hipMemsetAsync(check, 0, 2 * sizeof(int), st), "pm check")) return rc;
+    const int nb = (n + 255) / 256;
+    k_check_positions<<<nb < 2048 ? nb : 2048, 256, 0, st>>>(pos, n, mesh / P->box, check);
+    if (hipMemcpyAsync(found, check, sizeof(found), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return set_error(FMM_ERR_HIP, "pm sync");
+    if (found[0]) return set_error(FMM_ERR_NAN, "non-finite particle position");
+    if (!P->deterministic && use_order(n, mesh, found[1])) {
         const int order = P->pm_assign == 0 ? 2 : P->pm_assign;
         MortonSort &s = g_order;
-        int rc = morton_order(s, n, P->box, pos, mass, cube_levels(mesh, order), bad, st);
+        int rc = morton_order(s, n, P->box, pos, mass, cube_levels(mesh, order), check, st);
         if (rc == 0) {
-            if ((rc = check_flag(bad, st)) == 0)
-                rc = pm_run(pl, P, mesh, n,
-                            MortonOrder{ptr<double>(s.xs), ptr<double>(s.ys), ptr<double>(s.zs), ptr<double>(s.ms),
-                                        ptr<int>(s.idx[s.sorted])},
-                            ptr<uint64_t>(s.keys[s.sorted]), nullptr, acc, st);
+            rc = pm_run(pl, P, mesh, n,
+                        MortonOrder{ptr<double>(s.xs), ptr<double>(s.ys), ptr<double>(s.zs), ptr<double>(s.ms),
+                                    ptr<int>(s.idx[s.sorted])},
+                        ptr<uint64_t>(s.keys[s.sorted]), false, acc, st);
             if ((size_t)n * 56 > kOrderKeep) release_order();
             return rc;
         }
@@ -495,7 +646,7 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
         clear_error();  // no room for the order: the particles as they come
         release_order();
     }
-    return pm_run(pl, P, mesh, n, CallerOrder{pos, mass}, nullptr, pos, acc, st);
+    return pm_run(pl, P, mesh, n, CallerOrder{pos, mass}, nullptr, false, acc, st);
 }
 
 // PM on the particles of a built tree (Morton order, already wrapped and checked).
@@ -509,7 +660,7 @@ int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipS
     return pm_run(pl, P, mesh, (int)t->n,
                   MortonOrder{ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs), ptr<double>(t->ms),
                               ptr<int>(t->perm)},
-                  ptr<uint64_t>(t->keys[t->sorted]), nullptr, acc, st);
+                  ptr<uint64_t>(t->keys[t->sorted]), true, acc, st);
 }
 
 int add_into(double *acc, const double *other, int64_t n3, hipStream_t st)

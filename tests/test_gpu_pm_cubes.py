@@ -57,6 +57,26 @@ def test_hybrid_deposits_in_tree_order(n, mesh):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("mesh,assign", [(33, 0), (120, 3), (161, 0)])
+def test_interpolation_by_cubes(mesh, assign):
+    """From 2^21 particles and half of one a cell on; (161, 0) is just under that density."""
+    n = (1 << 21) + 5
+    pos, m = inputs.clustered(n, 300, inputs.rng_for(655, mesh))
+    pos[:64] = np.round(pos[:64] * mesh) / mesh
+    _close(_run(pos, m, mesh, assign), pm_ewald.pm_forces(pos, m, 1.0, min(0.1, 1.25 / mesh), mesh, order=assign or 2))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,extra", [(16384, 0), (16386, 0), (60000, 3)])
+def test_runs_of_one_cell(n, extra):
+    """Few particles, the order chosen by 2^14 of them that follow one in their own cell (one more or less)."""
+    rng = inputs.rng_for(656, n)
+    pos, m = inputs.uniform(n, rng)
+    pos[:16386] = 0.4 + 1e-3 * pos[:16386]
+    _close(_run(pos, m, 24, extra), pm_ewald.pm_forces(pos, m, 1.0, min(0.1, 1.25 / 24), 24, order=extra or 2))
+
+
+@pytest.mark.gpu
 def test_no_room_for_the_order_falls_back():
     n = (1 << 19) + 5
     pos, m = inputs.clustered(n, 40, inputs.rng_for(652))

@@ -159,6 +159,13 @@ __device__ __forceinline__ int xcd_order(int b, int n)
     return ((i / kXcdRun) * kXcds + x) * kXcdRun + i % kXcdRun;
 }
 
+// Orders one wave's LDS accesses (the hardware keeps them in order, the compiler is told to).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // The value of the previous lane (0 in lane 0): DPP wave_shr:1.
 __device__ __forceinline__ int wave_shift_up1(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false); }
 

@@ -246,6 +246,12 @@ __global__ __launch_bounds__(64) void k_p2m(const Cell *__restrict__ cells, cons
     for (int k = 0; k < NC; ++k) out[k] = (tb.d[k] & 1) ? -acc[k] : acc[k];
 }
 
+// Octant of cell c in its parent: bit 0 x, bit 1 y, bit 2 z.
+__device__ __forceinline__ int octant(const Cell &c)
+{
+    return (cell_ix(c) & 1) | (c.iy & 1) << 1 | (c.iz & 1) << 2;
+}
+
 template <int P, class T>
 __global__ __launch_bounds__(64) void k_m2m(const Cell *__restrict__ cells, const int *__restrict__ inner, int lbeg,
                                             int ln, T *__restrict__ M)
@@ -469,6 +475,66 @@ template <int P, class T> __device__ __forceinline__ void shift_weights(T h, boo
     for (int i = 1; i <= P; ++i) {
         v *= h / (T)i;
         w[i] = (neg && (i & 1)) ? -v : v;
+    }
+}
+
+// M2M for the parents of one level, a workgroup per parent, a wave per child: in each pass of a
+// child's shift a lane takes one line of coefficients along the pass's axis from the LDS row
+// into registers and puts it back shifted.  The children are summed at the end, in the order
+// of the thread-per-parent form below (the results are the same bit for bit).  That form is
+// bound by its chain of dependent operations, some 1,300 multiply-adds a child, eight
+// children in turn: about 41 us a level however few its parents.  The upward pass of a 2M box
+// with the learned selector, whose traversal waits for it (13 levels): 0.52 -> 0.21 ms.
+template <int P, class T>
+__global__ __launch_bounds__(512) void k_m2m_axis_wave(const Cell *__restrict__ cells, const int *__restrict__ inner,
+                                                       int lbeg, T *__restrict__ M)
+{
+    constexpr int NC = ncoef(P), kLines = (P + 1) * (P + 2) / 2;
+    static_assert(kLines <= 64, "a line per lane");
+    __shared__ T rows[8][NC];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, c = inner[lbeg + blockIdx.x];
+    const int nch = cell_nchild(cells[c]), child = cells[c].child;
+    if (nch == 0) return;
+    if (q < nch) {
+        const T *src = M + (size_t)(child + q) * NC;
+        T *row = rows[q];
+        for (int k = lane; k < NC; k += 64) row[k] = src[k];
+        const int oct = octant(cells[child + q]);
+        // the line's two fixed components u, v and the length that leaves the third
+        int e = 0;
+        while ((e + 1) * (e + 2) / 2 <= lane) ++e;
+        const int v = lane - e * (e + 1) / 2, u = e - v, len = P - e;
+        wave_sync();
+        auto pass = [&](auto at, bool neg) __attribute__((always_inline)) {
+            T w[P + 1], C[P + 1];
+            shift_weights<P, T>((T)0.5, neg, w);
+#pragma unroll
+            for (int i = 0; i <= P; ++i) C[i] = lane < kLines ? row[at(min(i, len))] : (T)0;
+#pragma unroll
+            for (int i = P; i >= 1; --i) {
+                T sum = C[i];
+#pragma unroll
+                for (int j = 1; j <= i; ++j) sum = fma(w[j], C[i - j], sum);
+                C[i] = sum;
+            }
+            wave_sync();
+#pragma unroll
+            for (int i = 1; i <= P; ++i)
+                if (i <= len) row[at(i)] = C[i];
+            wave_sync();
+        };
+        pass([&](int i) { return midx(i, u, v); }, oct & 1);
+        pass([&](int i) { return midx(u, i, v); }, oct & 2);
+        pass([&](int i) { return midx(u, v, i); }, oct & 4);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < NC; k += 512) {
+        int d = 0;  // degree of coefficient k
+        while (ncoef(d) <= k) ++d;
+        const T s = (T)(1.0 / (double)(1 << d));
+        T acc = rows[0][k] * s;
+        for (int j = 1; j < nch; ++j) acc += rows[j][k] * s;
+        M[(size_t)c * NC + k] = acc;
     }
 }
 
@@ -864,12 +930,19 @@ template <int P, class T> struct Upward {
         for (int l = t->nlevel - 2; l >= 0; --l) {
             const int lb = t->lvl_beg[l] - t->leaf_lvl[l], ln = t->lvl_beg[l + 1] - t->leaf_lvl[l + 1] - lb;
             if (ln <= 0) continue;
-            if constexpr (P >= 7)
-                k_m2m_axis<P, T><<<nblk(ln, 64), 64, 0, st>>>(ptr<Cell>(t->cells), ptr<int>(t->inner), lb, ln,
-                                                               ptr<T>(t->Mc));
-            else
+            if constexpr (P >= 7) {
+                // the workgroup-per-parent form up to where the thread-per-parent form, whose
+                // time hardly depends on the number of parents, catches up; FP32 order 8:
+                // 362 parents 11 us against 41, 1,861 parents 22 / 41, 3,753 parents 45 / 42
+                if (ln <= 2048)
+                    k_m2m_axis_wave<P, T><<<ln, 512, 0, st>>>(ptr<Cell>(t->cells), ptr<int>(t->inner), lb, ptr<T>(t->Mc));
+                else
+                    k_m2m_axis<P, T><<<nblk(ln, 64), 64, 0, st>>>(ptr<Cell>(t->cells), ptr<int>(t->inner), lb, ln,
+                                                                   ptr<T>(t->Mc));
+            } else {
                 k_m2m<P, T><<<nblk(ln, 64), 64, 0, st>>>(ptr<Cell>(t->cells), ptr<int>(t->inner), lb, ln,
                                                           ptr<T>(t->Mc));
+            }
         }
         return hip_check(hipGetLastError(), "upward pass");
     }

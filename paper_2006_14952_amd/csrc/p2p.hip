@@ -91,13 +91,6 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v)
     s = t;
 }
 
-// Orders one wave's LDS accesses (the hardware keeps them in order, the compiler is told to).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 constexpr int kStage = 256;  // FP32 form; the FP64 form's 32-byte records are staged 128 at a time
 template <bool F64> constexpr int stage_slots() { return F64 ? 128 : kStage; }
 

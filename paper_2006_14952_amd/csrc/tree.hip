@@ -58,13 +58,11 @@ __global__ void k_keys(const double *__restrict__ pos, int n, double box, uint64
 }
 
 // ---------------------------------------------------------------------------
-// LSD radix sort, 8-bit digits.  A tile of 4096 keys per 256-thread block; each wave
-// handles 1024 consecutive keys in 16 rounds of 64, ranking equal digits inside a
+// LSD radix sort, 8-bit digits.  A tile of 256 ROUNDS keys per 256-thread block; each wave
+// handles 64 ROUNDS consecutive keys in rounds of 64, ranking equal digits inside a
 // round with ballots, so the scatter is stable.
 
 constexpr int kRsThreads = 256;
-constexpr int kRsRounds = 16;
-constexpr int kRsTile = kRsThreads * kRsRounds;
 
 // Box of original particle index v: the largest b with off[b] <= v (empty boxes skipped).
 __device__ inline int box_of(const int *off, int nbox, uint32_t v)
@@ -86,6 +84,8 @@ __device__ inline int rs_digit(uint64_t key, uint32_t val, int shift, const int 
     return (int)((key >> shift) & 0xff);
 }
 
+// Digit counts of each tile: hist[digit][tile], or hist[tile][digit] (OWN, below).
+template <int ROUNDS, bool OWN>
 __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint64_t *__restrict__ keys,
                                                         const uint32_t *__restrict__ vals, int n, int shift,
                                                         const int *__restrict__ boxoff, int nbox, int nblocks,
@@ -94,19 +94,22 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint64_t *__restri
     __shared__ int h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
-    int base = blockIdx.x * kRsTile;
-    for (int k = 0; k < kRsRounds; ++k) {
+    int base = blockIdx.x * kRsThreads * ROUNDS;
+    for (int k = 0; k < ROUNDS; ++k) {
         int i = base + k * kRsThreads + threadIdx.x;
         if (i < n) atomicAdd(&h[rs_digit(keys[i], vals[i], shift, boxoff, nbox)], 1);
     }
     __syncthreads();
-    hist[threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    if constexpr (OWN) hist[blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+    else hist[threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
 // Scatter of one tile: the keys are ranked by digit in registers (ballots, as before),
 // placed in LDS in the tile's digit order, and written from there by consecutive threads, so
 // each digit's run of the tile goes out as consecutive addresses (whole cache lines) rather
-// than as one scattered 8-byte store per key.
+// than as one scattered 8-byte store per key.  offs: the scanned counts; or (OWN, few tiles) the
+// counts, from which every tile adds up its own places, instead of one to three launches of a scan.
+template <int ROUNDS, bool OWN>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint64_t *__restrict__ kin,
                                                            const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout,
                                                            uint32_t *__restrict__ vout, int n, int shift,
@@ -117,11 +120,27 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint64_t *__res
     __shared__ int boff[256];
     __shared__ int dstart[256];  // first slot of each digit in the tile ordered by digit
     __shared__ int wsum[4];
+    constexpr int kRsRounds = ROUNDS, kRsTile = kRsThreads * ROUNDS;
     __shared__ uint64_t skey[kRsTile];
     __shared__ uint32_t sval[kRsTile];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int k = threadIdx.x; k < 4 * 256; k += kRsThreads) (&cnt[0][0])[k] = 0;
-    boff[threadIdx.x] = offs[threadIdx.x * nblocks + blockIdx.x];
+    if constexpr (OWN) {
+        int before = 0, total = 0;
+#pragma unroll 16
+        for (int b = 0; b < nblocks; ++b) {
+            const int c = offs[b * 256 + threadIdx.x];
+            total += c;
+            before += b < (int)blockIdx.x ? c : 0;
+        }
+        const int incl = wave_incl_sum(total);
+        if (lane == 63) wsum[w] = incl;
+        __syncthreads();
+        for (int q = 0; q < w; ++q) before += wsum[q];
+        boff[threadIdx.x] = before + incl - total;
+    } else {
+        boff[threadIdx.x] = offs[threadIdx.x * nblocks + blockIdx.x];
+    }
     __syncthreads();
     const uint64_t lt = (1ull << lane) - 1ull;
     const int base = blockIdx.x * kRsTile + w * (kRsTile / 4);
@@ -184,31 +203,152 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint64_t *__res
     }
 }
 
-// Passes over the Morton key's digits first_digit .. 7, then (batches) 1 or 2 passes over
-// the box index, so the order is by box, then by key; stable throughout.  Sorts the buffer
-// pair `sorted` of keys and idx (0 after k_keys) and sets it to the pair with the result.
-static int radix_sort(DevBuf (&keys)[2], DevBuf (&idx)[2], DevBuf &tmp, DevBuf &scan_tmp, int &sorted, int n,
-                      const int *boxoff, int nbox, int first_digit, hipStream_t st)
+// All passes of a small sort in one workgroup: the particles stay in registers, ROUNDS to a
+// thread, and change places through LDS; ranks as in k_rs_scatter, over sixteen waves.  Bound by
+// the LDS chains of a pass and its five barriers.
+template <int ROUNDS>
+__global__ __launch_bounds__(1024) void k_rs_small(uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, int n,
+                                                   int first_digit, int npass, const int *__restrict__ boxoff, int nbox)
 {
-    int nb = (n + kRsTile - 1) / kRsTile;
-    if (int rc = grow(tmp, (size_t)256 * nb * 2 * sizeof(int))) return rc;
-    int *hist = ptr<int>(tmp), *offs = hist + 256 * nb;
-    int npass = 8 + (nbox > 1) + (nbox > 256);
-    int cur = sorted;
+    __shared__ int cnt[16][256];
+    __shared__ int dstart[256], wsum[4];
+    __shared__ uint64_t skey[1024 * ROUNDS];
+    __shared__ uint32_t sval[1024 * ROUNDS];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, base = w * 64 * ROUNDS + lane;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    uint64_t key[ROUNDS];
+    uint32_t val[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int i = base + 64 * r;
+        key[r] = i < n ? keys[i] : 0;
+        val[r] = i < n ? vals[i] : 0;
+    }
     for (int pass = first_digit; pass < npass; ++pass) {
-        bool bpass = pass >= 8;
-        int shift = bpass ? 8 * (pass - 8) : 8 * pass;
-        const int *bo = bpass ? boxoff : nullptr;
-        k_rs_hist<<<nb, kRsThreads, 0, st>>>(ptr<uint64_t>(keys[cur]), ptr<uint32_t>(idx[cur]), n, shift, bo, nbox, nb,
-                                             hist);
-        if (int rc = scan_exclusive(hist, offs, 256 * nb, nullptr, st, scan_tmp)) return rc;
-        k_rs_scatter<<<nb, kRsThreads, 0, st>>>(ptr<uint64_t>(keys[cur]), ptr<uint32_t>(idx[cur]),
-                                                ptr<uint64_t>(keys[cur ^ 1]), ptr<uint32_t>(idx[cur ^ 1]), n, shift, bo,
-                                                nbox, nb, offs);
+        const int shift = pass >= 8 ? 8 * (pass - 8) : 8 * pass;
+        const int *bo = pass >= 8 ? boxoff : nullptr;
+        for (int k = threadIdx.x; k < 16 * 256; k += 1024) (&cnt[0][0])[k] = 0;
+        __syncthreads();
+        int pos[ROUNDS], dig[ROUNDS];
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const bool ok = base + 64 * r < n;
+            const int d = rs_digit(key[r], val[r], shift, bo, nbox);
+            uint64_t peers = __ballot(ok);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const uint64_t m = __ballot((d >> b) & 1);
+                peers &= ((d >> b) & 1) ? m : ~m;
+            }
+            const int old = cnt[w][d], rank = __popcll(peers & lt);
+            if (ok && rank == 0) cnt[w][d] = old + __popcll(peers);
+            dig[r] = d;
+            pos[r] = ok ? old + rank : -1;
+        }
+        __syncthreads();
+        int run = 0, incl = 0;
+        if (threadIdx.x < 256) {  // per-digit prefix over the waves, then over the digits
+            int c[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) c[q] = cnt[q][threadIdx.x];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                cnt[q][threadIdx.x] = run;
+                run += c[q];
+            }
+            incl = wave_incl_sum(run);
+            if (lane == 63) wsum[w] = incl;
+        }
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            int add = incl - run;
+            for (int q = 0; q < w; ++q) add += wsum[q];
+            dstart[threadIdx.x] = add;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            if (pos[r] < 0) continue;
+            const int l = dstart[dig[r]] + cnt[w][dig[r]] + pos[r];
+            skey[l] = key[r];
+            sval[l] = val[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            key[r] = skey[base + 64 * r];
+            val[r] = sval[base + 64 * r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int i = base + 64 * r;
+        if (i < n) {
+            keys[i] = key[r];
+            vals[i] = val[r];
+        }
+    }
+}
+
+struct RsArgs {
+    DevBuf *keys, *idx;
+    int n, nbox, first_digit, npass;
+    const int *boxoff;
+};
+
+template <int ROUNDS, bool OWN>
+static int radix_passes(const RsArgs &a, DevBuf &tmp, DevBuf &scan_tmp, int &sorted, hipStream_t st)
+{
+    constexpr int kRsTile = kRsThreads * ROUNDS;
+    const int nb = (a.n + kRsTile - 1) / kRsTile;
+    if (int rc = grow(tmp, (size_t)256 * nb * 2 * sizeof(int))) return rc;
+    int *hist = ptr<int>(tmp), *offs = OWN ? hist : hist + 256 * nb;
+    int cur = sorted;
+    for (int pass = a.first_digit; pass < a.npass; ++pass) {
+        const int shift = pass >= 8 ? 8 * (pass - 8) : 8 * pass;
+        const int *bo = pass >= 8 ? a.boxoff : nullptr;
+        const uint64_t *kin = ptr<uint64_t>(a.keys[cur]);
+        const uint32_t *vin = ptr<uint32_t>(a.idx[cur]);
+        k_rs_hist<ROUNDS, OWN><<<nb, kRsThreads, 0, st>>>(kin, vin, a.n, shift, bo, a.nbox, nb, hist);
+        if constexpr (!OWN)
+            if (int rc = scan_exclusive(hist, offs, 256 * nb, nullptr, st, scan_tmp)) return rc;
+        k_rs_scatter<ROUNDS, OWN><<<nb, kRsThreads, 0, st>>>(kin, vin, ptr<uint64_t>(a.keys[cur ^ 1]),
+                                                             ptr<uint32_t>(a.idx[cur ^ 1]), a.n, shift, bo, a.nbox, nb,
+                                                             offs);
         cur ^= 1;
     }
     sorted = cur;
     return hip_check(hipGetLastError(), "radix sort");
+}
+
+// Passes over the Morton key's digits first_digit .. 7, then (batches) 1 or 2 passes over
+// the box index, so the order is by box, then by key; stable throughout.  Sorts the buffer
+// pair `sorted` of keys and idx (0 after k_keys) and sets it to the pair with the result.
+//
+// Three forms, by the time of a whole tree build (us, clustered boxes):
+//   n                                   4,096  8,192  16,384  65,536  131,072  524,288  1,048,576  2,097,152
+//   one workgroup                         124    148
+//   tiles of 1,024 that add up places     161    179     168     175      192      288        500      1,255
+//   tiles of 2,048, the same              179    191     194     196      205      262        349        610
+//   tiles of 4,096 and a scan             214    249     255     295      305      332        364        453
+// Small sorts are bound by the launches of six passes, in sequence some 20 us a pass with the
+// scan; large ones by memory, and the tiles' own sums grow with the square of their number.
+static int radix_sort(DevBuf (&keys)[2], DevBuf (&idx)[2], DevBuf &tmp, DevBuf &scan_tmp, int &sorted, int n,
+                      const int *boxoff, int nbox, int first_digit, hipStream_t st)
+{
+    const RsArgs a{keys, idx, n, nbox, first_digit, 8 + (nbox > 1) + (nbox > 256), boxoff};
+    auto small = [&](auto kernel) {
+        kernel<<<1, 1024, 0, st>>>(ptr<uint64_t>(keys[sorted]), ptr<uint32_t>(idx[sorted]), n, first_digit, a.npass,
+                                   boxoff, nbox);
+        return hip_check(hipGetLastError(), "radix sort");
+    };
+    if (n <= 1 << 10) return small(k_rs_small<1>);
+    if (n <= 1 << 11) return small(k_rs_small<2>);
+    if (n <= 1 << 12) return small(k_rs_small<4>);
+    if (n <= 1 << 13) return small(k_rs_small<8>);
+    if (n <= 1 << 17) return radix_passes<4, true>(a, tmp, scan_tmp, sorted, st);
+    if (n <= 1 << 20) return radix_passes<8, true>(a, tmp, scan_tmp, sorted, st);
+    return radix_passes<16, false>(a, tmp, scan_tmp, sorted, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -412,8 +412,8 @@ __device__ __forceinline__ int first_level(const TreeIn &t, int i, int b, uint64
     return 1 + shared_levels(key, t.keys[i - 1], t.lmax);
 }
 
-constexpr int kTreeThreads = 256, kTreeItems = 4, kTreeTile = kTreeThreads * kTreeItems;
-constexpr int kTreeChunks = kTreeTile / 64;  // runs of 64 particles, one wave each
+// Tiles of 256 ITEMS particles, runs of 64 of them to a wave.
+constexpr int kTreeThreads = 256;
 constexpr int kTreeWin = 512;                // widest window (n_crit) whose maximum is taken in LDS
 
 // Widest windows: e_j for j >= -n_crit in bytes, then maxima over 2, 4, ... of them.
@@ -434,10 +434,12 @@ __global__ void k_window_max(const unsigned char *__restrict__ in, unsigned char
 // Depths D_i and, per tile and level, the cells and the leaves that begin there:
 // count[(l - 1) nblk + tile] and count[(21 + l - 1) nblk + tile] for l = 1 .. 21.
 // win: maxima over 2^wexp entries of the window array (wide windows), else nullptr.
+template <int ITEMS>
 __global__ __launch_bounds__(kTreeThreads) void k_depth(TreeIn t, const unsigned char *__restrict__ win, int wexp,
                                                         unsigned char *__restrict__ depth, int nblk,
                                                         int *__restrict__ count, int *__restrict__ deep)
 {
+    constexpr int kTreeTile = kTreeThreads * ITEMS;
     __shared__ unsigned char m[2][kTreeTile + kTreeWin];
     __shared__ int cnt[2][kMaxLevel];
     const int lane = threadIdx.x & 63;
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_depth(TreeIn t, const unsigned
         __syncthreads();
     }
     bool isdeep = false;
-    for (int k = 0; k < kTreeItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const int p = k * kTreeThreads + threadIdx.x, i = base + p;
         const bool valid = i < t.n;
         int d = kMaxLevel + 1, D = 0;
@@ -500,11 +502,20 @@ __global__ __launch_bounds__(kTreeThreads) void k_depth(TreeIn t, const unsigned
 }
 
 // One workgroup: the roots (level 0, one per box, empty boxes too).  out: their cells, and
-// their places among the leaves and the cells with children (nullptr: only the leaf count).
+// their places among the leaves and the cells with children; or (cells nullptr) what the host
+// sizes the tree by: the roots' leaf count, the scan of count at the first tile of every level,
+// starts[0 .. 41], and its total, starts[42].
 __global__ __launch_bounds__(1024) void k_roots(const int *__restrict__ boxoff, int nbox, int ncrit,
                                                 Cell *__restrict__ cells, int *__restrict__ leaves,
-                                                int *__restrict__ inner, int *__restrict__ nleaf0)
+                                                int *__restrict__ inner, int *__restrict__ nleaf0,
+                                                const int *__restrict__ count, const int *__restrict__ scan, int nblk,
+                                                int *__restrict__ starts)
 {
+    constexpr int kRows = 2 * kMaxLevel;
+    if (starts && threadIdx.x <= kRows) {
+        const size_t end = (size_t)kRows * nblk - 1, at = (size_t)threadIdx.x * nblk;
+        starts[threadIdx.x] = threadIdx.x < kRows ? scan[at] : scan[end] + count[end];
+    }
     __shared__ int wsum[16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int before = 0;
@@ -541,23 +552,21 @@ __global__ __launch_bounds__(1024) void k_roots(const int *__restrict__ boxoff, 
     if (nleaf0 && threadIdx.x == 0) *nleaf0 = before;
 }
 
-// The scan's values at the first tile of every level: out[0 .. 41], and its total at out[42].
-__global__ void k_level_starts(const int *__restrict__ scan, int nblk, const int *__restrict__ total, int *__restrict__ out)
-{
-    const int k = threadIdx.x;
-    if (k < 2 * kMaxLevel) out[k] = scan[(size_t)k * nblk];
-    if (k == 2 * kMaxLevel) out[k] = *total;
-}
-
 // The cells of levels 1 .. 21 (all but the child counts), the leaf and inner-cell lists and
 // the leaf of each particle.  Each wave takes runs of 64 particles; a level's cells that begin
-// in the run are numbered by ballots.
+// in the run are numbered by ballots.  The cells that reach past their run, at most one a level,
+// all hold the run's last particle: their ends are searched for first, a thread per run and
+// level.  Searched for level by level where the cells are written, the dependent key reads took
+// most of the pass: 262k box 40 -> 26 us, 2M box 62 -> 43, 16.7M box 312 -> 246.
+template <int ITEMS>
 __global__ __launch_bounds__(kTreeThreads) void k_cells(TreeIn t, const unsigned char *__restrict__ depth, int nblk,
                                                         const int *__restrict__ scan, int nleaf0,
                                                         Cell *__restrict__ cells, int *__restrict__ leaves,
                                                         int *__restrict__ inner, int *__restrict__ leaf_of)
 {
+    constexpr int kTreeTile = kTreeThreads * ITEMS, kTreeChunks = kTreeTile / 64;
     __shared__ int cc[kTreeChunks][kMaxLevel + 1], cl[kTreeChunks][kMaxLevel + 1];
+    __shared__ int ends[kTreeChunks][kMaxLevel + 1], open[kTreeChunks][2];  // open: levels to search, [0] .. [1]
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t lt = (1ull << lane) - 1ull, le = lt | 1ull << lane;
     const int base = blockIdx.x * kTreeTile;
@@ -566,10 +575,10 @@ __global__ __launch_bounds__(kTreeThreads) void k_cells(TreeIn t, const unsigned
         (&cl[0][0])[q] = 0;
     }
     __syncthreads();
-    uint64_t key[kTreeItems];
-    int box[kTreeItems], d[kTreeItems], D[kTreeItems];
+    uint64_t key[ITEMS];
+    int box[ITEMS], d[ITEMS], D[ITEMS];
 #pragma unroll
-    for (int k = 0; k < kTreeItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const int i = base + k * kTreeThreads + threadIdx.x, ch = k * (kTreeThreads / 64) + w;
         key[k] = 0;
         box[k] = 0;
@@ -582,11 +591,21 @@ __global__ __launch_bounds__(kTreeThreads) void k_cells(TreeIn t, const unsigned
             d[k] = first_level(t, i, box[k], key[k]);
         }
         const bool starts = d[k] <= D[k];  // never past the last particle
+        const int last = min(63, t.n - 1 - (base + ch * 64));
+        if (lane == 0) {  // none
+            open[ch][0] = kMaxLevel + 1;
+            open[ch][1] = 0;
+        }
         if (__ballot(starts) == 0) continue;
         int lo = starts ? d[k] : kMaxLevel + 1, hi = starts ? D[k] : 0;
         for (int o = 32; o > 0; o >>= 1) {
             lo = min(lo, __shfl_xor(lo, o, 64));
             hi = max(hi, __shfl_xor(hi, o, 64));
+        }
+        const int dlast = __builtin_amdgcn_readlane(D[k], last);
+        if (lane == 0) {
+            open[ch][0] = lo;
+            open[ch][1] = dlast;
         }
         for (int l = lo > 1 ? lo : 1; l <= hi; ++l) {
             const uint64_t mc = __ballot(starts && d[k] <= l && l <= D[k]), ml = __ballot(starts && D[k] == l);
@@ -597,6 +616,31 @@ __global__ __launch_bounds__(kTreeThreads) void k_cells(TreeIn t, const unsigned
         }
     }
     __syncthreads();
+    for (int q = threadIdx.x; q < kTreeChunks * 32; q += kTreeThreads) {
+        const int ch = q >> 5, l = q & 31;
+        if (l < max(open[ch][0], 1) || l > open[ch][1]) continue;
+        // the first key outside the last particle's cell: by doubling steps, then bisection
+        const int last = min(base + ch * 64 + 63, t.n - 1), sh = 3 * (kMaxLevel - l);
+        const int bend = box_end(t, tree_box(t, last));
+        const uint64_t pre = t.keys[last] >> sh;
+        int a = last, step = 1;  // particle a is inside
+        int z = bend;            // particle z is outside, or z = bend
+        while (a < bend - 1) {
+            const int e = a + min(step, bend - 1 - a);
+            if ((t.keys[e] >> sh) != pre) {
+                z = e;
+                break;
+            }
+            a = e;
+            step *= 2;
+        }
+        while (z - a > 1) {
+            const int mid = a + (z - a) / 2;
+            if ((t.keys[mid] >> sh) == pre) a = mid;
+            else z = mid;
+        }
+        ends[ch][l] = z;
+    }
     if (lane >= 1 && lane <= kMaxLevel && w < 2) {  // exclusive over the runs, from the scan's base
         const int l = lane;
         const size_t row = (size_t)((w ? kMaxLevel : 0) + l - 1) * nblk;
@@ -610,7 +654,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_cells(TreeIn t, const unsigned
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kTreeItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const int ch = k * (kTreeThreads / 64) + w, c0 = base + ch * 64, i = c0 + lane;
         if (c0 >= t.n) continue;
         const bool valid = i < t.n, starts = valid && d[k] <= D[k];
@@ -637,30 +681,8 @@ __global__ __launch_bounds__(kTreeThreads) void k_cells(TreeIn t, const unsigned
                 const int c = at - 1, sh = 3 * (kMaxLevel - l);
                 const int lb = cl[ch][l] + (int)__popcll(ml & lt);  // leaves before this cell
                 const uint64_t pre = key[k] >> sh;
-                int end;
                 const uint64_t later = mb & ~le;
-                const int bend = box_end(t, box[k]);
-                if (later) {
-                    end = c0 + (int)__ffsll((unsigned long long)later) - 1;
-                } else {  // past this run: the first key outside the cell, by doubling steps, then bisection
-                    int a = c0 + 63, step = 1;  // particle a is inside, or the box ends at it
-                    int z = bend;                // particle z is outside, or z = bend
-                    while (a < bend - 1) {
-                        const int q = a + min(step, bend - 1 - a);
-                        if ((t.keys[q] >> sh) != pre) {
-                            z = q;
-                            break;
-                        }
-                        a = q;
-                        step *= 2;
-                    }
-                    while (z - a > 1) {
-                        const int mid = a + (z - a) / 2;
-                        if ((t.keys[mid] >> sh) == pre) a = mid;
-                        else z = mid;
-                    }
-                    end = z;
-                }
+                const int end = later ? c0 + (int)__ffsll((unsigned long long)later) - 1 : ends[ch][l];
                 Cell q;
                 q.xln = pack_xln((int)compact3(pre >> 2), l, 0);
                 q.iy = (int)compact3(pre >> 1);
@@ -777,7 +799,8 @@ int tree_build(fmm_tree *t, const fmm_params *P, int64_t n64, const double *pos,
     t->lvl_beg.assign(1, 0);
     if (n == 0) {  // the empty roots
         if ((rc = grow(t->cells, sizeof(Cell) * (size_t)nbox))) return rc;
-        k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, P->n_crit, ptr<Cell>(t->cells), nullptr, nullptr, nullptr);
+        k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, P->n_crit, ptr<Cell>(t->cells), nullptr, nullptr, nullptr, nullptr,
+                                    nullptr, 0, nullptr);
         t->lvl_beg.push_back(nbox);
         t->nlevel = 1;
         t->ncell = nbox;
@@ -794,11 +817,15 @@ int tree_build(fmm_tree *t, const fmm_params *P, int64_t n64, const double *pos,
     // a tree that splits a level-15 cell needs the two lowest digits: its arrays are sorted
     // again over every digit (a full LSD sort of the partly sorted arrays).
     constexpr int kPartialDigit = 2, kPartialLevel = 15;
-    const int nblk = blocks(n, kTreeTile), ncount = 2 * kMaxLevel * nblk;
+    // small tiles, a run to each wave, where one run after another is what bounds the passes;
+    // measured (us a build, tiles of 256 / 1,024 particles): 4,096 particles 112 / 118, 131,072
+    // 155 / 166, 524,288 230 / 242, 1,048,576 330 / 330, 2,097,152 446 / 435, 16,777,216 2,880 / 2,743
+    const bool small = n <= 1 << 19;
+    const int nblk = blocks(n, kTreeThreads * (small ? 1 : 4)), ncount = 2 * kMaxLevel * nblk;
     const int nc = P->n_crit;
     int wexp = 0;  // 2^wexp <= n_crit + 1 < 2^(wexp + 1)
     while (((int64_t)2 << wexp) <= (int64_t)nc + 1) ++wexp;
-    int *total = bad + 1, *deep = bad + 2, *nleaf0 = bad + 3, *starts = bad + 8;  // flag area
+    int *deep = bad + 2, *nleaf0 = bad + 3, *starts = bad + 8;  // flag area
     int *h = t->host;
     int *scan = nullptr;
     const unsigned char *depth = nullptr;
@@ -827,10 +854,10 @@ int tree_build(fmm_tree *t, const fmm_params *P, int64_t n64, const double *pos,
         if ((rc = grow(t->nch, (size_t)ncount * 2 * sizeof(int)))) return rc;
         int *count = ptr<int>(t->nch);
         scan = count + ncount;
-        k_depth<<<nblk, kTreeThreads, 0, st>>>(in, win, wexp, dep, nblk, count, deep);
-        if ((rc = scan_exclusive(count, scan, ncount, total, st, t->scan_tmp))) return rc;
-        k_level_starts<<<1, 64, 0, st>>>(scan, nblk, total, starts);
-        k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, nc, nullptr, nullptr, nullptr, nleaf0);
+        (small ? k_depth<1> : k_depth<4>)<<<nblk, kTreeThreads, 0, st>>>(in, win, wexp, dep, nblk, count, deep);
+        if ((rc = scan_exclusive(count, scan, ncount, nullptr, st, t->scan_tmp))) return rc;
+        k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, nc, nullptr, nullptr, nullptr, nleaf0, count, scan, nblk,
+                                    starts);
         if ((rc = hip_check(hipMemcpyAsync(h, bad, 64 * sizeof(int), hipMemcpyDeviceToHost, st), "tree sizes")) ||
             (rc = hip_check(hipEventRecord(t->bev, st), "event")))
             return rc;
@@ -876,8 +903,8 @@ int tree_build(fmm_tree *t, const fmm_params *P, int64_t n64, const double *pos,
               grow(t->inner, (size_t)ninner * 4 + 4)))
         return rc;
     k_roots<<<1, 1024, 0, st>>>(ptr<int>(t->boxoff), nbox, nc, ptr<Cell>(t->cells), ptr<int>(t->leaves),
-                                ptr<int>(t->inner), nullptr);
-    k_cells<<<nblk, kTreeThreads, 0, st>>>(in, depth, nblk, scan, n0, ptr<Cell>(t->cells), ptr<int>(t->leaves),
+                                ptr<int>(t->inner), nullptr, nullptr, nullptr, 0, nullptr);
+    (small ? k_cells<1> : k_cells<4>)<<<nblk, kTreeThreads, 0, st>>>(in, depth, nblk, scan, n0, ptr<Cell>(t->cells), ptr<int>(t->leaves),
                                            ptr<int>(t->inner), ptr<int>(t->leaf_of));
     if (ninner > 0)
         k_child_counts<<<blocks(ninner, 256), 256, 0, st>>>(ptr<Cell>(t->cells), t->ncell, ptr<int>(t->inner), ninner);

@@ -607,9 +607,7 @@ static int pm_run(PMPlan *pl, const fmm_params *P, int mesh, int n, S src, const
     else if (order == 3) k_interp<S, 3><<<nb, 256, 0, st>>>(src, n, P->box, mesh, ptr<double>(pl->amesh), acc);
     else if (order == 4) k_interp<S, 4><<<nb, 256, 0, st>>>(src, n, P->box, mesh, ptr<double>(pl->amesh), acc);
     else k_interp<S, 2><<<nb, 256, 0, st>>>(src, n, P->box, mesh, ptr<double>(pl->amesh), acc);
-    int rc = hip_check(hipGetLastError(), "pm");
-    if (rc == 0) rc = hip_check(hipStreamSynchronize(st), "pm");  // mesh buffers are reused by the next call
-    return rc;
+    return hip_check(hipGetLastError(), "pm");
 }
 
 int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, const double *mass, double *acc,
@@ -639,6 +637,7 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
                         MortonOrder{ptr<double>(s.xs), ptr<double>(s.ys), ptr<double>(s.zs), ptr<double>(s.ms),
                                     ptr<int>(s.idx[s.sorted])},
                         ptr<uint64_t>(s.keys[s.sorted]), false, acc, st);
+            if (rc == 0) rc = hip_check(hipStreamSynchronize(st), "pm");  // the buffers are the next call's
             if ((size_t)n * 56 > kOrderKeep) release_order();
             return rc;
         }
@@ -646,17 +645,20 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
         clear_error();  // no room for the order: the particles as they come
         release_order();
     }
-    return pm_run(pl, P, mesh, n, CallerOrder{pos, mass}, nullptr, false, acc, st);
+    if (int rc = pm_run(pl, P, mesh, n, CallerOrder{pos, mass}, nullptr, false, acc, st)) return rc;
+    return hip_check(hipStreamSynchronize(st), "pm");
 }
 
-// PM on the particles of a built tree (Morton order, already wrapped and checked).
-int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st)
+// PM on the particles of a built tree (Morton order, already wrapped and checked), enqueued on
+// st.  The plan's buffers are shared: lk is held on return, until st has done with them.
+int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st,
+                   std::unique_lock<std::mutex> &lk)
 {
     if (mesh < 8 || mesh > 1024) return set_error(FMM_ERR_ARG, "mesh must be in [8, 1024]");
     if (t->n == 0) return 0;
     PMPlan *pl;
     if (int rc = pm_plan(mesh, &pl)) return rc;
-    std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
+    lk = std::unique_lock<std::mutex>(g_pm_mu);
     return pm_run(pl, P, mesh, (int)t->n,
                   MortonOrder{ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs), ptr<double>(t->ms),
                               ptr<int>(t->perm)},

@@ -524,18 +524,16 @@ __global__ __launch_bounds__(256) void k_check_positions(const double *__restric
     if (threadIdx.x == 0 && same) atomicAdd(&out[1], same);
 }
 
-// Whether to bring n caller-order particles, `same` of them in the cell of the one before,
-// into mesh order.  Two things make the direct deposit slow: particles of a clump that follow
-// each other in the caller's arrays and queue on the same nodes (some 10 ns each, against 0.1 to
-// 0.2 ms for the order), and mesh nodes that miss the caches.  Measured, ms direct / ordered:
-// clustered 65,536 on 32^3 0.60 / 0.23, 100,000 on 64^3 0.90 / 0.35, 30,000 on 64^3 0.24 / 0.45;
-// uniform 262,144 on 64^3 0.25 / 0.28, 500,000 on 80^3 0.41 / 0.33, 1,048,576 on 100^3 0.81 / 0.44, but
+// Whether to bring n caller-order particles into mesh order: always if enough of them share the
+// mesh's nodes (dense), else if many, `same` of them, lie in the cell of the one before.  Two
+// things make the direct deposit slow: particles of a clump that follow each other in the
+// caller's arrays and queue on the same nodes (some 10 ns each, against 0.1 to 0.2 ms for the
+// order), and mesh nodes that miss the caches.  Measured, ms direct / ordered: clustered
+// 65,536 on 32^3 0.60 / 0.23, 100,000 on 64^3 0.90 / 0.35, 30,000 on 64^3 0.24 / 0.45; uniform
+// 262,144 on 64^3 0.25 / 0.28, 500,000 on 80^3 0.41 / 0.33, 1,048,576 on 100^3 0.81 / 0.44, but
 // 1,000,000 on 250^3, whose nodes hardly two particles share, 1.92 / 2.06.
-static bool use_order(int n, int mesh, int same)
-{
-    const double cells = (double)mesh * mesh * mesh;
-    return same >= 1 << 14 || (n >= 1 << 19 && 8.0 * n >= cells);
-}
+static bool dense(int n, int mesh) { return n >= 1 << 19 && 8.0 * n >= (double)mesh * mesh * mesh; }
+constexpr int kSameMin = 1 << 14;
 
 // Morton levels at which a cube is at most 19 - order mesh cells wide (k_deposit_cubes).
 static int cube_levels(int mesh, int order)
@@ -620,23 +618,32 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
     PMPlan *pl;
     if (int rc = pm_plan(mesh, &pl)) return rc;
     std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
-    int *check = ptr<int>(pl->amesh), found[2];  // scratch in the (not yet used) output mesh
+    int *check = ptr<int>(pl->amesh), found[2] = {0, 0};  // scratch in the (not yet used) output mesh
     if (int rc = hip_check(hipMemsetAsync(check, 0, 2 * sizeof(int), st), "pm check")) return rc;
-    const int nb = (n + 255) / 256;
-    k_check_positions<<<nb < 2048 ? nb : 2048, 256, 0, st>>>(pos, n, mesh / P->box, check);
-    if (hipMemcpyAsync(found, check, sizeof(found), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return set_error(FMM_ERR_HIP, "pm sync");
-    if (found[0]) return set_error(FMM_ERR_NAN, "non-finite particle position");
-    if (!P->deterministic && use_order(n, mesh, found[1])) {
+    auto read_check = [&]() -> int {
+        if (hipMemcpyAsync(found, check, sizeof(found), hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return set_error(FMM_ERR_HIP, "pm sync");
+        return found[0] ? set_error(FMM_ERR_NAN, "non-finite particle position") : 0;
+    };
+    auto check_all = [&]() -> int {
+        const int nb = (n + 255) / 256;
+        k_check_positions<<<nb < 2048 ? nb : 2048, 256, 0, st>>>(pos, n, mesh / P->box, check);
+        return read_check();
+    };
+    const bool sure = !P->deterministic && dense(n, mesh);  // the keys' pass finds non-finite positions too
+    if (!sure)
+        if (int rc = check_all()) return rc;
+    if (sure || (!P->deterministic && found[1] >= kSameMin)) {
         const int order = P->pm_assign == 0 ? 2 : P->pm_assign;
         MortonSort &s = g_order;
         int rc = morton_order(s, n, P->box, pos, mass, cube_levels(mesh, order), check, st);
         if (rc == 0) {
-            rc = pm_run(pl, P, mesh, n,
-                        MortonOrder{ptr<double>(s.xs), ptr<double>(s.ys), ptr<double>(s.zs), ptr<double>(s.ms),
-                                    ptr<int>(s.idx[s.sorted])},
-                        ptr<uint64_t>(s.keys[s.sorted]), false, acc, st);
+            if (!sure || (rc = read_check()) == 0)
+                rc = pm_run(pl, P, mesh, n,
+                            MortonOrder{ptr<double>(s.xs), ptr<double>(s.ys), ptr<double>(s.zs), ptr<double>(s.ms),
+                                        ptr<int>(s.idx[s.sorted])},
+                            ptr<uint64_t>(s.keys[s.sorted]), false, acc, st);
             if (rc == 0) rc = hip_check(hipStreamSynchronize(st), "pm");  // the buffers are the next call's
             if ((size_t)n * 56 > kOrderKeep) release_order();
             return rc;
@@ -644,6 +651,8 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
         if (rc != FMM_ERR_NOMEM) return rc;
         clear_error();  // no room for the order: the particles as they come
         release_order();
+        if (sure)
+            if (int rc2 = check_all()) return rc2;
     }
     if (int rc = pm_run(pl, P, mesh, n, CallerOrder{pos, mass}, nullptr, false, acc, st)) return rc;
     return hip_check(hipStreamSynchronize(st), "pm");

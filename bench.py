@@ -414,6 +414,7 @@ def p2p_roofline(st, p2p_ms, wl, workload, pr, n, split, learned=None, fused=Fal
             same = all(rec.get(k) == v for k, v in (("n", n), ("p", pr["p"]), ("theta", wl["theta"]),
                                                     ("n_crit", wl["n_crit"]), ("learned", bool(learned)),
                                                     ("split", split), ("p2p_source_sha", p2p_source_sha()),
+                                                    ("evaluated_pairs", st["p2p_evaluated"]),  # of one sink tile
                                                     ("per_level", bool(per_level))))
             if same:
                 traffic = rec.get("bytes_per_launch")

@@ -180,9 +180,11 @@ __device__ __forceinline__ double pair_weight64(const P2PConst64 &k, double r2, 
 template <bool F64> struct P2PSink {
     Cell ca;
     double hA, cax, cay, caz;
-    // FP64 form: its coordinates count from the box's far face along an axis where the cutoff
-    // reaches past that face: an image x + box would be rounded to the last place of box, while
-    // x - box of the particles beside the face is exact
+    // FP64 form: along an axis where the leaf lies in the box's last quarter, its coordinates
+    // count from the box's far face.  An image x + box would be rounded to the last place of
+    // box, while x - box of a particle at box / 2 or above is exact; the particles below box / 2,
+    // for which it is not, are a quarter of the box away.  Wider leaves keep their coordinates:
+    // they hold particles nearer to such ones, or such ones themselves.
     double Ox = 0.0, Oy = 0.0, Oz = 0.0;
     // FP64 form: the boxes are FP32 and relative to their leaves, so their rounding grows with
     // the leaves' sides, however small the cutoff: the tests' margin does too
@@ -200,10 +202,10 @@ template <bool F64> struct P2PSink {
         ahi = a.bbox[2 * (size_t)A + 1];
         if constexpr (F64) {
             cutA = k.rc * 1.0001f + 1e-6f * (float)hA;
-            const double face = a.box - (double)k.rc - hA;
-            Ox = cax > face ? a.box : 0.0;
-            Oy = cay > face ? a.box : 0.0;
-            Oz = caz > face ? a.box : 0.0;
+            const int q = cell_level(ca) - 2;
+            Ox = q >= 0 && cell_ix(ca) >> q == 3 ? a.box : 0.0;
+            Oy = q >= 0 && ca.iy >> q == 3 ? a.box : 0.0;
+            Oz = q >= 0 && ca.iz >> q == 3 ? a.box : 0.0;
         }
     }
 

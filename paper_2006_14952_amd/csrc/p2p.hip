@@ -108,8 +108,13 @@ constexpr double kP2PFit64Cut = 5.0;
 struct P2PConst64 {
     double c[kP2PPoly64Max];  // S(t) / (8 r_s^3), coefficients of t^0 .. t^(ncoef-1)
     double two_over_rc2, rc2, rs, irc2, irc3;
-    float rc;   // for the box tests
-    int ncoef;  // 20 or 23; 0: no fit (erfc and exp)
+    // The form works in lengths times `scale`, the power of two that brings r_cut into
+    // [1/2, 1): exact, and no power of a length leaves the range of the type, however small
+    // or large the box (the gaps squared in FP32 by the box tests least of all).
+    double scale;
+    float scale32;  // the same for the FP32 boxes
+    float cut;      // r_cut and a margin for the box tests; infinite: no tests
+    int ncoef;      // 20 or 23; 0: no fit (erfc and exp)
 };
 // Sink particles per pass over a leaf's list unless fmm_params.p2p_chunk names 16 or 64: a
 // leaf of more is processed in Morton-ordered chunks of this many, each tested against the
@@ -179,7 +184,7 @@ __device__ __forceinline__ double pair_weight64(const P2PConst64 &k, double r2, 
 // One sink leaf: its cell and the box of the particles at hand (relative to the cell's centre).
 template <bool F64> struct P2PSink {
     Cell ca;
-    double hA, cax, cay, caz;
+    double box, hA, cax, cay, caz;  // FP64 form: times scale, as the rest
     // FP64 form: along an axis where the leaf lies in the box's last quarter, its coordinates
     // count from the box's far face.  An image x + box would be rounded to the last place of
     // box, while x - box of a particle at box / 2 or above is exact; the particles below box / 2,
@@ -194,34 +199,47 @@ template <bool F64> struct P2PSink {
     __device__ __forceinline__ P2PSink(const P2PArgs &a, const P2PLaw<F64> &k, int A)
     {
         ca = a.cells[A];
-        hA = ldexp(a.box, -cell_level(ca));
+        box = a.box;
+        if constexpr (F64) box *= k.scale;
+        hA = ldexp(box, -cell_level(ca));
         cax = (cell_ix(ca) + 0.5) * hA;
         cay = (ca.iy + 0.5) * hA;
         caz = (ca.iz + 0.5) * hA;
         alo = a.bbox[2 * (size_t)A];
         ahi = a.bbox[2 * (size_t)A + 1];
         if constexpr (F64) {
-            cutA = k.rc * 1.0001f + 1e-6f * (float)hA;
+            scale_box(k);
+            cutA = k.cut + 1e-6f * (float)hA;
             const int q = cell_level(ca) - 2;
-            Ox = q >= 0 && cell_ix(ca) >> q == 3 ? a.box : 0.0;
-            Oy = q >= 0 && ca.iy >> q == 3 ? a.box : 0.0;
-            Oz = q >= 0 && ca.iz >> q == 3 ? a.box : 0.0;
+            Ox = q >= 0 && cell_ix(ca) >> q == 3 ? box : 0.0;
+            Oy = q >= 0 && ca.iy >> q == 3 ? box : 0.0;
+            Oz = q >= 0 && ca.iz >> q == 3 ? box : 0.0;
         }
     }
 
+    __device__ __forceinline__ void scale_box(const P2PConst64 &k)
+    {
+        alo = make_float4(alo.x * k.scale32, alo.y * k.scale32, alo.z * k.scale32, 0.0f);
+        ahi = make_float4(ahi.x * k.scale32, ahi.y * k.scale32, ahi.z * k.scale32, 0.0f);
+    }
+
     // the box of the ns particles from `first` (one chunk of the leaf)
-    __device__ __forceinline__ void chunk_box(const P2PArgs &a, int first, int ns, int lane)
+    __device__ __forceinline__ void chunk_box(const P2PArgs &a, const P2PLaw<F64> &k, int first, int ns, int lane)
     {
         const float4 me = a.rel[first + (lane < ns ? lane : 0)];
         alo = make_float4(wave_minf(me.x), wave_minf(me.y), wave_minf(me.z), 0.0f);
         ahi = make_float4(wave_maxf(me.x), wave_maxf(me.y), wave_maxf(me.z), 0.0f);
+        if constexpr (F64) scale_box(k);
     }
 
     // sink particle i in the pair loop's coordinates
-    template <class R> __device__ __forceinline__ void load(const P2PArgs &a, int i, R &xi, R &yi, R &zi) const
+    template <class R>
+    __device__ __forceinline__ void load(const P2PArgs &a, const P2PLaw<F64> &k, int i, R &xi, R &yi, R &zi) const
     {
         if constexpr (F64) {
-            xi = a.xs[i] - Ox; yi = a.ys[i] - Oy; zi = a.zs[i] - Oz;
+            xi = fma(a.xs[i], k.scale, -Ox);
+            yi = fma(a.ys[i], k.scale, -Oy);
+            zi = fma(a.zs[i], k.scale, -Oz);
         } else {
             float4 me = a.rel[i];
             xi = me.x; yi = me.y; zi = me.z;
@@ -241,17 +259,21 @@ template <bool F64> struct P2PSink {
         Cell cb = a.cells[it >> 5];
         cntj = listed = cb.end - cb.beg;
         jbeg = cb.beg;
-        double shx = (double)(s / 9 - 1) * a.box, shy = (double)((s / 3) % 3 - 1) * a.box,
-               shz = (double)(s % 3 - 1) * a.box;
+        double shx = (double)(s / 9 - 1) * box, shy = (double)((s / 3) % 3 - 1) * box, shz = (double)(s % 3 - 1) * box;
         // exact in FP64: dyadic centres and integer image shifts
-        double hB = ldexp(a.box, -cell_level(cb));
+        double hB = ldexp(box, -cell_level(cb));
         const float ox = (float)((cell_ix(cb) + 0.5) * hB + shx - cax);
         const float oy = (float)((cb.iy + 0.5) * hB + shy - cay);
         const float oz = (float)((cb.iz + 0.5) * hB + shz - caz);
         if constexpr (F64) eoff[lane] = make_double4(shx - Ox, shy - Oy, shz - Oz, 0.0);
         else eoff[lane] = make_float4(ox, oy, oz, 0.0f);
         // gap between the two boxes; the margin covers FP32 rounding many times over
-        const float4 blo = a.bbox[2 * (size_t)(it >> 5)], bhi = a.bbox[2 * (size_t)(it >> 5) + 1];
+        float4 blo = a.bbox[2 * (size_t)(it >> 5)], bhi = a.bbox[2 * (size_t)(it >> 5) + 1];
+        if constexpr (F64) {
+            const float c = k.scale32;
+            blo.x *= c; blo.y *= c; blo.z *= c;
+            bhi.x *= c; bhi.y *= c; bhi.z *= c;
+        }
         const float gx = fmaxf(0.0f, fmaxf(alo.x - (bhi.x + ox), (blo.x + ox) - ahi.x));
         const float gy = fmaxf(0.0f, fmaxf(alo.y - (bhi.y + oy), (blo.y + oy) - ahi.y));
         const float gz = fmaxf(0.0f, fmaxf(alo.z - (bhi.z + oz), (blo.z + oz) - ahi.z));
@@ -330,17 +352,20 @@ template <bool F64> struct P2PFetch {
         for (int u = 0; u < kPer; ++u) {
             const V4 eo = eoff[ev[u]];
             V4 sv;
-            sv.x = rv[u].x + eo.x;
-            sv.y = rv[u].y + eo.y;
-            sv.z = rv[u].z + eo.z;
             sv.w = rv[u].w;
             float px, py, pz, far2;  // the source relative to the sink leaf's centre
             if constexpr (F64) {
+                sv.x = fma(rv[u].x, k.scale, eo.x);
+                sv.y = fma(rv[u].y, k.scale, eo.y);
+                sv.z = fma(rv[u].z, k.scale, eo.z);
                 px = (float)(sv.x - (sk.cax - sk.Ox));
                 py = (float)(sv.y - (sk.cay - sk.Oy));
                 pz = (float)(sv.z - (sk.caz - sk.Oz));
                 far2 = sk.cutA * sk.cutA;
             } else {
+                sv.x = rv[u].x + eo.x;
+                sv.y = rv[u].y + eo.y;
+                sv.z = rv[u].z + eo.z;
                 px = sv.x; py = sv.y; pz = sv.z;
                 far2 = k.rc2 * 1.0001f;
             }
@@ -425,7 +450,9 @@ __device__ __forceinline__ void p2p_sum64(const P2PConst64 &k, const double4 *sr
 }
 
 // The copies of each sink particle (red[copy ns + particle]) summed and written.
-__device__ __forceinline__ void p2p_write(const P2PArgs &a, const double (*red)[3], int first, int ns, int G, int lane)
+template <bool F64>
+__device__ __forceinline__ void p2p_write(const P2PArgs &a, const P2PLaw<F64> &k, const double (*red)[3], int first,
+                                          int ns, int G, int lane)
 {
     if (lane >= ns) return;
     double tx = 0, ty = 0, tz = 0;
@@ -433,6 +460,11 @@ __device__ __forceinline__ void p2p_write(const P2PArgs &a, const double (*red)[
         tx += red[q * ns + lane][0];
         ty += red[q * ns + lane][1];
         tz += red[q * ns + lane][2];
+    }
+    if constexpr (F64) {  // masses over lengths squared
+        tx = tx * k.scale * k.scale;
+        ty = ty * k.scale * k.scale;
+        tz = tz * k.scale * k.scale;
     }
     const int o = first + lane;
     a.nearf[o] = tx;
@@ -475,10 +507,10 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
     for (int ib = 0; ib < nA; ib += CHUNK) {
         const int ns = min(CHUNK, nA - ib);
         const int G = 64 / ns, g = lane / ns, si = lane - g * ns;
-        if (nA > CHUNK) sk.chunk_box(a, sk.ca.beg + ib, ns, lane);
+        if (nA > CHUNK) sk.chunk_box(a, k, sk.ca.beg + ib, ns, lane);
         const bool valid = g < G;
         R xi, yi, zi;
-        sk.load(a, sk.ca.beg + ib + (valid ? si : 0), xi, yi, zi);
+        sk.load(a, k, sk.ca.beg + ib + (valid ? si : 0), xi, yi, zi);
         double ax = 0, ay = 0, az = 0;              // FP64 form
         float sx = 0, sy = 0, sz = 0, cx = 0, cy = 0, cz = 0;  // FP32 form (Kahan)
         // the list is read a chunk ahead: the next chunk's items are on their way while the
@@ -537,7 +569,7 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
         red[lane][1] = ay;
         red[lane][2] = az;
         wave_sync();
-        p2p_write(a, red, sk.ca.beg + ib, ns, G, lane);
+        p2p_write<F64>(a, k, red, sk.ca.beg + ib, ns, G, lane);
         wave_sync();
     }
     if (lane == 0) p2p_count(a, li, npairs, nevald);
@@ -573,10 +605,10 @@ __device__ __forceinline__ void p2p_leaf_wide(const P2PArgs &a, const P2PLaw<F64
     for (int ib = 0; ib < nA; ib += CHUNK) {
         const int ns = min(CHUNK, nA - ib);
         const int G = 64 / ns, g = lane / ns, si = lane - g * ns;
-        if (nA > CHUNK) sk.chunk_box(a, sk.ca.beg + ib, ns, lane);
+        if (nA > CHUNK) sk.chunk_box(a, k, sk.ca.beg + ib, ns, lane);
         const bool valid = g < G;
         R xi, yi, zi;
-        sk.load(a, sk.ca.beg + ib + (valid ? si : 0), xi, yi, zi);
+        sk.load(a, k, sk.ca.beg + ib + (valid ? si : 0), xi, yi, zi);
         double ax = 0, ay = 0, az = 0;
         float sx = 0, sy = 0, sz = 0, cx = 0, cy = 0, cz = 0;  // FP32 form: wave 0
         int cur = a.head[A];
@@ -686,7 +718,7 @@ __device__ __forceinline__ void p2p_leaf_wide(const P2PArgs &a, const P2PLaw<F64
                 }
                 wave_sync();
             }
-            p2p_write(a, red, sk.ca.beg + ib, ns, G, lane);
+            p2p_write<F64>(a, k, red, sk.ca.beg + ib, ns, G, lane);
         }
         __syncthreads();
     }
@@ -920,14 +952,21 @@ static void p2p_setup64(const fmm_params *P, P2PConst64 &k)
     static double cached_vcut = -1.0, cached[kP2PPoly64Max];
     static int cached_m = 0;
     k = P2PConst64{};
-    k.rs = P->r_s;
-    k.rc2 = P->r_cut * P->r_cut;
-    k.rc = (float)P->r_cut;
+    int e;
+    const double rc = frexp(P->r_cut, &e);
+    k.scale = ldexp(1.0, -e);
+    k.rs = P->r_s * k.scale;
+    k.rc2 = rc * rc;
     k.two_over_rc2 = 2.0 / k.rc2;
     k.irc2 = 1.0 / k.rc2;
-    k.irc3 = k.irc2 / P->r_cut;
+    k.irc3 = k.irc2 / rc;
+    // the boxes are FP32 in the caller's units: tests only where these hold the boxes of leaves
+    // down to 2^-21 of the box to P2PSink's margin
+    const bool tests = P->box >= 0x1p-80 && P->box <= 0x1p100 && e >= -120 && e <= 120;
+    k.scale32 = tests ? (float)k.scale : 0.0f;
+    k.cut = tests ? (float)rc * 1.0001f : INFINITY;
     if (P->split == 1 || P->r_cut > kP2PFit64Cut * P->r_s) return;
-    const double vcut = k.rc2 / (4.0 * P->r_s * P->r_s);
+    const double vcut = k.rc2 / (4.0 * k.rs * k.rs);
     std::lock_guard<std::mutex> lk(mu);
     if (vcut != cached_vcut) {
         cached_m = 0;
@@ -936,7 +975,7 @@ static void p2p_setup64(const fmm_params *P, P2PConst64 &k)
         cached_vcut = vcut;
     }
     k.ncoef = cached_m;
-    const double inv8rs3 = 1.0 / (8.0 * P->r_s * P->r_s * P->r_s);
+    const double inv8rs3 = 1.0 / (8.0 * k.rs * k.rs * k.rs);
     for (int j = 0; j < cached_m; ++j) k.c[j] = cached[j] * inv8rs3;
 }
 

@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "expand_impl.h"
+#include "p2p_law.h"
 
 namespace hfmm {
 
@@ -94,28 +95,6 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v)
 constexpr int kStage = 256;  // FP32 form; the FP64 form's 32-byte records are staged 128 at a time
 template <bool F64> constexpr int stage_slots() { return F64 ? 128 : kStage; }
 
-// FP64 force-law constants: f_(1) = -1/r^3 + S(t)/(8 r_s^3) as in the FP32 form, S fitted to
-// FP64 rounding.  S's terms are summed from the smallest, so the sum is good to a few units
-// of 1e-16 of 1/r^3, which is what the particles' forces are rounded to by their nearest
-// pairs anyway.  Accelerations of 4096 particles against extended precision (median, 99th
-// percentile of the relative error, means of four boxes): uniform 2.3e-16 and 1.1e-15, clustered
-// 2.0e-16 and 1.5e-15; the erfc/exp form on unshifted coordinates 2.8e-16 and 3.8e-15,
-// 2.1e-16 and 2.4e-15.
-// Fits exist up to kP2PFit64Cut: there r^3 f_(1) has fallen to 1/170 at the cutoff; past it
-// the cancellation would show in the forces of isolated particles, and erfc/exp are used.
-constexpr int kP2PPoly64Max = 23;
-constexpr double kP2PFit64Cut = 5.0;
-struct P2PConst64 {
-    double c[kP2PPoly64Max];  // S(t) / (8 r_s^3), coefficients of t^0 .. t^(ncoef-1)
-    double two_over_rc2, rc2, rs, irc2, irc3;
-    // The form works in lengths times `scale`, the power of two that brings r_cut into
-    // [1/2, 1): exact, and no power of a length leaves the range of the type, however small
-    // or large the box (the gaps squared in FP32 by the box tests least of all).
-    double scale;
-    float scale32;  // the same for the FP32 boxes
-    float cut;      // r_cut and a margin for the box tests; infinite: no tests
-    int ncoef;      // 20 or 23; 0: no fit (erfc and exp)
-};
 // Sink particles per pass over a leaf's list unless fmm_params.p2p_chunk names 16 or 64: a
 // leaf of more is processed in Morton-ordered chunks of this many, each tested against the
 // box of its own particles.
@@ -898,85 +877,14 @@ int p2p_setup(const fmm_params *P, P2PConst &k)
     return 0;
 }
 
-
-
-// S(v) in extended precision: sum (-1)^k v^k / (k! (2k+3)), whose terms stay below e^v.
-static long double S_of_v_ext(long double v)
-{
-    long double s = 0, term = 1;
-    for (int k = 0; k < 80; ++k) {
-        s += term / (2 * k + 3);
-        term *= -v / (k + 1);
-    }
-    return 4.0L / sqrtl(3.14159265358979323846264338327950288L) * s;
-}
-
-// Interpolation of S at the m Chebyshev points through its Chebyshev series, rewritten in
-// powers of t, in extended precision; returns the largest error of the rounded coefficients
-// in r^3 f_(1) (as fit_error).
-static double fit_S64(double vcut, int m, double *coef)
-{
-    const long double pi = 3.14159265358979323846264338327950288L;
-    long double f[kP2PPoly64Max], mono[kP2PPoly64Max] = {0};
-    for (int k = 0; k < m; ++k) f[k] = S_of_v_ext((cosl(pi * (k + 0.5L) / m) + 1.0L) * 0.5L * vcut);
-    long double t0[kP2PPoly64Max] = {1}, t1[kP2PPoly64Max] = {0, 1}, t2[kP2PPoly64Max];
-    for (int j = 0; j < m; ++j) {
-        long double cj = 0;
-        for (int k = 0; k < m; ++k) cj += f[k] * cosl(pi * j * (k + 0.5L) / m);
-        cj *= (j ? 2.0L : 1.0L) / m;
-        for (int q = 0; q < m; ++q) mono[q] += cj * t0[q];
-        for (int q = 0; q < m; ++q) t2[q] = (q ? 2.0L * t1[q - 1] : 0.0L) - t0[q];  // T_(j+2)
-        for (int q = 0; q < m; ++q) {
-            t0[q] = t1[q];
-            t1[q] = t2[q];
-        }
-    }
-    for (int j = 0; j < m; ++j) coef[j] = (double)mono[j];
-    double worst = 0.0;
-    for (int i = 0; i <= 400; ++i) {
-        const long double t = -1.0L + i / 200.0L, v = (t + 1.0L) * 0.5L * vcut;
-        long double S = coef[m - 1];
-        for (int j = m - 2; j >= 0; --j) S = S * t + coef[j];
-        worst = std::max(worst, (double)(fabsl(S - S_of_v_ext(v)) * v * sqrtl(v)));
-    }
-    return worst;
-}
-
-// FP64 constants: the shorter fit whose error stays within FP64 rounding (20 coefficients
-// serve r_cut up to about 4.8 r_s, 23 up to 5 r_s), else none.  The last fit is kept, by its
-// vcut alone.
 static void p2p_setup64(const fmm_params *P, P2PConst64 &k)
 {
-    constexpr double kTol = 2.0e-16;
-    static std::mutex mu;
-    static double cached_vcut = -1.0, cached[kP2PPoly64Max];
-    static int cached_m = 0;
-    k = P2PConst64{};
-    int e;
-    const double rc = frexp(P->r_cut, &e);
-    k.scale = ldexp(1.0, -e);
-    k.rs = P->r_s * k.scale;
-    k.rc2 = rc * rc;
-    k.two_over_rc2 = 2.0 / k.rc2;
-    k.irc2 = 1.0 / k.rc2;
-    k.irc3 = k.irc2 / rc;
+    law64_setup(P->r_s, P->r_cut, P->split, k);
     // the boxes are FP32 in the caller's units: tests only where these hold the boxes of leaves
     // down to 2^-21 of the box to P2PSink's margin
-    const bool tests = P->box >= 0x1p-80 && P->box <= 0x1p100 && e >= -120 && e <= 120;
+    const bool tests = P->box >= 0x1p-80 && P->box <= 0x1p100 && k.scale >= 0x1p-120 && k.scale <= 0x1p120;
     k.scale32 = tests ? (float)k.scale : 0.0f;
-    k.cut = tests ? (float)rc * 1.0001f : INFINITY;
-    if (P->split == 1 || P->r_cut > kP2PFit64Cut * P->r_s) return;
-    const double vcut = k.rc2 / (4.0 * k.rs * k.rs);
-    std::lock_guard<std::mutex> lk(mu);
-    if (vcut != cached_vcut) {
-        cached_m = 0;
-        for (int m : {20, kP2PPoly64Max})
-            if (!cached_m && fit_S64(vcut, m, cached) <= kTol) cached_m = m;
-        cached_vcut = vcut;
-    }
-    k.ncoef = cached_m;
-    const double inv8rs3 = 1.0 / (8.0 * k.rs * k.rs * k.rs);
-    for (int j = 0; j < cached_m; ++j) k.c[j] = cached[j] * inv8rs3;
+    k.cut = tests ? (float)(P->r_cut * k.scale) * 1.0001f : INFINITY;
 }
 
 // The leaves' bounding boxes (they depend on the tree only).

@@ -12,9 +12,9 @@
 // 7.83 ms at n_crit 48, 16.7M box 56.7 -> 51.6 ms and 134M box 480 -> 430 ms at n_crit 96
 // (chunks of 16: 1% slower).
 //
-// FP64 form: absolute FP64 positions, and for r_cut up to 5 r_s the same split of the force
-// law, f_(1) = -1/r^3 + S(t)/(8 r_s^3), with S of degree 19 or 22 fitted to FP64 rounding
-// (beyond that erfc and exp of the device math library); sums in FP64.
+// FP64 form: absolute FP64 positions, and for r_cut up to 5 r_s a polynomial for the force law
+// too, written about the cutoff so that nothing cancels there (p2p_law.h; beyond that erfc and
+// exp of the device math library); sums in FP64.
 // FP32 form: FP32 coordinates relative to each particle's leaf centre, the exact
 // centre offset c_B + s box - c_A added when staging, and
 //   f_(1)(r) = -1/r^3 + S(t)/(8 r_s^3),  t = 2 r^2/r_cut^2 - 1,
@@ -114,9 +114,6 @@ __device__ __forceinline__ float wave_maxf(float v)
     return v;
 }
 
-// POLY (FP32 form, polynomial split): f_(1) = -1/r^3 + 5/(2 r_c^3) - 3 r^2/(2 r_c^5) evaluated
-// as -(1-x)^2 (1 + 2x + 3x^2 + 3x^3/2) / r^3, x = r / r_c: the three terms cancel near r_cut
-// in FP32, the factored form does not.
 // Shared memory of one sink leaf's P2P (one 64-lane wave).
 template <bool F64> struct P2PShared {
     using V4 = typename std::conditional<F64, double4, float4>::type;
@@ -127,38 +124,6 @@ template <bool F64> struct P2PShared {
 };
 
 template <bool F64> using P2PLaw = typename std::conditional<F64, P2PConst64, P2PConst>::type;
-
-// One pair of the FP64 form: the weight m f_(1)(r), zero outside 0 < r^2 < r_cut^2.
-// 1/r^3 from the hardware's estimate y of 1/r (about 23 bits), cut to 26 bits so that y^2 and
-// with it the residual e = 1 - r^2 y^2 are exact: y^3 and one second-order correction then
-// carry three roundings, no more than a square root, a product and a division.  The self
-// pair's NaN is dropped by the select.
-template <bool POLY, int NPC>
-__device__ __forceinline__ double pair_weight64(const P2PConst64 &k, double r2, double m)
-{
-    const bool in = r2 > 0.0 && r2 < k.rc2;
-    if constexpr (!POLY && NPC == 0) {
-        const double rr2 = in ? r2 : 1.0, r = sqrt(rr2), u = r * (0.5 / k.rs);
-        const double h = erfc(u) + r * (1.0 / (k.rs * 1.7724538509055160273)) * exp(-u * u);
-        return in ? -m * h / (rr2 * r) : 0.0;
-    } else {
-        double y = __builtin_amdgcn_rsq(r2);
-        y = __longlong_as_double(__double_as_longlong(y) & ~0x7ffffffll);
-        const double y2 = y * y, y3 = y2 * y, e = fma(-r2, y2, 1.0);
-        const double q = fma(1.875, e, 1.5) * e;  // 1/r^3 = y^3 (1 - e)^(-3/2)
-        double S;
-        if constexpr (POLY) {  // -1/r^3 + 5/(2 r_c^3) - 3 r^2/(2 r_c^5)
-            S = k.irc3 * fma(-1.5 * k.irc2, r2, 2.5);
-        } else {
-            const double t = fma(r2, k.two_over_rc2, -1.0);
-            S = k.c[NPC - 1];
-#pragma unroll
-            for (int c = NPC - 2; c >= 0; --c) S = fma(S, t, k.c[c]);
-        }
-        const double f1 = fma(-y3, q, S - y3);
-        return in ? m * f1 : 0.0;
-    }
-}
 
 // One sink leaf: its cell and the box of the particles at hand (relative to the cell's centre).
 template <bool F64> struct P2PSink {
@@ -361,6 +326,9 @@ template <bool F64> struct P2PFetch {
 };
 
 // FP32 form: the force of the staged sources g, g + G, ... on one sink particle.
+// POLY (polynomial split): f_(1) = -1/r^3 + 5/(2 r_c^3) - 3 r^2/(2 r_c^5) evaluated as
+// -(1-x)^2 (1 + 2x + 3x^2 + 3x^3/2) / r^3, x = r / r_c: the three terms cancel near r_cut in
+// FP32, the factored form does not.
 template <bool POLY, int NPC>
 __device__ __forceinline__ void p2p_sum32(const P2PConst &k, const float4 *src, int nst, int g, int G, float xi, float yi,
                                           float zi, float &px, float &py, float &pz)
@@ -408,13 +376,14 @@ __device__ __forceinline__ void p2p_sum32(const P2PConst &k, const float4 *src, 
 }
 
 // FP64 form: the same, added to ax, ay, az.
-template <bool POLY, int NPC>
+template <int NPC>
 __device__ __forceinline__ void p2p_sum64(const P2PConst64 &k, const double4 *src, int nst, int g, int G, double xi,
                                           double yi, double zi, double &ax, double &ay, double &az)
 {
     auto pair = [&](const double4 s) __attribute__((always_inline)) {
         const double dx = xi - s.x, dy = yi - s.y, dz = zi - s.z;
-        const double w = pair_weight64<POLY, NPC>(k, dx * dx + dy * dy + dz * dz, s.w);
+        const double r2 = dx * dx + dy * dy + dz * dz;
+        const double w = law64_weight<NPC>(k, r2, s.w, __builtin_amdgcn_rsq(r2));
         ax += w * dx;
         ay += w * dy;
         az += w * dz;
@@ -526,7 +495,7 @@ __device__ __forceinline__ void p2p_leaf(const P2PArgs &a, const P2PLaw<F64> &k,
                 wave_sync();
                 if (valid) {
                     if constexpr (F64) {
-                        p2p_sum64<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, ax, ay, az);
+                        p2p_sum64<NPC>(k, sh.src, nst, g, G, xi, yi, zi, ax, ay, az);
                     } else {
                         float px, py, pz;
                         p2p_sum32<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, px, py, pz);
@@ -659,7 +628,7 @@ __device__ __forceinline__ void p2p_leaf_wide(const P2PArgs &a, const P2PLaw<F64
                     nevald += (unsigned long long)ns * (unsigned)nst;
                     wave_sync();
                     if (valid) {
-                        if constexpr (F64) p2p_sum64<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, ax, ay, az);
+                        if constexpr (F64) p2p_sum64<NPC>(k, sh.src, nst, g, G, xi, yi, zi, ax, ay, az);
                         else p2p_sum32<POLY, NPC>(k, sh.src, nst, g, G, xi, yi, zi, px, py, pz);
                     }
                     wave_sync();
@@ -709,10 +678,11 @@ __device__ __forceinline__ void p2p_leaf_wide(const P2PArgs &a, const P2PLaw<F64
 // (a load under its own branch waited for the one before it, and the sink's own load for all
 // of them: 300,007 particles, polynomial split, step 3.50 -> 3.33 ms; 2M 8.13 -> 8.01 ms; 64-box
 // forest 11.77 -> 11.46 ms).
-// FP64 form: bound by FP64 issue, 43 operations a pair with the degree-19 law against well over
-// 200 of erfc, exp, the square root and the division, on the pairs the box tests leave (62% of
-// the listed ones on the 2M box) at four waves per SIMD instead of three: uniform 32^3 step
-// 1.21 -> 0.83 ms, 262,144 clustered step 9.0 -> 4.5 ms.
+// FP64 form: bound by FP64 issue, 51 vector operations a pair with 19 coefficients (43 of them
+// FP64; 48 with the cancelling form of the law: 262,144 clustered step 1.96 against 2.00 ms)
+// against well over 200 of erfc, exp, the square root and the division, on the pairs the box
+// tests leave (62% of the listed ones on the 2M box) at four waves per SIMD instead of three:
+// uniform 32^3 step 1.21 -> 0.83 ms, 262,144 clustered step 9.0 -> 4.5 ms with one wave per leaf.
 template <bool F64, bool POLY, int NPC, int CHUNK>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(F64 ? (NPC ? 4 : 2) : 5))) void k_p2p(P2PArgs a,
                                                                                                    P2PLaw<F64> k)
@@ -1023,9 +993,9 @@ static int launch_p2p(const fmm_params *P, const P2PArgs &a, int count, hipStrea
     if (!P->precision) {
         P2PConst64 k;
         p2p_setup64(P, k);
-        if (P->split == 1) launch_one<true, true, 1, CHUNK>(k, a, count, st);
-        else if (k.ncoef == 20) launch_one<true, false, 20, CHUNK>(k, a, count, st);
-        else if (k.ncoef == 23) launch_one<true, false, 23, CHUNK>(k, a, count, st);
+        if (k.ncoef == 1) launch_one<true, false, 1, CHUNK>(k, a, count, st);
+        else if (k.ncoef == 19) launch_one<true, false, 19, CHUNK>(k, a, count, st);
+        else if (k.ncoef == 22) launch_one<true, false, 22, CHUNK>(k, a, count, st);
         else launch_one<true, false, 0, CHUNK>(k, a, count, st);
         return hip_check(hipGetLastError(), "p2p");
     }

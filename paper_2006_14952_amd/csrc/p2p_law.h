@@ -1,70 +1,114 @@
-// FP64 force law of P2P: its constants, computed on the host.  Plain C++, so that a host
-// program can measure it.
+// FP64 force law of P2P: its constants, computed on the host, and the weight of one pair.
+// Also compiles as plain C++, so that a host program can measure both.
 #pragma once
 #include <math.h>
+#include <string.h>
 
 #include <mutex>
 
+#ifdef __HIPCC__
+#define HFMM_HD __host__ __device__ __forceinline__
+#else
+#define HFMM_HD inline
+#endif
+
 namespace hfmm {
 
-// f_(1) = -1/r^3 + S(t)/(8 r_s^3) as in the FP32 form, S fitted to FP64 rounding.  S's terms
-// are summed from the smallest, so the sum is good to a few units of 1e-16 of 1/r^3, which is
-// what the particles' forces are rounded to by their nearest pairs anyway.  Accelerations of
-// 4096 particles against extended precision (median, 99th percentile of the relative error,
-// means of four boxes): uniform 2.3e-16 and 1.1e-15, clustered 2.0e-16 and 1.5e-15; the erfc/exp
-// form on unshifted coordinates 2.8e-16 and 3.8e-15, 2.1e-16 and 2.4e-15.
-constexpr int kP2PPoly64Max = 23;
+// f_(1) = S(r^2) - 1/r^3 up to r_cut.  S, a smooth function of r^2, is written about the
+// cutoff, with d = r_cut^2 - r^2 >= 0:
+//   S = S_0 + d T(d),  T = sum c_k d^k, k < ncoef (19 or 22; the polynomial split: 1)
+// Near the cutoff S and 1/r^3 agree to one part in 1/h, h = r^3 |f_(1)| (57 at 4.5 r_s, 170 at
+// 5 r_s).  So S_0 is held to twice the precision, 1/r^3 is formed as y^3 plus its rounding
+// (law64_weight), S_0 - 1/r^3 is then exact within a few roundings of f_(1), and the rest, d T,
+// vanishes with d.  The terms that matter in T are positive, as all of S's Taylor series is.
+// Largest relative error of a pair's weight, any separation, against 80-bit arithmetic: 1.3e-15
+// at r_cut = 4.5 r_s, 2.3e-15 at 5 r_s; by erfc and exp 2.0e-15 and 2.4e-15; with S - 1/r^3
+// formed from a polynomial over the whole range, 3 operations a pair less, 2.3e-14 and 1.9e-13.
+constexpr int kP2PPoly64Max = 22;
 struct P2PConst64 {
-    double c[kP2PPoly64Max];  // S(t) / (8 r_s^3), coefficients of t^0 .. t^(ncoef-1)
-    double two_over_rc2, rc2, rs, irc2, irc3;
+    double c[kP2PPoly64Max];
+    double s0, s0_lo;  // S_0 and what FP64 leaves of it
+    double rc2, rs;
     // The form works in lengths times `scale`, the power of two that brings r_cut into
     // [1/2, 1): exact, and no power of a length leaves the range of the type, however small
     // or large the box (the gaps squared in FP32 by the box tests least of all).
     double scale;
     float scale32;  // the same for the FP32 boxes
     float cut;      // r_cut and a margin for the box tests; infinite: no tests
-    int ncoef;      // coefficients of the fit; 0: no fit (erfc and exp)
+    int ncoef;      // coefficients of T; 0: erfc and exp
 };
 
-// S(v) in extended precision: sum (-1)^k v^k / (k! (2k+3)), whose terms stay below e^v.
-inline long double S_of_v_ext(long double v)
+// One pair of the FP64 form: the weight m f_(1)(r), zero outside 0 < r^2 < r_cut^2.  y: an
+// estimate of 1/r to about 23 bits.  It is cut to 26 bits, so that y^2, the low part of y^3 and
+// the residual e = 1 - r^2 y^2 are exact to far below FP64's last place, and
+// 1/r^3 = y^3 (1 - e)^(-3/2).  The self pair's NaN is dropped by the select.
+template <int NPC> HFMM_HD double law64_weight(const P2PConst64 &k, double r2, double m, double y)
 {
-    long double s = 0, term = 1;
-    for (int k = 0; k < 80; ++k) {
-        s += term / (2 * k + 3);
-        term *= -v / (k + 1);
+    const bool in = r2 > 0.0 && r2 < k.rc2;
+    if constexpr (NPC == 0) {
+        const double rr2 = in ? r2 : 1.0, r = sqrt(rr2), u = r * (0.5 / k.rs);
+        const double h = erfc(u) + r * (1.0 / (k.rs * 1.7724538509055160273)) * exp(-u * u);
+        return in ? -m * h / (rr2 * r) : 0.0;
+    } else {
+        long long b;
+        memcpy(&b, &y, 8);
+        b &= ~0x7ffffffll;
+        memcpy(&y, &b, 8);
+        // y3 by fma: a product would be contracted into s0 - y3, which needs the rounded y3
+        const double y2 = y * y, y3 = fma(y2, y, 0.0), lo = fma(y2, y, -y3), e = fma(-r2, y2, 1.0);
+        const double q = fma(1.875, e, 1.5) * e;
+        const double d = k.rc2 - r2;
+        double T = k.c[NPC - 1];
+#pragma unroll
+        for (int c = NPC - 2; c >= 0; --c) T = fma(T, d, k.c[c]);
+        const double f1 = fma(d, T, k.s0 - y3) + (fma(-y3, q, k.s0_lo) - lo);
+        return in ? m * f1 : 0.0;
     }
-    return 4.0L / sqrtl(3.14159265358979323846264338327950288L) * s;
 }
 
-// Interpolation of S at the m Chebyshev points through its Chebyshev series, rewritten in
-// powers of t, in extended precision.
-inline void fit_S64(double vcut, int m, double *coef)
+// Coefficients by r_cut / r_s alone: the error left by the shortening of T, before its
+// coefficients are rounded, stays below one rounding of f_(1) itself up to 4.558 (19) and
+// 5.366 (22).  The lines lie between the ratios in use, whose last bits vary with r_s.  No fit
+// beyond the second: S - S_0 then outweighs f_(1) so far that its roundings pass those of
+// erfc and exp.
+inline int law64_ncoef(double ratio) { return ratio <= 4.55 ? 19 : ratio <= 5.05 ? 22 : 0; }
+
+// S = 4/sqrt(pi) int_0^1 y^2 exp(-v y^2) dy, v = r^2 / (4 r_s^2), about v0 in extended
+// precision: S = s0 + x sum T[k] x^k, x = 1 - v / v0 in [0, 1].  The Taylor coefficients
+// v0^k / k! 4/sqrt(pi) I_k, I_k = int_0^1 y^(2k+2) exp(-v0 y^2) dy, follow by downward
+// recurrence (all terms positive); their series is then shortened to m terms by taking off
+// multiples of the shifted Chebyshev polynomials, highest first.
+inline void law64_series(long double v0, int m, long double &s0, long double *T)
 {
-    const long double pi = 3.14159265358979323846264338327950288L;
-    long double f[kP2PPoly64Max], mono[kP2PPoly64Max] = {0};
-    for (int k = 0; k < m; ++k) f[k] = S_of_v_ext((cosl(pi * (k + 0.5L) / m) + 1.0L) * 0.5L * vcut);
-    long double t0[kP2PPoly64Max] = {1}, t1[kP2PPoly64Max] = {0, 1}, t2[kP2PPoly64Max];
-    for (int j = 0; j < m; ++j) {
-        long double cj = 0;
-        for (int k = 0; k < m; ++k) cj += f[k] * cosl(pi * j * (k + 0.5L) / m);
-        cj *= (j ? 2.0L : 1.0L) / m;
-        for (int q = 0; q < m; ++q) mono[q] += cj * t0[q];
-        for (int q = 0; q < m; ++q) t2[q] = (q ? 2.0L * t1[q - 1] : 0.0L) - t0[q];  // T_(j+2)
-        for (int q = 0; q < m; ++q) {
-            t0[q] = t1[q];
-            t1[q] = t2[q];
+    constexpr int N = 48;  // v0 <= 6.4: the first term left out is below 1e-22
+    struct Cheb {
+        long double e[N][N];
+        Cheb() : e{}
+        {
+            e[0][0] = 1;
+            e[1][0] = -1;
+            e[1][1] = 2;
+            for (int j = 2; j < N; ++j)
+                for (int q = 0; q <= j; ++q) e[j][q] = 2 * ((q ? 2 * e[j - 1][q - 1] : 0) - e[j - 1][q]) - e[j - 2][q];
         }
+    };
+    static const Cheb cheb;
+    long double I[N + 2], t[N];
+    const long double ev = expl(-v0);
+    I[N + 1] = ev / (2 * N + 5);
+    for (int k = N; k >= 0; --k) I[k] = (ev + 2 * v0 * I[k + 1]) / (2 * k + 3);
+    long double p = 2.25675833419102514779231781243L;  // 4 / sqrt(pi)
+    s0 = p * I[0];
+    for (int k = 0; k < N; ++k) {
+        p *= v0 / (k + 1);
+        t[k] = p * I[k + 1];
     }
-    for (int j = 0; j < m; ++j) coef[j] = (double)mono[j];
+    for (int j = N - 1; j >= m; --j) {
+        const long double a = t[j] / cheb.e[j][j];
+        for (int q = 0; q <= j; ++q) t[q] -= a * cheb.e[j][q];
+    }
+    for (int k = 0; k < m; ++k) T[k] = t[k];
 }
-
-// Coefficients by r_cut / r_s alone, from the fit's error before its coefficients are rounded
-// (in r^3 f_(1); 20 of them reach 2e-16 at 4.96, 23 past 5.5).  The lines lie between the
-// ratios in use, whose last bits vary with r_s.  No fit beyond the second: there r^3 f_(1) has
-// fallen to 1/170 at the cutoff, and the cancellation would show in the forces of isolated
-// particles.
-inline int law64_ncoef(double ratio) { return ratio <= 4.85 ? 20 : ratio <= 5.05 ? 23 : 0; }
 
 inline void law64_setup(double r_s, double r_cut, int split, P2PConst64 &k)
 {
@@ -74,24 +118,35 @@ inline void law64_setup(double r_s, double r_cut, int split, P2PConst64 &k)
     k.scale = ldexp(1.0, -e);
     k.rs = r_s * k.scale;
     k.rc2 = rc * rc;
-    k.two_over_rc2 = 2.0 / k.rc2;
-    k.irc2 = 1.0 / k.rc2;
-    k.irc3 = k.irc2 / rc;
-    if (split == 1) return;
+    const long double rc2 = k.rc2;
+    if (split == 1) {  // S = 5/(2 r_c^3) - 3 r^2/(2 r_c^5); f_(1) vanishes with d^2, so S_0 is formed exactly:
+        // 1/r_c^3 = s0 (1 + (1 - s0 r_c^3)), and r_c^2 = rc2 + low moves S_0 off it
+        const double low = fma(rc, rc, -k.rc2), cube = k.rc2 * rc, cube_lo = fma(k.rc2, rc, -cube) + low * rc;
+        k.s0 = 1.0 / cube;
+        k.s0_lo = k.s0 * (fma(-k.s0, cube, 1.0) - k.s0 * cube_lo + 1.5 * low / k.rc2);
+        k.c[0] = (double)(1.5L / (rc2 * rc2 * rc));
+        k.ncoef = 1;
+        return;
+    }
     k.ncoef = law64_ncoef(r_cut / r_s);
     if (k.ncoef == 0) return;
-    static std::mutex mu;  // the last fit is kept
-    static double cached_vcut = -1.0, cached[kP2PPoly64Max];
+    static std::mutex mu;  // the last series is kept
+    static long double cached_v0 = -1, cached_s0, cached[kP2PPoly64Max];
     static int cached_m = 0;
-    const double vcut = k.rc2 / (4.0 * k.rs * k.rs);
+    const long double v0 = rc2 / (4 * (long double)k.rs * k.rs);
     std::lock_guard<std::mutex> lk(mu);
-    if (vcut != cached_vcut || k.ncoef != cached_m) {
-        fit_S64(vcut, k.ncoef, cached);
-        cached_vcut = vcut;
+    if (v0 != cached_v0 || k.ncoef != cached_m) {
+        law64_series(v0, k.ncoef, cached_s0, cached);
+        cached_v0 = v0;
         cached_m = k.ncoef;
     }
-    const double inv8rs3 = 1.0 / (8.0 * k.rs * k.rs * k.rs);
-    for (int j = 0; j < k.ncoef; ++j) k.c[j] = cached[j] * inv8rs3;
+    long double p = 1 / (8 * (long double)k.rs * k.rs * k.rs);
+    k.s0 = (double)(cached_s0 * p);
+    k.s0_lo = (double)(cached_s0 * p - k.s0);
+    for (int j = 0; j < k.ncoef; ++j) {
+        p /= rc2;
+        k.c[j] = (double)(cached[j] * p);
+    }
 }
 
 }  // namespace hfmm

@@ -33,7 +33,6 @@
 #include <vector>
 
 #include "expand_impl.h"
-#include "p2p_law.h"
 
 namespace hfmm {
 
@@ -847,14 +846,22 @@ int p2p_setup(const fmm_params *P, P2PConst &k)
     return 0;
 }
 
-static void p2p_setup64(const fmm_params *P, P2PConst64 &k)
+static const P2PConst64 &p2p_setup64(fmm_tree *t, const fmm_params *P)
 {
+    P2PLaw64 &w = t->law64;
+    P2PConst64 &k = w.k;
+    if (w.split == P->split && w.box == P->box && w.r_s == P->r_s && w.r_cut == P->r_cut) return k;
     law64_setup(P->r_s, P->r_cut, P->split, k);
     // the boxes are FP32 in the caller's units: tests only where these hold the boxes of leaves
     // down to 2^-21 of the box to P2PSink's margin
     const bool tests = P->box >= 0x1p-80 && P->box <= 0x1p100 && k.scale >= 0x1p-120 && k.scale <= 0x1p120;
     k.scale32 = tests ? (float)k.scale : 0.0f;
     k.cut = tests ? (float)(P->r_cut * k.scale) * 1.0001f : INFINITY;
+    w.box = P->box;
+    w.r_s = P->r_s;
+    w.r_cut = P->r_cut;
+    w.split = P->split;
+    return k;
 }
 
 // The leaves' bounding boxes (they depend on the tree only).
@@ -988,11 +995,10 @@ static void launch_one(const P2PLaw<F64> &k, const P2PArgs &a, int count, hipStr
 }
 
 template <int CHUNK>
-static int launch_p2p(const fmm_params *P, const P2PArgs &a, int count, hipStream_t st)
+static int launch_p2p(fmm_tree *t, const fmm_params *P, const P2PArgs &a, int count, hipStream_t st)
 {
     if (!P->precision) {
-        P2PConst64 k;
-        p2p_setup64(P, k);
+        const P2PConst64 &k = p2p_setup64(t, P);
         if (k.ncoef == 1) launch_one<true, false, 1, CHUNK>(k, a, count, st);
         else if (k.ncoef == 19) launch_one<true, false, 19, CHUNK>(k, a, count, st);
         else if (k.ncoef == 22) launch_one<true, false, 22, CHUNK>(k, a, count, st);
@@ -1011,11 +1017,11 @@ static int launch_p2p(const fmm_params *P, const P2PArgs &a, int count, hipStrea
 
 int p2p_tile(const fmm_params *P) { return P->p2p_chunk == 16 || P->p2p_chunk == 64 ? P->p2p_chunk : kSinkChunk; }
 
-static int launch_p2p(const fmm_params *P, const P2PArgs &a, int count, hipStream_t st)
+static int launch_p2p(fmm_tree *t, const fmm_params *P, const P2PArgs &a, int count, hipStream_t st)
 {
-    if (P->p2p_chunk == 16) return launch_p2p<16>(P, a, count, st);
-    if (P->p2p_chunk == 64) return launch_p2p<64>(P, a, count, st);
-    return launch_p2p<kSinkChunk>(P, a, count, st);
+    if (P->p2p_chunk == 16) return launch_p2p<16>(t, P, a, count, st);
+    if (P->p2p_chunk == 64) return launch_p2p<64>(t, P, a, count, st);
+    return launch_p2p<kSinkChunk>(t, P, a, count, st);
 }
 
 int p2p_range(fmm_tree *t, const fmm_params *P, int first, int count, const int *err, hipStream_t st)
@@ -1027,7 +1033,7 @@ int p2p_range(fmm_tree *t, const fmm_params *P, int first, int count, const int 
     p2p_args(t, a);
     a.first = first;
     a.err = err;
-    return launch_p2p(P, a, count, st);
+    return launch_p2p(t, P, a, count, st);
 }
 
 // Where the line lies between one wave and a workgroup for a leaf, in p2p_cost: a leaf that
@@ -1071,7 +1077,7 @@ int p2p_wide_launch(fmm_tree *t, const fmm_params *P, long long line, hipStream_
     P2PArgs a;
     p2p_args(t, a);
     a.wide_cost = line;
-    return launch_p2p(P, a, 0, st);
+    return launch_p2p(t, P, a, 0, st);
 }
 
 int p2p(fmm_tree *t, const fmm_params *P, long long line, hipStream_t st)
@@ -1081,7 +1087,7 @@ int p2p(fmm_tree *t, const fmm_params *P, long long line, hipStream_t st)
     P2PArgs a;
     p2p_args(t, a);
     a.wide_cost = line;
-    return launch_p2p(P, a, t->nleaf, st);
+    return launch_p2p(t, P, a, t->nleaf, st);
 }
 
 }  // namespace hfmm

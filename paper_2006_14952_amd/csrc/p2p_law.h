@@ -4,8 +4,6 @@
 #include <math.h>
 #include <string.h>
 
-#include <mutex>
-
 #ifdef __HIPCC__
 #define HFMM_HD __host__ __device__ __forceinline__
 #else
@@ -110,6 +108,7 @@ inline void law64_series(long double v0, int m, long double &s0, long double *T)
     for (int k = 0; k < m; ++k) T[k] = t[k];
 }
 
+// A few microseconds; a tree keeps the result (P2PLaw64).
 inline void law64_setup(double r_s, double r_cut, int split, P2PConst64 &k)
 {
     k = P2PConst64{};
@@ -130,23 +129,22 @@ inline void law64_setup(double r_s, double r_cut, int split, P2PConst64 &k)
     }
     k.ncoef = law64_ncoef(r_cut / r_s);
     if (k.ncoef == 0) return;
-    static std::mutex mu;  // the last series is kept
-    static long double cached_v0 = -1, cached_s0, cached[kP2PPoly64Max];
-    static int cached_m = 0;
-    const long double v0 = rc2 / (4 * (long double)k.rs * k.rs);
-    std::lock_guard<std::mutex> lk(mu);
-    if (v0 != cached_v0 || k.ncoef != cached_m) {
-        law64_series(v0, k.ncoef, cached_s0, cached);
-        cached_v0 = v0;
-        cached_m = k.ncoef;
-    }
+    long double s0, T[kP2PPoly64Max];
+    law64_series(rc2 / (4 * (long double)k.rs * k.rs), k.ncoef, s0, T);
     long double p = 1 / (8 * (long double)k.rs * k.rs * k.rs);
-    k.s0 = (double)(cached_s0 * p);
-    k.s0_lo = (double)(cached_s0 * p - k.s0);
+    k.s0 = (double)(s0 * p);
+    k.s0_lo = (double)(s0 * p - k.s0);
     for (int j = 0; j < k.ncoef; ++j) {
         p /= rc2;
-        k.c[j] = (double)(cached[j] * p);
+        k.c[j] = (double)(T[j] * p);
     }
 }
+
+// The constants of the last evaluation and what they were computed for.
+struct P2PLaw64 {
+    P2PConst64 k{};
+    double box = 0, r_s = 0, r_cut = 0;
+    int split = -1;
+};
 
 }  // namespace hfmm

@@ -3,6 +3,7 @@
 #include <vector>
 
 #include "common.h"
+#include "p2p_law.h"
 
 namespace hfmm {
 constexpr int kHostInts = 4096;
@@ -77,6 +78,7 @@ struct fmm_tree {
     int stk_cap = 4096;                              // entries per wave (grows on overflow)
     int64_t n_m2l = 0, n_p2p = 0, n_visit = 0, p2p_pairs = 0;
     int64_t p2p_max_cost = 0;                        // most list entries x passes of one sink leaf
+    hfmm::P2PLaw64 law64;                            // FP64 P2P: the force law's constants
     hfmm::DevBuf p2p_wide;                           // sink leaves computed by workgroups of several waves
     hfmm::DevBuf counters;                           // device counters
 

@@ -94,3 +94,15 @@ def test_a_pairs_weight_is_good_at_any_separation(law, ratio, split, r_cut):
         assert out[0] <= 1.0, (lo, hi, out[0], out[1])
         if split == 0:  # no more than erfc and exp are off by near the cutoff
             assert out[1] <= 3e-15, (lo, hi, out[1])
+
+
+def test_alternating_force_laws_cost_little_host_time(law):
+    """Two trees of different r_s, evaluated in turn: microseconds a setup (the bar is 40), not a fit's 0.2 to 0.5 ms."""
+    import time
+    best = 1.0
+    for _ in range(5):
+        t0 = time.perf_counter()
+        for k in range(200):
+            law.ncoef(0.02 + 1e-9 * (k & 1), 0.09 + 4.5e-9 * (k & 1), 0)
+        best = min(best, (time.perf_counter() - t0) / 200)
+    assert best < 40e-6, best

@@ -396,7 +396,8 @@ def p2p_roofline(st, p2p_ms, wl, workload, pr, n, split, learned=None, fused=Fal
     the persistent schedule the kernel is the one P2P + M2L launch and its work adds the
     M2L arithmetic, 2 C(p+6, 6) flop per accepted pair.  With P2P launched per leaf level
     beside the traversal, the duration is the sum of those launches, which share the device
-    with the traversal.
+    with the traversal; else it lasts from the start of the first P2P launch to the end of the
+    last (the costliest leaves, where there are such, have one of their own beside the others').
     traffic: scaled FETCH_SIZE + WRITE_SIZE of the step's P2P launches from profiles/, when
     those counters were taken on this workload with these parameters, the same launch
     pattern and the current P2P sources."""
@@ -426,7 +427,8 @@ def p2p_roofline(st, p2p_ms, wl, workload, pr, n, split, learned=None, fused=Fal
             "listed_pairs": st["p2p_pairs"], "evaluated_pairs": st["p2p_evaluated"],
             "p2p_ms_per_launch": p2p_ms,
             "launches": ("one per leaf level, beside the traversal: duration = their sum per step" if per_level
-                         else "one per step")}
+                         else "one per step, and one of workgroups of eight waves beside it if some leaves are "
+                              "that costly: duration = from the first's start to the last's end")}
 
 
 def _binom(n, k):
@@ -437,8 +439,9 @@ def _binom(n, k):
 def stage_rooflines(counts, stages, build_ms, step_ms, n, p, learned, precision, split):
     """Per-stage work at its own peak against the stage's measured span, and the whole step:
     sum of the stages' times at peak / ms per step.  Work per unit: tree 250 B per particle
-    (HBM); P2M 2 n_p per particle and M2M, L2L 2 C(p+6,6) per cell; traversal ~40 FP64
-    operations per visited pair; M2L 2 C(p+6,6) per accepted pair (at each pair's order for
+    (HBM); P2M 2 n_p per particle and M2M, L2L 2 C(p+6,6) per cell; traversal ~40
+    operations per visited pair, at the FP64 rate (FP32 and whole numbers where those hold the
+    distances); M2L 2 C(p+6,6) per accepted pair (at each pair's order for
     the learned selector); P2P 38 flop per listed pair (30 with the polynomial split);
     L2P 6 C(p+2,3) per particle.  Stages on the two streams overlap, so their spans do too."""
     pe = 8 if learned else p  # expansions are kept at order 8 under the selector

@@ -129,8 +129,10 @@ typedef struct fmm_stats {
     int64_t p2p_evaluated;     /* particle pairs the P2P kernel evaluated: the listed pairs less
                                   those of source leaves whose particles' bounding box is
                                   farther than r_cut from the sink leaf's */
-    /* stage spans (with timing on; stages on the two streams overlap); under schedule 2
-       t_m2l_ms and t_p2p_ms are both the span of the one P2P + M2L launch */
+    /* stage spans (with timing on; stages on the two streams overlap); t_p2p_ms lasts from the
+       first to the end of the last of P2P's launches (the costliest leaves may have one of their
+       own, ahead of M2L on its stream); with P2P launched per level it is the launches' sum;
+       under schedule 2 t_m2l_ms and t_p2p_ms are both the span of the one P2P + M2L launch */
     double t_tree_ms, t_upward_ms, t_traverse_ms, t_m2l_ms, t_p2p_ms, t_downward_ms, t_total_ms;
     double t_build_ms;         /* last fmm_build_tree */
     double t_pm_ms;            /* long-range (PM) part of the last fmm_hybrid_forces_tree */

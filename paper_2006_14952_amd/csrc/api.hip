@@ -199,6 +199,7 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
         mark(t, 6, st);
         mark(t, 3, st);
     }
+    bool wide = false;
     if (!fused && !per_level) {  // P2P after the whole traversal
         // the costliest leaves, if any, by workgroups of several waves on st (the launch of
         // the others waits for their selection only, so they find the GPU empty)
@@ -207,9 +208,13 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
         if ((rc = hip_check(hipEventRecord(t->dep[2], st), "event")) ||
             (rc = hip_check(hipStreamWaitEvent(ax, t->dep[2], 0), "event wait")))
             return rc;
-        if (line < 1ll << 62)
-            if ((rc = hip_check(hipStreamWaitEvent(st, t->dep[1], 0), "event wait")) || (rc = p2p_wide_launch(t, P, line, st)))
-                return rc;
+        wide = line < 1ll << 62;
+        if (wide) {
+            if ((rc = hip_check(hipStreamWaitEvent(st, t->dep[1], 0), "event wait"))) return rc;
+            mark(t, 12, st);
+            if ((rc = p2p_wide_launch(t, P, line, st))) return rc;
+            mark(t, 13, st);
+        }
         mark(t, 5, ax);
         if ((rc = p2p(t, P, line, ax))) return rc;
         mark(t, 6, ax);
@@ -237,10 +242,12 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
         if ((rc = hip_check(hipEventSynchronize(t->ev[11]), "timing event"))) return rc;
         S.t_upward_ms = ev_ms(t, 9, 1);
         S.t_traverse_ms = P->learned ? ev_ms(t, 1, 2) : ev_ms(t, 0, 2);
-        S.t_m2l_ms = fused ? ev_ms(t, 5, 6) : ev_ms(t, 2, 3);  // schedule 2: both stages are one launch
+        S.t_m2l_ms = fused ? ev_ms(t, 5, 6) : ev_ms(t, wide ? 13 : 2, 3);  // schedule 2: both stages are one launch
         S.t_downward_ms = ev_ms(t, 3, 4) + ev_ms(t, 10, 11);
         if (!per_level) {
-            S.t_p2p_ms = ev_ms(t, 5, 6);
+            // from the first of its launches to the end of the last
+            const int first = wide && ev_ms(t, 12, 5) > 0.0f ? 12 : 5, last = wide && ev_ms(t, 6, 13) > 0.0f ? 13 : 6;
+            S.t_p2p_ms = ev_ms(t, first, last);
         } else {  // the sum of the per-level P2P launches
             S.t_p2p_ms = 0.0;
             for (int l = 0; l + 1 < (int)t->leaf_lvl.size() && l <= kMaxLevel; ++l) {

@@ -14,8 +14,7 @@ void clear_error();
 int pm_forces(const fmm_params *P, int mesh, int64_t n, const double *pos, const double *mass, double *acc,
               hipStream_t st);
 int add_into(double *acc, const double *other, int64_t n3, hipStream_t st);
-int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st,
-                   std::unique_lock<std::mutex> &lk);
+int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st);
 const MacModel *current_model(MacModel *host_copy);
 uint64_t model_serial();
 int run_labels(fmm_tree *t, const fmm_params *P, const double *aref_sorted, double eps, int stride, float *feats,
@@ -106,21 +105,8 @@ static int p2p_level_hook(void *ctx, int l, hipStream_t st)
 }
 
 // The stages of one short-range evaluation on a built tree (or forest of boxes).
-// pm: the long-range part of a hybrid step as well (acc is then the sum).
-struct LongRange {
-    int mesh;
-    std::unique_lock<std::mutex> *lk;
-
-    int run(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t st) const
-    {
-        mark(t, 7, st);
-        if (int rc = pm_forces_tree(P, mesh, t, acc, st, *lk)) return rc;  // deposits in Morton order
-        mark(t, 8, st);
-        return hip_check(hipEventRecord(t->pm_done, st), "event");
-    }
-};
-
-static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t st, const LongRange *pm = nullptr)
+// mesh > 0: the long-range part of a hybrid step as well (acc is then the sum).
+static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t st, int mesh = 0)
 {
     MacModel hm;
     const MacModel *dm = nullptr;
@@ -163,7 +149,11 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
     // on the second stream, beside the traversal, which leaves most of the GPU idle: hybrid step
     // 6.43 -> 6.31 ms.  Beside P2P it was slower than on its own (6.70 -> 6.87): its launches wait
     // behind P2P's waves, and M2L behind them.
-    if (pm && (rc = pm->run(t, P, acc, ax))) return rc;
+    if (mesh > 0) {
+        mark(t, 7, ax);
+        if ((rc = pm_forces_tree(P, mesh, t, acc, ax))) return rc;  // deposits in Morton order
+        mark(t, 8, ax);
+    }
     const bool fused = P->schedule == 2;
     // P2P level by level beside the traversal, measured on one box each: 134M box 718 ->
     // 697 ms (19M leaves), 16.7M box 75.5 -> 75.0 ms (2.3M leaves), slower on small trees
@@ -229,7 +219,7 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
     mark(t, 4, st);
     if (!fused && (rc = hip_check(hipStreamWaitEvent(st, t->dep[3], 0), "event wait"))) return rc;
     mark(t, 10, st);
-    if ((rc = l2p_combine(t, &P8, acc, pm != nullptr, st))) return rc;
+    if ((rc = l2p_combine(t, &P8, acc, mesh > 0, st))) return rc;
     mark(t, 11, st);
     t->last_p = P->p;
     t->last_prec = P->precision;
@@ -643,14 +633,11 @@ int fmm_hybrid_forces_tree(fmm_tree **tree, const fmm_params *P, int mesh, int64
     hipStream_t st = (hipStream_t)stream;
     if (int rc = fmm_build_tree(P, n, pos, mass, stream, tree)) return rc;
     fmm_tree *t = *tree;
-    if (!t->pm_done && hipEventCreateWithFlags(&t->pm_done, hipEventDisableTiming) != hipSuccess)
-        return set_error(FMM_ERR_HIP, "hipEventCreateWithFlags");
-    std::unique_lock<std::mutex> lk;
-    const LongRange pm{mesh, &lk};
-    int rc = run_forces(t, P, acc, st, &pm);
-    // the mesh buffers are the next call's; after an error acc is no longer written either
-    const int rc_pm = !lk.owns_lock() ? 0 : hip_check(rc ? hipStreamSynchronize(t->aux) : hipEventSynchronize(t->pm_done), "pm");
-    if (rc || (rc = rc_pm)) return rc;
+    if (mesh < 8 || mesh > 1024) return set_error(FMM_ERR_ARG, "mesh must be in [8, 1024]");
+    if (int rc = run_forces(t, P, acc, st, mesh)) {
+        if (t->aux) (void)hipStreamSynchronize(t->aux);  // after an error acc is no longer written either
+        return rc;
+    }
     if (t->timing) {
         (void)hipEventSynchronize(t->ev[8]);  // timing only
         t->stats.t_pm_ms = ev_ms(t, 7, 8);
@@ -715,7 +702,6 @@ void fmm_free_tree(fmm_tree *t)
         for (auto &e : t->p2p_t0) (void)hipEventDestroy(e);
         for (auto &e : t->p2p_t1) (void)hipEventDestroy(e);
     }
-    if (t->pm_done) (void)hipEventDestroy(t->pm_done);
     if (t->aux) {
         (void)hipStreamSynchronize(t->aux);
         for (auto &e : t->dep) (void)hipEventDestroy(e);

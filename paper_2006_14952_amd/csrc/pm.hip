@@ -27,8 +27,10 @@ struct PMPlan {
     int mesh = 0;
     hipfftHandle r2c = 0, c2r = 0;
     DevBuf rho, rhok, work, amesh;
+    hipEvent_t done = nullptr;  // the last call that left its launches behind has done with the buffers
 };
 
+// Held while a call uses a plan on the host; on the device a call's launches wait for `done`.
 static std::mutex g_pm_mu;
 static std::map<int, PMPlan *> g_pm;  // one plan set per mesh size per process
 // Caller-order particles brought into mesh order, for every mesh size (guarded by g_pm_mu, as
@@ -53,6 +55,10 @@ static int pm_plan(int mesh, PMPlan **out)
     }
     PMPlan *p = new PMPlan();
     p->mesh = mesh;
+    if (hipEventCreateWithFlags(&p->done, hipEventDisableTiming) != hipSuccess) {
+        delete p;
+        return set_error(FMM_ERR_HIP, "hipEventCreateWithFlags");
+    }
     if (hipfftPlan3d(&p->r2c, mesh, mesh, mesh, HIPFFT_D2Z) != HIPFFT_SUCCESS ||
         hipfftPlan3d(&p->c2r, mesh, mesh, mesh, HIPFFT_Z2D) != HIPFFT_SUCCESS) {
         delete p;
@@ -618,6 +624,7 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
     PMPlan *pl;
     if (int rc = pm_plan(mesh, &pl)) return rc;
     std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
+    if (int rc = hip_check(hipStreamWaitEvent(st, pl->done, 0), "pm event wait")) return rc;
     int *check = ptr<int>(pl->amesh), found[2] = {0, 0};  // scratch in the (not yet used) output mesh
     if (int rc = hip_check(hipMemsetAsync(check, 0, 2 * sizeof(int), st), "pm check")) return rc;
     auto read_check = [&]() -> int {
@@ -659,19 +666,23 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
 }
 
 // PM on the particles of a built tree (Morton order, already wrapped and checked), enqueued on
-// st.  The plan's buffers are shared: lk is held on return, until st has done with them.
-int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st,
-                   std::unique_lock<std::mutex> &lk)
+// st.  The plan's buffers are the next call's once `done` has passed, so the host lock covers
+// the launches only: hybrid steps of several threads share the mesh part one after the other,
+// and nothing else.
+int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st)
 {
     if (mesh < 8 || mesh > 1024) return set_error(FMM_ERR_ARG, "mesh must be in [8, 1024]");
     if (t->n == 0) return 0;
     PMPlan *pl;
     if (int rc = pm_plan(mesh, &pl)) return rc;
-    lk = std::unique_lock<std::mutex>(g_pm_mu);
-    return pm_run(pl, P, mesh, (int)t->n,
-                  MortonOrder{ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs), ptr<double>(t->ms),
-                              ptr<int>(t->perm)},
-                  ptr<uint64_t>(t->keys[t->sorted]), true, acc, st);
+    std::lock_guard<std::mutex> lk(g_pm_mu);
+    if (int rc = hip_check(hipStreamWaitEvent(st, pl->done, 0), "pm event wait")) return rc;
+    const int rc = pm_run(pl, P, mesh, (int)t->n,
+                          MortonOrder{ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs), ptr<double>(t->ms),
+                                      ptr<int>(t->perm)},
+                          ptr<uint64_t>(t->keys[t->sorted]), true, acc, st);
+    const int rc_done = hip_check(hipEventRecord(pl->done, st), "pm event");  // after an error too
+    return rc ? rc : rc_done;
 }
 
 int add_into(double *acc, const double *other, int64_t n3, hipStream_t st)

@@ -336,10 +336,13 @@ int fmm_mlp_adam(float *params, const float *grad, float *m, float *v, int64_t s
 
 /* Bound on the device memory the library's own buffers may hold, process-wide: trees and
  * their lists, forests, PM meshes, training scratch (not the caller's arrays, the FFT plans'
- * work areas, the selector model or the fixed scratch array of fmm_mlp_grad_noalloc).  0, the default, is no bound.  The buffers are kept
- * for reuse and freed only with their tree (PM meshes at exit; the mesh order that
- * pm_long_range_forces may bring its particles into after a call in which it took over 2 GiB), so
- * the bound applies to what they hold together.  A call that would grow a buffer past it fails with
+ * work areas, the selector model or the fixed scratch array of fmm_mlp_grad_noalloc).  0, the
+ * default, is no bound.  The buffers are kept for reuse and freed only with their tree (PM
+ * meshes at exit), so the bound applies to what they hold together.  The exception is the mesh
+ * order that pm_long_range_forces may bring its particles into, about 71 bytes a particle: it is
+ * kept between calls of up to 38 million particles (2.7 GB), and given back when any other
+ * buffer of the library does not fit without, or when a bound below what is held is set.  A
+ * call that would grow a buffer past the bound fails with
  * FMM_ERR_NOMEM before allocating, as a failed device allocation does; a tree whose build
  * fails that way is left empty (rebuild it or free it).  Always returns 0. */
 int fmm_set_memory_limit(uint64_t bytes);

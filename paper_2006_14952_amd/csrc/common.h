@@ -109,6 +109,9 @@ int hip_check(hipError_t e, const char *what);
 
 // scans (int32), result is exclusive; total (device int) optional
 int scan_exclusive(const int *in, int *out, int n, int *total, hipStream_t st, DevBuf &tmp);
+// Gives back device buffers kept for reuse that no call is using (the mesh order of the PM's
+// caller-order particles); false if there are none.
+bool release_idle();
 int zero_async(void *p, size_t bytes, hipStream_t st);  // p 16-byte aligned, bytes a multiple of 4
 // ---------------------------------------------------------------------------
 // Inclusive scans over one 64-lane wave by DPP: shifts by 1, 2, 4 and 8 lanes within each

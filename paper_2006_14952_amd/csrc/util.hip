@@ -33,22 +33,31 @@ uint64_t buffer_moves() { return g_moves.load(std::memory_order_relaxed); }
 
 // Bytes the library's device buffers hold (process-wide) and the caller's bound on them.
 static std::atomic<uint64_t> g_used{0}, g_limit{0};
-void set_memory_limit(uint64_t bytes) { g_limit.store(bytes, std::memory_order_relaxed); }
 uint64_t memory_in_use() { return g_used.load(std::memory_order_relaxed); }
+void set_memory_limit(uint64_t bytes)
+{
+    g_limit.store(bytes, std::memory_order_relaxed);
+    if (bytes && memory_in_use() > bytes) (void)release_idle();
+}
 
 int grow(DevBuf &b, size_t bytes)
 {
     if (bytes <= b.bytes) return 0;
     size_t want = bytes + bytes / 4 + 256;
     const uint64_t lim = g_limit.load(std::memory_order_relaxed);
-    if (lim && memory_in_use() - b.bytes + want > lim)
+    auto over = [&]() { return lim && memory_in_use() - b.bytes + want > lim; };
+    if (over()) (void)release_idle();
+    if (over())
         return set_error(FMM_ERR_NOMEM, "device buffers would hold %llu bytes, over the limit of %llu",
                          (unsigned long long)(memory_in_use() - b.bytes + want), (unsigned long long)lim);
     g_moves.fetch_add(1, std::memory_order_relaxed);  // a recorded graph may hold the old address
     void *p = nullptr;
     if (hipMalloc(&p, want) != hipSuccess) {
         (void)hipGetLastError();
-        return set_error(FMM_ERR_NOMEM, "hipMalloc of %zu bytes failed", want);
+        if (!release_idle() || hipMalloc(&p, want) != hipSuccess) {
+            (void)hipGetLastError();
+            return set_error(FMM_ERR_NOMEM, "hipMalloc of %zu bytes failed", want);
+        }
     }
     release(b);
     g_used.fetch_add(want, std::memory_order_relaxed);

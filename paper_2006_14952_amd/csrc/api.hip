@@ -136,12 +136,12 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
         t->lev_ready = true;
     }
     hipStream_t ax = t->aux;
-    // Dependencies: {upward, leaf boxes} -> M2L (and the leaves wide_line selects); traversal of level l -> P2P of level l's leaves;
-    // traversal -> M2L; M2L -> L2L; {L2L, P2P} -> L2P.
+    // Dependencies: {upward, leaf boxes} -> M2L (and the leaves wide_line selects); traversal of
+    // level l -> P2P of level l's leaves; traversal -> M2L; M2L -> L2L; {L2L, P2P} -> L2P.
     // The plain traversal does not read multipoles, so the upward pass runs beside it on
     // the second stream; P2P runs there, level by level beside the traversal, then beside
-    // M2L and L2L.  The FP32 P2P's leaf boxes depend on the tree only: they are computed
-    // on the second stream ahead of P2P.
+    // M2L and L2L.  P2P's leaf boxes depend on the tree only: they are computed on the second
+    // stream ahead of P2P.
     if ((rc = hip_check(hipEventRecord(t->dep[0], st), "event")) || (rc = hip_check(hipStreamWaitEvent(ax, t->dep[0], 0), "event wait")))
         return rc;
     mark(t, 0, st);

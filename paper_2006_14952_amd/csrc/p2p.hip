@@ -812,7 +812,7 @@ int p2p_setup(const fmm_params *P, P2PConst &k)
     const double vcut = (P->r_cut * P->r_cut) / (4.0 * P->r_s * P->r_s);
     double coef[kP2PPolyMax] = {0};
     int m = 0;
-    if (P->precision == 1 && P->split == 0) {  // the FP64 form evaluates erfc/exp: no fit, no limit
+    if (P->precision == 1 && P->split == 0) {  // the FP64 form has its own law (p2p_law.h) and no limit
         if (P->r_cut > kP2PMaxCut * P->r_s)
             return set_error(FMM_ERR_ARG, "precision 1 supports r_cut <= %.0f r_s (r_cut / r_s = %.3g): beyond it the "
                                           "FP32 pair force loses accuracy near the cutoff; use precision 0",

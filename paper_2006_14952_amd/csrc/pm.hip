@@ -104,8 +104,8 @@ static int pm_plan(int mesh, PMPlan **out)
 
 // Mass-assignment weights of the B-spline schemes on the cell-centred mesh (node i at
 // (i + 0.5) Delta): ORDER 2 cloud-in-cell, 3 triangular-shaped cloud, 4 piecewise cubic.
-// The particle touches nodes i0 .. i0 + ORDER - 1 (mod M) with weights w[0 .. ORDER-1].
-// The same without the wrap: first node (may lie outside [0, M)) and weights.
+// Weights w[0 .. ORDER-1] of a particle's nodes along one axis; returns the first of them, which
+// may lie outside [0, M).
 template <int ORDER> __device__ __forceinline__ int assign_first(double x, double inv_d, double *w)
 {
     const double g = x * inv_d - 0.5;
@@ -132,6 +132,7 @@ template <int ORDER> __device__ __forceinline__ int assign_first(double x, doubl
     return (int)first;
 }
 
+// The same with the first node wrapped: nodes i0 .. i0 + ORDER - 1 (mod M).
 template <int ORDER> __device__ __forceinline__ void assign_weights(double x, double inv_d, int M, int &i0, double *w)
 {
     const int i = assign_first<ORDER>(x, inv_d, w);

@@ -158,7 +158,7 @@ int p2p_tile(const fmm_params *P);  // sink particles per pass over a leaf's lis
 // P2P of the sink leaves leaves[first .. first+count-1]; with err non-NULL the launch does
 // nothing while *err is non-zero (lists of a traversal that overflowed)
 int p2p_range(fmm_tree *t, const fmm_params *P, int first, int count, const int *err, hipStream_t st);
-int p2p_bbox(fmm_tree *t, const fmm_params *P, hipStream_t st);  // before p2p (FP32 form): leaf boxes
+int p2p_bbox(fmm_tree *t, const fmm_params *P, hipStream_t st);  // before p2p: leaf boxes
 bool fused_applies(const fmm_params *P);                            // schedule 2 serves these parameters
 int p2p_m2l_fused_prepare(fmm_tree *t, const fmm_params *P, hipStream_t st);  // schedule 2: L, pairs, queue
 int p2p_m2l_fused_launch(fmm_tree *t, const fmm_params *P, hipStream_t st);   // P2P + M2L, one launch

@@ -187,7 +187,8 @@ __global__ void k_deposit(S src, int n, double box, int M, double inv_vol, doubl
 // particles, whose nodes are hardly shared) adds straight to the mesh.
 // 16.7M clustered particles on 256^3 (in this order): 6.27 -> 0.30 ms; the 2M box in tree order on
 // 128^3: 1.81 -> 0.09 ms.
-constexpr int kDepositThreads = 512, kDepositTile = 4096, kDepositSide = 20, kDepositCubes = 32;
+constexpr int kDepositThreads = 512, kDepositTile = 4096, kDepositSide = 20, kDepositPerCube = 128;
+constexpr int kDepositCubes = kDepositTile / kDepositPerCube;
 constexpr int kDepositPer = kDepositTile / kDepositThreads;
 
 // Node index modulo M; nodes lie in [-2, M + 4] and M >= 8.
@@ -253,12 +254,12 @@ template <int ORDER> struct CubeNodes {
 
 template <int ORDER>
 __global__ __launch_bounds__(kDepositThreads) void k_deposit_cubes(MortonOrder src, const uint64_t *__restrict__ keys,
-                                                                   int levels, int n, double box, int M, double inv_vol,
-                                                                   double *__restrict__ rho)
+                                                                   int levels, int n, int tile, double box, int M,
+                                                                   double inv_vol, double *__restrict__ rho)
 {
     __shared__ double acc[kDepositSide * kDepositSide * kDepositSide];
     __shared__ CubeHeads heads;
-    const int base = blockIdx.x * kDepositTile, cnt = min(kDepositTile, n - base), sh = 63 - 3 * levels;
+    const int base = blockIdx.x * tile, cnt = min(tile, n - base), sh = 63 - 3 * levels;
     const int cubes = find_cubes(heads, keys, base, cnt, sh);
     const double inv_d = M / box;
     auto direct = [&](const int *i, const double (*w)[ORDER], double m) __attribute__((always_inline)) {
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit_cubes(MortonOrder s
                     atomicAdd(&rho[((size_t)ix * M + iy) * M + iz], m * w[0][dx] * w[1][dy] * w[2][dz]);
                 }
     };
-    if (cubes > kDepositCubes) {
+    if (cubes > tile / kDepositPerCube) {
         for (int q = threadIdx.x; q < cnt; q += kDepositThreads) {
             const int p = base + q;
             int i[3];
@@ -535,39 +536,57 @@ __global__ void k_add3(double *__restrict__ acc, const double *__restrict__ othe
     if (i < n3) acc[i] += other[i];
 }
 
-// out[0]: a position is not finite; out[1]: particles in the mesh cell of the one before them.
+// out[0]: a position is not finite; out[1]: particles in the mesh cell of the one before them;
+// out[2] (LAG): particles in the mesh cell of the one 64 places before.
+constexpr int kRunLag = 64;
+
+__device__ __forceinline__ bool same_cell(const double *__restrict__ pos, int i, int j, double inv_d)
+{
+    bool eq = true;
+    for (int a = 0; a < 3; ++a)
+        eq = eq && floor(pos[3 * (size_t)i + a] * inv_d) == floor(pos[3 * (size_t)j + a] * inv_d);
+    return eq;
+}
+
+template <bool LAG>
 __global__ __launch_bounds__(256) void k_check_positions(const double *__restrict__ pos, int n, double inv_d,
                                                          int *__restrict__ out)
 {
-    __shared__ int same;
-    if (threadIdx.x == 0) same = 0;
+    __shared__ int same[2];
+    if (threadIdx.x < 2) same[threadIdx.x] = 0;
     __syncthreads();
-    int mine = 0;
+    int mine = 0, far = 0;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-        bool eq = i > 0;
-        for (int a = 0; a < 3; ++a) {
-            const double x = pos[3 * (size_t)i + a];
-            if (!isfinite(x)) out[0] = 1;
-            if (i > 0) eq = eq && floor(x * inv_d) == floor(pos[3 * (size_t)i + a - 3] * inv_d);
-        }
-        mine += eq;
+        for (int a = 0; a < 3; ++a)
+            if (!isfinite(pos[3 * (size_t)i + a])) out[0] = 1;
+        if (i > 0) mine += same_cell(pos, i, i - 1, inv_d);
+        if (LAG && i >= kRunLag) far += same_cell(pos, i, i - kRunLag, inv_d);
     }
-    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-    if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&same, mine);
+    for (int o = 32; o > 0; o >>= 1) {
+        mine += __shfl_xor(mine, o, 64);
+        if (LAG) far += __shfl_xor(far, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        if (mine) atomicAdd(&same[0], mine);
+        if (far) atomicAdd(&same[1], far);
+    }
     __syncthreads();
-    if (threadIdx.x == 0 && same) atomicAdd(&out[1], same);
+    if (threadIdx.x < 2 && same[threadIdx.x]) atomicAdd(&out[1 + threadIdx.x], same[threadIdx.x]);
 }
 
 // Whether to bring n caller-order particles into mesh order: always if enough of them share the
-// mesh's nodes (dense), else if many, `same` of them, lie in the cell of the one before.  Two
-// things make the direct deposit slow: particles of a clump that follow each other in the
-// caller's arrays and queue on the same nodes (some 10 ns each, against 0.1 to 0.2 ms for the
-// order), and mesh nodes that miss the caches.  Measured, ms direct / ordered: clustered
-// 65,536 on 32^3 0.60 / 0.23, 100,000 on 64^3 0.90 / 0.35, 30,000 on 64^3 0.24 / 0.45; uniform
-// 262,144 on 64^3 0.25 / 0.28, 500,000 on 80^3 0.41 / 0.33, 1,048,576 on 100^3 0.81 / 0.44, but
-// 1,000,000 on 250^3, whose nodes hardly two particles share, 1.92 / 2.06.
+// mesh's nodes (dense), else if many lie in the cell of the one before (kSameMin).  Two things
+// make the direct deposit slow: particles of a clump that follow each other in the caller's
+// arrays and queue on the same nodes (some 10 ns each, against 0.1 to 0.2 ms for the order), and
+// mesh nodes that miss the caches.  Measured, ms direct / ordered: clustered 65,536 on 32^3
+// 0.34 / 0.15, 100,000 on 64^3 0.40 / 0.20; uniform 500,000 on 80^3 0.41 / 0.33, 1,048,576 on
+// 100^3 0.81 / 0.44, but 1,000,000 on 250^3, whose nodes hardly two particles share,
+// 1.92 / 2.06.  Particles that come in mesh order follow each other in their cells although
+// nothing queues: there the order pays from some 100,000 of them on (uniform ones so sorted, on
+// 16^3: 65,536 0.114 / 0.123, 100,000 0.149 / 0.135), and below if cells hold so many that the
+// one 64 places before is still in them (kFarMin: clustered 30,000 on 16^3 0.37 / 0.16).
 static bool dense(int n, int mesh) { return n >= 1 << 19 && 8.0 * n >= (double)mesh * mesh * mesh; }
-constexpr int kSameMin = 1 << 14;
+constexpr int kSameMin = 1 << 14, kFarMin = 2000, kManyMin = 100000;
 
 // Morton levels at which a cube is at most 19 - order mesh cells wide (k_deposit_cubes).
 static int cube_levels(int mesh, int order)
@@ -575,6 +594,20 @@ static int cube_levels(int mesh, int order)
     int l = 0;
     while (mesh > (19 - order) << l) ++l;
     return l;
+}
+
+// Particles per workgroup of k_deposit_cubes: fewer where 4,096 would leave the chip idle (64
+// nodes a particle on 64^3, clumps in mesh order: 65,536 particles in tiles of 4,096 1.75 ms, of
+// 512 0.45; the direct deposit 0.70).  But where a cube takes several tiles, each sends all of the
+// cube's nodes to the mesh, so a tile then keeps several contributions a node (8 nodes a particle
+// on 16^3, one cube, 300,000 uniform: tiles of 4,096 0.215 ms, of 512 0.233).
+static int deposit_tile(int n, int levels, int order)
+{
+    const int cube = n >> 3 * levels, several = order == 4 ? 512 : order == 3 ? 1024 : kDepositTile;
+    const int least = cube < several ? cube : several;
+    int t = kDepositTile;
+    while (t > kDepositThreads && n / t < 512 && t / 2 >= least) t /= 2;
+    return t;
 }
 
 // keys: the Morton keys of src's particles, in order by their first 3 cube_levels bits
@@ -600,12 +633,12 @@ static int pm_run(PMPlan *pl, const fmm_params *P, int mesh, int n, S src, const
         k_fixed_to_double<<<(unsigned)((nr + 255) / 256), 256, 0, st>>>(irho, nr, mx, n, inv_vol);
     } else if (keys) {
         if constexpr (std::is_same<S, MortonOrder>::value) {
-            const unsigned g = (unsigned)((n + kDepositTile - 1) / kDepositTile);
-            const int lv = cube_levels(mesh, order);
+            const int lv = cube_levels(mesh, order), tile = deposit_tile(n, lv, order);
+            const unsigned g = (unsigned)((n + tile - 1) / tile);
             double *rho = ptr<double>(pl->rho);
-            if (order == 3) k_deposit_cubes<3><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, inv_vol, rho);
-            else if (order == 4) k_deposit_cubes<4><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, inv_vol, rho);
-            else k_deposit_cubes<2><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, P->box, mesh, inv_vol, rho);
+            if (order == 3) k_deposit_cubes<3><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, tile, P->box, mesh, inv_vol, rho);
+            else if (order == 4) k_deposit_cubes<4><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, tile, P->box, mesh, inv_vol, rho);
+            else k_deposit_cubes<2><<<g, kDepositThreads, 0, st>>>(src, keys, lv, n, tile, P->box, mesh, inv_vol, rho);
         }
     } else if (order == 3) {
         k_deposit<S, 3><<<nb, 256, 0, st>>>(src, n, P->box, mesh, inv_vol, ptr<double>(pl->rho));
@@ -653,8 +686,8 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
     if (int rc = pm_plan(mesh, &pl)) return rc;
     std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
     if (int rc = hip_check(hipStreamWaitEvent(st, pl->done, 0), "pm event wait")) return rc;
-    int *check = ptr<int>(pl->amesh), found[2] = {0, 0};  // scratch in the (not yet used) output mesh
-    if (int rc = hip_check(hipMemsetAsync(check, 0, 2 * sizeof(int), st), "pm check")) return rc;
+    int *check = ptr<int>(pl->amesh), found[4] = {0, 0, 0, 0};  // scratch in the (not yet used) output mesh
+    if (int rc = hip_check(hipMemsetAsync(check, 0, sizeof(found), st), "pm check")) return rc;
     auto read_check = [&]() -> int {
         if (hipMemcpyAsync(found, check, sizeof(found), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
@@ -663,13 +696,15 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
     };
     auto check_all = [&]() -> int {
         const int nb = (n + 255) / 256;
-        k_check_positions<<<nb < 2048 ? nb : 2048, 256, 0, st>>>(pos, n, mesh / P->box, check);
+        const auto kernel = n < kManyMin ? k_check_positions<true> : k_check_positions<false>;
+        kernel<<<nb < 2048 ? nb : 2048, 256, 0, st>>>(pos, n, mesh / P->box, check);
         return read_check();
     };
     const bool sure = !P->deterministic && dense(n, mesh);  // the keys' pass finds non-finite positions too
     if (!sure)
         if (int rc = check_all()) return rc;
-    if (sure || (!P->deterministic && found[1] >= kSameMin)) {
+    const bool runs = found[1] >= kSameMin && (n >= kManyMin || found[2] >= kFarMin);
+    if (sure || (!P->deterministic && runs)) {
         const int order = P->pm_assign == 0 ? 2 : P->pm_assign;
         const OrderUse use;
         MortonSort &s = g_order;

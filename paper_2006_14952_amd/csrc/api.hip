@@ -14,7 +14,8 @@ void clear_error();
 int pm_forces(const fmm_params *P, int mesh, int64_t n, const double *pos, const double *mass, double *acc,
               hipStream_t st);
 int add_into(double *acc, const double *other, int64_t n3, hipStream_t st);
-int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st);
+int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st, uint64_t *call);
+int pm_tree_done(int mesh, uint64_t call);
 const MacModel *current_model(MacModel *host_copy);
 uint64_t model_serial();
 int run_labels(fmm_tree *t, const fmm_params *P, const double *aref_sorted, double eps, int stride, float *feats,
@@ -151,7 +152,7 @@ static int run_forces(fmm_tree *t, const fmm_params *P, double *acc, hipStream_t
     // behind P2P's waves, and M2L behind them.
     if (mesh > 0) {
         mark(t, 7, ax);
-        if ((rc = pm_forces_tree(P, mesh, t, acc, ax))) return rc;  // deposits in Morton order
+        if ((rc = pm_forces_tree(P, mesh, t, acc, ax, &t->pm_call))) return rc;  // deposits in Morton order
         mark(t, 8, ax);
     }
     const bool fused = P->schedule == 2;
@@ -638,6 +639,7 @@ int fmm_hybrid_forces_tree(fmm_tree **tree, const fmm_params *P, int mesh, int64
         if (t->aux) (void)hipStreamSynchronize(t->aux);  // after an error acc is no longer written either
         return rc;
     }
+    if (int rc = pm_tree_done(mesh, t->pm_call)) return rc;
     if (t->timing) {
         (void)hipEventSynchronize(t->ev[8]);  // timing only
         t->stats.t_pm_ms = ev_ms(t, 7, 8);

@@ -29,7 +29,8 @@ struct PMPlan {
     int mesh = 0;
     hipfftHandle r2c = 0, c2r = 0;
     DevBuf rho, rhok, work, amesh;
-    hipEvent_t done = nullptr;  // the last call that left its launches behind has done with the buffers
+    uint64_t behind = 0;  // number of the call whose launches may still use the buffers, 0: none
+    hipEvent_t done = nullptr;  // their end
 };
 
 // Held while a call uses a plan on the host; on the device a call's launches wait for `done`.
@@ -71,6 +72,12 @@ struct OrderUse {
     }
     ~OrderUse() { g_order_busy = false; }
 };
+
+// The launches on st wait for those a call has left behind.
+static int pm_wait(const PMPlan *pl, hipStream_t st)
+{
+    return pl->behind ? hip_check(hipStreamWaitEvent(st, pl->done, 0), "pm event wait") : 0;
+}
 
 static int pm_plan(int mesh, PMPlan **out)
 {
@@ -685,7 +692,7 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
     PMPlan *pl;
     if (int rc = pm_plan(mesh, &pl)) return rc;
     std::lock_guard<std::mutex> lk(g_pm_mu);  // plans and their buffers are shared per mesh size
-    if (int rc = hip_check(hipStreamWaitEvent(st, pl->done, 0), "pm event wait")) return rc;
+    if (int rc = pm_wait(pl, st)) return rc;
     int *check = ptr<int>(pl->amesh), found[4] = {0, 0, 0, 0};  // scratch in the (not yet used) output mesh
     if (int rc = hip_check(hipMemsetAsync(check, 0, sizeof(found), st), "pm check")) return rc;
     auto read_check = [&]() -> int {
@@ -732,21 +739,40 @@ int pm_forces(const fmm_params *P, int mesh, int64_t n64, const double *pos, con
 // PM on the particles of a built tree (Morton order, already wrapped and checked), enqueued on
 // st.  The plan's buffers are the next call's once `done` has passed, so the host lock covers
 // the launches only: hybrid steps of several threads share the mesh part one after the other,
-// and nothing else.
-int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st)
+// and nothing else.  *call receives the call's number for pm_tree_done (0: nothing launched).
+int pm_forces_tree(const fmm_params *P, int mesh, fmm_tree *t, double *acc, hipStream_t st, uint64_t *call)
 {
+    static uint64_t calls = 0;  // under g_pm_mu
+    *call = 0;
     if (mesh < 8 || mesh > 1024) return set_error(FMM_ERR_ARG, "mesh must be in [8, 1024]");
     if (t->n == 0) return 0;
     PMPlan *pl;
     if (int rc = pm_plan(mesh, &pl)) return rc;
     std::lock_guard<std::mutex> lk(g_pm_mu);
-    if (int rc = hip_check(hipStreamWaitEvent(st, pl->done, 0), "pm event wait")) return rc;
+    if (int rc = pm_wait(pl, st)) return rc;
     const int rc = pm_run(pl, P, mesh, (int)t->n,
                           MortonOrder{ptr<double>(t->xs), ptr<double>(t->ys), ptr<double>(t->zs), ptr<double>(t->ms),
                                       ptr<int>(t->perm)},
                           ptr<uint64_t>(t->keys[t->sorted]), true, acc, st);
-    const int rc_done = hip_check(hipEventRecord(pl->done, st), "pm event");  // after an error too
+    *call = pl->behind = ++calls;  // after an error too
+    const int rc_done = hip_check(hipEventRecord(pl->done, st), "pm event");
     return rc ? rc : rc_done;
+}
+
+// At a hybrid step's end, when its mesh part has long ended: the next call need not wait for it
+// on the device (a wait for an event of another stream costs some 10 us).
+int pm_tree_done(int mesh, uint64_t call)
+{
+    PMPlan *pl;
+    if (int rc = pm_plan(mesh, &pl)) return rc;
+    {
+        std::lock_guard<std::mutex> lk(g_pm_mu);
+        if (pl->behind != call) return 0;  // a later call waits for this one
+    }
+    if (int rc = hip_check(hipEventSynchronize(pl->done), "pm")) return rc;
+    std::lock_guard<std::mutex> lk(g_pm_mu);
+    if (pl->behind == call) pl->behind = 0;
+    return 0;
 }
 
 int add_into(double *acc, const double *other, int64_t n3, hipStream_t st)

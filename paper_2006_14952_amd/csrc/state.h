@@ -99,6 +99,7 @@ struct fmm_tree {
     // second stream (default priority) for stages independent of the caller's stream
     hipStream_t aux = nullptr;
     hipEvent_t dep[4]{};
+    uint64_t pm_call = 0;                   // hybrid step: the long-range part's number
     hipEvent_t bev = nullptr;               // tree build: its sizes are in t->host
     // traversal: the lists of level l's sinks are complete (lev); P2P launch of level l (timing)
     hipEvent_t lev[hfmm::kMaxLevel + 1]{}, p2p_t0[hfmm::kMaxLevel + 1]{}, p2p_t1[hfmm::kMaxLevel + 1]{};

@@ -98,7 +98,7 @@ def err_stats(e):
 def p2p_source_sha():
     """Hash of the P2P kernel's sources: stored traffic counters are used only while it holds."""
     h = hashlib.sha256()
-    for f in ("p2p.hip",):
+    for f in ("p2p.hip", "p2p_law.h"):
         with open(os.path.join(ROOT, "paper_2006_14952_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

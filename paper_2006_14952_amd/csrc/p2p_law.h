@@ -20,8 +20,12 @@ namespace hfmm {
 // (law64_weight), S_0 - 1/r^3 is then exact within a few roundings of f_(1), and the rest, d T,
 // vanishes with d.  The terms that matter in T are positive, as all of S's Taylor series is.
 // Largest relative error of a pair's weight, any separation, against 80-bit arithmetic: 1.3e-15
-// at r_cut = 4.5 r_s, 2.3e-15 at 5 r_s; by erfc and exp 2.0e-15 and 2.4e-15; with S - 1/r^3
+// at r_cut = 4.5 r_s, 2.3e-15 at 5 r_s; by erfc and exp 2.0e-15 and 2.4e-15 (the means by ranges of
+// r: between 0.5 and 0.8 r_cut up to 1.45 and 2.0 times theirs, elsewhere below); with S - 1/r^3
 // formed from a polynomial over the whole range, 3 operations a pair less, 2.3e-14 and 1.9e-13.
+// Accelerations of 4096 particles against extended precision at 4.5 r_s (median, 99th percentile
+// of the relative error): uniform 1.9e-16 and 8.1e-16, clustered 1.5e-16 and 7.0e-16; by erfc and
+// exp on unshifted coordinates 2.4e-16 and 3.9e-15, 1.9e-16 and 3.0e-15.
 constexpr int kP2PPoly64Max = 22;
 struct P2PConst64 {
     double c[kP2PPoly64Max];

@@ -89,10 +89,6 @@ static int pm_plan(int mesh, PMPlan **out)
     }
     PMPlan *p = new PMPlan();
     p->mesh = mesh;
-    if (hipEventCreateWithFlags(&p->done, hipEventDisableTiming) != hipSuccess) {
-        delete p;
-        return set_error(FMM_ERR_HIP, "hipEventCreateWithFlags");
-    }
     if (hipfftPlan3d(&p->r2c, mesh, mesh, mesh, HIPFFT_D2Z) != HIPFFT_SUCCESS ||
         hipfftPlan3d(&p->c2r, mesh, mesh, mesh, HIPFFT_Z2D) != HIPFFT_SUCCESS) {
         delete p;
@@ -100,6 +96,7 @@ static int pm_plan(int mesh, PMPlan **out)
     }
     size_t nr = (size_t)mesh * mesh * mesh, nc = (size_t)mesh * mesh * (mesh / 2 + 1);
     int rc = grow(p->rho, nr * 8) | grow(p->rhok, nc * 16) | grow(p->work, nc * 16) | grow(p->amesh, 3 * nr * 8);
+    if (!rc) rc = hip_check(hipEventCreateWithFlags(&p->done, hipEventDisableTiming), "pm event");
     if (rc) {
         delete p;
         return rc;

@@ -677,9 +677,9 @@ __device__ __forceinline__ void p2p_leaf_wide(const P2PArgs &a, const P2PLaw<F64
 // (a load under its own branch waited for the one before it, and the sink's own load for all
 // of them: 300,007 particles, polynomial split, step 3.50 -> 3.33 ms; 2M 8.13 -> 8.01 ms; 64-box
 // forest 11.77 -> 11.46 ms).
-// FP64 form: bound by FP64 issue, 51 vector operations a pair with 19 coefficients (43 of them
-// FP64; the cancelling form of the law takes 48: 262,144 clustered step 1.96 against 2.00 ms, on
-// another box 2.00 against 2.08) against well over 200 of erfc, exp, the square root and the division, on the pairs the box
+// FP64 form: bound by FP64 issue, 49 vector operations a pair with 19 coefficients (41 of them
+// FP64; the cancelling form of the law takes 48: 262,144 clustered step 1.73 ms with either, a
+// uniform box that is P2P nearly alone 1.18 against 1.23) against well over 200 of erfc, exp, the square root and the division, on the pairs the box
 // tests leave (62% of the listed ones on the 2M box) at four waves per SIMD instead of three:
 // uniform 32^3 step 1.21 -> 0.83 ms, 262,144 clustered step 9.0 -> 4.5 ms with one wave per leaf.
 template <bool F64, bool POLY, int NPC, int CHUNK>

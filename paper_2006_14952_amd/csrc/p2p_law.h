@@ -16,17 +16,18 @@ namespace hfmm {
 // cutoff, with d = r_cut^2 - r^2 >= 0:
 //   S = S_0 + d T(d),  T = sum c_k d^k, k < ncoef (19 or 22; the polynomial split: 1)
 // Near the cutoff S and 1/r^3 agree to one part in 1/h, h = r^3 |f_(1)| (57 at 4.5 r_s, 170 at
-// 5 r_s).  So S_0 is held to twice the precision, 1/r^3 is formed as y^3 plus its rounding
-// (law64_weight), S_0 - 1/r^3 is then exact within a few roundings of f_(1), and the rest, d T,
-// vanishes with d.  The terms that matter in T are positive, as all of S's Taylor series is.
-// Largest relative error of a pair's weight, any separation, against 80-bit arithmetic: 1.3e-15
-// at r_cut = 4.5 r_s, 2.3e-15 at 5 r_s; by erfc and exp 2.0e-15 and 2.4e-15 (the means by ranges of
-// r: between 0.5 and 0.8 r_cut up to 1.45 and 2.0 times theirs, elsewhere below); with S - 1/r^3
-// formed from a polynomial over the whole range, 3 operations a pair less, 2.3e-14 and 1.9e-13.
+// 5 r_s).  So S_0 is held to twice the precision, S_0 - 1/r^3 is formed from the exact cube of an
+// estimate and its correction (law64_weight), good to a few roundings of f_(1), and the rest,
+// d T, vanishes with d.  The terms that matter in T are positive, as all of S's Taylor series is.
+// Largest relative error of a pair's weight, any separation, against 80-bit arithmetic: 1.4e-15
+// at r_cut = 4.5 r_s, 2.3e-15 at 5 r_s; by erfc and exp 2.0e-15 and 2.4e-15 (the means by tenths of
+// r_cut: up to 1.33 times theirs between 0.6 and 0.9, at 5 r_s 2.0 times between 0.5 and 0.8, and
+// below them elsewhere); with S - 1/r^3
+// formed from a polynomial over the whole range, an operation a pair less, 2.3e-14 and 1.9e-13.
 // Accelerations of 4096 particles against extended precision at 4.5 r_s (median, 99th percentile
-// of the relative error): uniform 1.9e-16 and 8.1e-16, clustered 1.5e-16 and 7.0e-16; by erfc and
+// of the relative error): uniform 1.9e-16 and 8.0e-16, clustered 1.6e-16 and 7.4e-16; by erfc and
 // exp on unshifted coordinates 2.4e-16 and 3.9e-15, 1.9e-16 and 3.0e-15.
-constexpr int kP2PPoly64Max = 22;
+constexpr int kLawShort = 19, kP2PPoly64Max = 22;
 struct P2PConst64 {
     double c[kP2PPoly64Max];
     double s0, s0_lo;  // S_0 and what FP64 leaves of it
@@ -41,9 +42,11 @@ struct P2PConst64 {
 };
 
 // One pair of the FP64 form: the weight m f_(1)(r), zero outside 0 < r^2 < r_cut^2.  y: an
-// estimate of 1/r to about 23 bits.  It is cut to 26 bits, so that y^2, the low part of y^3 and
-// the residual e = 1 - r^2 y^2 are exact to far below FP64's last place, and
-// 1/r^3 = y^3 (1 - e)^(-3/2).  The self pair's NaN is dropped by the select.
+// estimate of 1/r to about 23 bits.  It is cut to 26 bits, so that y^2 and the residual
+// e = 1 - r^2 y^2 are exact to far below FP64's last place, and 1/r^3 = y^3 (1 - e)^(-3/2).
+// S_0 - y^3 is rounded once with 19 coefficients, two operations a pair less than the exact form
+// that 22 need (3.5e-15 otherwise at 5 r_s) and the polynomial split, whose force vanishes with
+// d^2.  The self pair's NaN is dropped by the select.
 template <int NPC> HFMM_HD double law64_weight(const P2PConst64 &k, double r2, double m, double y)
 {
     const bool in = r2 > 0.0 && r2 < k.rc2;
@@ -56,14 +59,20 @@ template <int NPC> HFMM_HD double law64_weight(const P2PConst64 &k, double r2, d
         memcpy(&b, &y, 8);
         b &= ~0x7ffffffll;
         memcpy(&y, &b, 8);
-        // y3 by fma: a product would be contracted into s0 - y3, which needs the rounded y3
-        const double y2 = y * y, y3 = fma(y2, y, 0.0), lo = fma(y2, y, -y3), e = fma(-r2, y2, 1.0);
-        const double q = fma(1.875, e, 1.5) * e;
+        const double y2 = y * y, e = fma(-r2, y2, 1.0), q = fma(1.875, e, 1.5) * e;
         const double d = k.rc2 - r2;
         double T = k.c[NPC - 1];
 #pragma unroll
         for (int c = NPC - 2; c >= 0; --c) T = fma(T, d, k.c[c]);
-        const double f1 = fma(d, T, k.s0 - y3) + (fma(-y3, q, k.s0_lo) - lo);
+        double f1;
+        if constexpr (NPC == kLawShort) {
+            f1 = fma(d, T, fma(-y2, y, k.s0)) + fma(-(y2 * y), q, k.s0_lo);
+        } else {
+            // the rounded y^3 (an fma: a product would be contracted into the difference, which is
+            // then exact near the cutoff) and what the rounding left
+            const double y3 = fma(y2, y, 0.0), lo = fma(y2, y, -y3);
+            f1 = fma(d, T, k.s0 - y3) + (fma(-y3, q, k.s0_lo) - lo);
+        }
         return in ? m * f1 : 0.0;
     }
 }
@@ -73,7 +82,7 @@ template <int NPC> HFMM_HD double law64_weight(const P2PConst64 &k, double r2, d
 // 5.366 (22).  The lines lie between the ratios in use, whose last bits vary with r_s.  No fit
 // beyond the second: S - S_0 then outweighs f_(1) so far that its roundings pass those of
 // erfc and exp.
-inline int law64_ncoef(double ratio) { return ratio <= 4.55 ? 19 : ratio <= 5.05 ? 22 : 0; }
+inline int law64_ncoef(double ratio) { return ratio <= 4.55 ? kLawShort : ratio <= 5.05 ? kP2PPoly64Max : 0; }
 
 // S = 4/sqrt(pi) int_0^1 y^2 exp(-v y^2) dy, v = r^2 / (4 r_s^2), about v0 in extended
 // precision: S = s0 + x sum T[k] x^k, x = 1 - v / v0 in [0, 1].  The Taylor coefficients
